@@ -98,12 +98,64 @@ __device__ inline cx<R> ldc(const cx<R> *p) { return *p; }
 template <typename R>
 __device__ inline void stc(cx<R> *p, cx<R> v) { *p = v; }
 
-// Wavefront-wide sum (64 lanes) with DPP/shuffle via __shfl_xor.
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// Lane exchanges on the vector unit (DPP row operations, permlane swaps)
+// instead of ds_bpermute: a 64-lane sum takes 6 steps of a few cycles each,
+// where every __shfl_xor step is a round trip through the LDS crossbar.
+template <int CTRL>
+__device__ __forceinline__ int dpp_mov(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double v) {
+  return __hiloint2double(dpp_mov<CTRL>(__double2hiint(v)), dpp_mov<CTRL>(__double2loint(v)));
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v) { return __int_as_float(dpp_mov<CTRL>(__float_as_int(v))); }
+
+// Sum over each row of 16 lanes, in every lane of the row.
+template <typename R>
+__device__ __forceinline__ R row16_sum(R v) {
+  v += dpp_mov<0xB1>(v);     // quad_perm [1,0,3,2]
+  v += dpp_mov<0x4E>(v);     // quad_perm [2,3,0,1]
+  v += dpp_mov<0x141>(v);    // row_half_mirror
+  v += dpp_mov<0x140>(v);    // row_mirror
   return v;
 }
+
+// Sum over the four rows of lanes (lanes l, l ^ 16, l ^ 32, l ^ 48), in every lane.
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ void swap16(int v, int &a, int &b) {
+  const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+  a = (int)r[0]; b = (int)r[1];
+}
+__device__ __forceinline__ void swap32(int v, int &a, int &b) {
+  const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+  a = (int)r[0]; b = (int)r[1];
+}
+#else
+__device__ inline void swap16(int v, int &a, int &b) { a = b = v; }
+__device__ inline void swap32(int v, int &a, int &b) { a = b = v; }
+#endif
+__device__ __forceinline__ double rows_sum(double v) {
+  int h0, h1, l0, l1;
+  swap16(__double2hiint(v), h0, h1);
+  swap16(__double2loint(v), l0, l1);
+  v = __hiloint2double(h0, l0) + __hiloint2double(h1, l1);
+  swap32(__double2hiint(v), h0, h1);
+  swap32(__double2loint(v), l0, l1);
+  return __hiloint2double(h0, l0) + __hiloint2double(h1, l1);
+}
+__device__ __forceinline__ float rows_sum(float v) {
+  int a, b;
+  swap16(__float_as_int(v), a, b);
+  v = __int_as_float(a) + __int_as_float(b);
+  swap32(__float_as_int(v), a, b);
+  return __int_as_float(a) + __int_as_float(b);
+}
+
+// Wavefront-wide sum (all 64 lanes active), the same value in every lane.
+__device__ __forceinline__ double wave_sum(double v) { return rows_sum(row16_sum(v)); }
+__device__ __forceinline__ float wave_sum(float v) { return rows_sum(row16_sum(v)); }
 __device__ inline double wave_max(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));

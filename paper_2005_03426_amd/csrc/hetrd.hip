@@ -14,11 +14,24 @@
 // After the panel the trailing matrix takes one rank-2k update
 // A -= [V W] [W V]^H on the matrix cores (lower triangle only).
 //
-// Per column the row-parallel kernels are: reflector (scale x), HEMV over
-// the lower trailing triangle, the panel corrections W^H v / V^H v, the
-// reduction of the partials into w0, and the final w together with the
-// update of the next panel column.  All sums are over fixed partitions in
-// fixed order (deterministic).
+// Per column two launches (the order of the reduction is a chain of n - 1
+// columns, so below a few thousand rows its time is launches and dependent
+// memory round trips, not bytes):
+//   ht_column: every workgroup derives (beta, tau, scale) from the raw column
+//     x and its norm partials, forms the entries of v it needs from x, and
+//     does its share of A v over the lower trailing triangle, of v^H A v, of
+//     the panel products W^H v / V^H v, or stores v;
+//   ht_finish: u from the partials.  With x1 = W^H v, x2 = V^H v,
+//     v^H u = v^H A v - 2 Re(x2^H x1) =: g is real, so w = tau u - (|tau|^2 g
+//     / 2) v needs no further pass over the rows; the same launch updates
+//     column i+1 by the k+1 reflectors so far (w[i+1] formed in every
+//     workgroup) and leaves its norm partials.
+// Four launches per column (reflector, product, u, w with the next column)
+// took 18.5 us per column at order 82, 23 at 450 and 31.5 at 1715
+// (profiled); the two take 3.1 (all in the tail), 11.3 and 13.2.
+// The last HT_TAIL rows of every matrix (all of a smaller one) are reduced by
+// one workgroup in LDS (ht_tail).
+// All sums are over fixed partitions in fixed order (deterministic).
 //
 // Every kernel is a template over the scalar type R: R = double is the
 // complex128 path; R = float is the complex64 reduction of the precision
@@ -27,8 +40,7 @@
 //
 // Grouped execution: every kernel takes a device table of problems (HtProb)
 // and works on problem blockIdx.z, so one launch advances column i of every
-// matrix of a batch; a matrix whose reduction has finished (i >= n - 1) simply
-// exits.  Grids are sized for the largest matrix.  A single reduction is the
+// matrix of a batch; a matrix that has reached its tail simply exits.  Grids are sized for the largest matrix.  A single reduction is the
 // one-entry case.
 #include <vector>
 #include "common.h"
@@ -40,30 +52,26 @@
 namespace mmf {
 
 constexpr int HV_T = 64;        // HEMV tile
-constexpr int HV_CH = 8;        // interior tiles per HEMV workgroup (one block column strip)
-constexpr int RW = 256;         // rows per workgroup in row-parallel kernels
-constexpr int DOT_ROWS = 1024;  // rows per workgroup of the panel dot products
+constexpr int HV_CH = 8;        // most interior tiles per HEMV workgroup (one block column strip)
+constexpr int64_t HV_NT_BYTES = (int64_t)512 << 20;   // lower trailing triangle from which its tiles are read non-temporally
+constexpr int DOT_MIN = 256;    // fewest rows per wavefront of the panel dot products
+constexpr int HT_TAIL = 92;     // largest order of the LDS tail: 92 x 93 complex128 + partials = 156 KB
+constexpr int TAIL_THREADS = 1024;
 
-template <typename R>
-__device__ inline R block_sum256(R v, R *sh) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) sh[wv] = v;
-  __syncthreads();
-  return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+// First column of the tail: the panels before it are all full.
+__host__ __device__ inline int64_t ht_tail_start(int64_t n) {
+  return n <= HT_TAIL ? 0 : (n - HT_TAIL + HT_NB - 1) / HT_NB * HT_NB;
 }
 
 template <typename R>
 struct HtWs {
   cx<R> *P3;       // n x 3NB (ld n): [V | W | V]
+  cx<R> *x;        // mpad: the current column before it is scaled into v
   cx<R> *pdir;     // nbt x mpad: direct partial of block column lb for local row
-  cx<R> *ptrn;     // nbt x nchmax x 64: transposed partials (slot 0 diagonal/edge tiles)
+  cx<R> *ptrn;     // nbt x nchmax x 64: transposed partials (slots 0, 1: diagonal, edge tile)
   cx<R> *dots;     // gdot x 2NB
-  R *norms;        // grow partials
-  cx<R> *sparts;   // nbt partials
-  cx<R> *w0first;  // 1
+  R *norms;        // nbt partials
+  R *sparts;       // nbt x nchmax partials of v^H A v
   int64_t nbt, mpad, nchmax;
   size_t bytes;
 };
@@ -77,16 +85,15 @@ inline HtWs<R> hetrd_ws(int64_t n, void *base) {
   w.nbt = (n + HV_T - 1) / HV_T;
   if (w.nbt < 1) w.nbt = 1;
   w.mpad = w.nbt * HV_T;
-  w.nchmax = (w.nbt + HV_CH - 1) / HV_CH + 1;    // slot 0: diagonal/edge tiles
+  w.nchmax = w.nbt + 2;                          // one interior tile per workgroup at least
   w.P3 = cv.take<cx<R>>((size_t)n * 3 * HT_NB);
+  w.x = cv.take<cx<R>>((size_t)w.mpad);
   w.pdir = cv.take<cx<R>>((size_t)w.nbt * w.mpad);
   w.ptrn = cv.take<cx<R>>((size_t)w.nbt * w.nchmax * HV_T);
-  const int64_t gdot = (n + DOT_ROWS - 1) / DOT_ROWS + 1;
+  const int64_t gdot = (n + DOT_MIN - 1) / DOT_MIN + 1;
   w.dots = cv.take<cx<R>>((size_t)gdot * 2 * HT_NB);
-  const int64_t grow = (n + RW - 1) / RW + 1;
-  w.norms = cv.take<R>(grow);
-  w.sparts = cv.take<cx<R>>(w.nbt + 1);
-  w.w0first = cv.take<cx<R>>(4);
+  w.norms = cv.take<R>((size_t)w.nbt + 1);
+  w.sparts = cv.take<R>((size_t)w.nbt * w.nchmax);
   w.bytes = cv.used();
   return w;
 }
@@ -95,6 +102,29 @@ template <typename R>
 size_t hetrd_ws_bytes_t(int64_t n) { return hetrd_ws<R>(n, nullptr).bytes; }
 size_t hetrd_ws_bytes(int64_t n) { return hetrd_ws_bytes_t<double>(n) + 256; }
 
+// Split of one matrix's sums, from its own order and the panel alone (a
+// matrix gives the same bits alone and in any batch).
+// Interior tiles per workgroup of the panel at column p: at most 128
+// workgroups of single tiles, then strips of up to HV_CH (the next tile is
+// loaded during the current one).  Strips of eight at every order left 200 of
+// the 256 CUs idle at order 1715 (17.7 us per product against 6.9 for single
+// tiles).  Targets of 512 / 256 / 128 / 64 workgroups: order 1715 alone 31.0 /
+// 31.2 / 31.2 / 33.1 ms, 48 uneven matrices together, which fill the chip
+// anyway, 151 / 147 / 140 / 135 ms, order 5000 180 / 177 / 181 / 184 ms.
+__host__ __device__ inline int ht_strip(int64_t n, int64_t p) {
+  const int64_t nb = n / HV_T - (p + 1) / HV_T;
+  const int64_t want = (nb * (nb - 1) / 2 + 127) / 128;
+  return (int)(want < 1 ? 1 : (want > HV_CH ? HV_CH : want));
+}
+// Strip slots of the panel's widest block column.
+__host__ __device__ inline int ht_slots(int64_t n, int64_t i, int ch) {
+  const int64_t inner = n / HV_T - (i + 1) / HV_T - 1;
+  return 2 + (inner > 0 ? (int)((inner + ch - 1) / ch) : 0);
+}
+// Rows per wavefront of the panel products: one round of four loads per lane
+// while the partials stay few, longer chunks for long columns.
+__host__ __device__ inline int ht_dot_rows(int64_t n) { return n <= 8 * DOT_MIN ? DOT_MIN : 4 * DOT_MIN; }
+
 // one row of the problem table
 template <typename R>
 struct HtProb {
@@ -102,9 +132,8 @@ struct HtProb {
   cx<R> *A;
   double *d, *e;
   cx<R> *tau;
-  cx<R> *P3, *pdir, *ptrn, *dots;
-  R *norms;
-  cx<R> *sparts, *w0first;
+  cx<R> *P3, *x, *pdir, *ptrn, *dots;
+  R *norms, *sparts;
 };
 
 template <typename R>
@@ -113,116 +142,94 @@ inline HtProb<R> ht_prob(int64_t n, cx<R> *A, int64_t lda, double *d, double *e,
   HtProb<R> q;
   q.n = n; q.lda = lda; q.mpad = w.mpad; q.nchmax = w.nchmax;
   q.A = A; q.d = d; q.e = e; q.tau = tau;
-  q.P3 = w.P3; q.pdir = w.pdir; q.ptrn = w.ptrn; q.dots = w.dots;
-  q.norms = w.norms; q.sparts = w.sparts; q.w0first = w.w0first;
+  q.P3 = w.P3; q.x = w.x; q.pdir = w.pdir; q.ptrn = w.ptrn; q.dots = w.dots;
+  q.norms = w.norms; q.sparts = w.sparts;
   return q;
 }
 
 // ---------------------------------------------------------------- kernels
+// First column of a panel: x <- A[p:, p], d[p], and the partial norms of
+// x[p+2:] per 64-row block of the absolute grid (one wavefront each).
 template <typename R>
-__global__ void ht_zero_panel(const HtProb<R> *pr, int64_t p) {
+__global__ void __launch_bounds__(256) ht_colnorm(const HtProb<R> *pr, int64_t p) {
   const HtProb<R> &q = pr[blockIdx.z];
   const int64_t n = q.n;
-  const int64_t r = p + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n) return;
-  for (int c = 0; c < 3 * HT_NB; ++c) q.P3[r + c * n] = cmk<R>(0, 0);
+  if (p >= ht_tail_start(n)) return;
+  const int64_t blk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);     // local block
+  const int64_t r = (p / HV_T + blk) * HV_T + (threadIdx.x & 63);
+  if ((p / HV_T + blk) * HV_T >= n) return;                             // wavefront-uniform
+  cx<R> a = cmk<R>(0, 0);
+  if (r >= p && r < n) {
+    a = gload((const MMF_GLOBAL cx<R> *)q.A + r + p * q.lda);
+    ((MMF_GLOBAL cx<R> *)q.x)[r] = a;
+    if (r == p) q.d[p] = (double)a.re;
+  }
+  const R s = wave_sum(r >= p + 2 ? cabs2(a) : R(0));
+  if ((threadIdx.x & 63) == 0) q.norms[blk] = s;
 }
 
-// partial ||A[i+2:, i]||^2 (first column of a panel)
+// Householder scalars of a column (alpha, x) with |x|^2 = xn2: the real beta,
+// tau and scale = 1 / (alpha - beta) with v = (1, scale x).
 template <typename R>
-__global__ void __launch_bounds__(RW) ht_colnorm(const HtProb<R> *pr, int64_t i) {
-  __shared__ R sh[4];
-  const HtProb<R> &q = pr[blockIdx.z];
-  const int64_t n = q.n, lda = q.lda;
-  const cx<R> *A = q.A;
-  R *norms = q.norms;
-  if (i >= n - 1) return;
-  // only this matrix's partials (its norms buffer has that many entries)
-  if ((int64_t)blockIdx.x >= ((n - i - 2 > 0 ? n - i - 2 : 1) + RW - 1) / RW) return;
-  const int64_t r = i + 2 + (int64_t)blockIdx.x * RW + threadIdx.x;
-  R s = 0;
-  if (r < n) s = cabs2(A[r + i * lda]);
-  s = block_sum256(s, sh);
-  if (threadIdx.x == 0) norms[blockIdx.x] = s;
-}
-
-// Reflector of column i: every workgroup derives (beta, tau) from the norm
-// partials and scales its rows of x into v.
-template <typename R>
-__global__ void __launch_bounds__(RW) ht_reflector(const HtProb<R> *pr, int64_t p, int k) {
-  __shared__ R sh[4];
-  const HtProb<R> &q = pr[blockIdx.z];
-  const int64_t n = q.n, lda = q.lda, i = p + k;
-  if (i >= n - 1) return;
-  cx<R> *A = q.A;
-  cx<R> *P3 = q.P3;
-  const R *norms = q.norms;
-  double *d = q.d, *e = q.e;
-  cx<R> *tau = q.tau;
-  // norm partials come from ht_colnorm (first panel column) or ht_finish_w
-  const int gnorm = (int)((k == 0) ? (((n - p - 2 > 0 ? n - p - 2 : 1) + RW - 1) / RW) : ((n - i + RW - 1) / RW));
-  R xp = 0;
-  for (int g = threadIdx.x; g < gnorm; g += RW) xp += norms[g];
-  const R xn2 = block_sum256(xp, sh);
-  const cx<R> alpha = A[(i + 1) + i * lda];
-  R beta;
-  cx<R> t, scale;
+__device__ __forceinline__ void ht_scalars(cx<R> alpha, R xn2, R &beta, cx<R> &tau, cx<R> &scale) {
   if (xn2 == R(0) && alpha.im == R(0)) {
     beta = alpha.re;
-    t = cmk<R>(0, 0);
+    tau = cmk<R>(0, 0);
     scale = cmk<R>(0, 0);
   } else {
     const R nrm = sqrt(alpha.re * alpha.re + alpha.im * alpha.im + xn2);
     beta = alpha.re >= R(0) ? -nrm : nrm;
-    t = cmk<R>((beta - alpha.re) / beta, -alpha.im / beta);
-    // scale = 1 / (alpha - beta)
+    tau = cmk<R>((beta - alpha.re) / beta, -alpha.im / beta);
     const cx<R> den = cmk<R>(alpha.re - beta, alpha.im);
     const R q = den.re * den.re + den.im * den.im;
     scale = cmk<R>(den.re / q, -den.im / q);
   }
-  const int64_t r = i + 2 + (int64_t)blockIdx.x * RW + threadIdx.x;
-  if (r < n) {
-    const cx<R> v = cmul(A[r + i * lda], scale);
-    A[r + i * lda] = v;
-    P3[r + (int64_t)k * n] = v;
-    P3[r + (int64_t)(2 * HT_NB + k) * n] = v;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    P3[(i + 1) + (int64_t)k * n] = cmk<R>(1, 0);
-    P3[(i + 1) + (int64_t)(2 * HT_NB + k) * n] = cmk<R>(1, 0);
-    d[i] = (double)A[i + i * lda].re;
-    e[i] = (double)beta;
-    tau[i] = t;
-  }
+}
+
+// The same of column i from its norm partials (one per 64-row block from row i on), in every lane.
+template <typename R>
+__device__ __forceinline__ void ht_column_scalars(const HtProb<R> &q, int64_t i, R &beta, cx<R> &tau, cx<R> &scale) {
+  const MMF_GLOBAL R *norms = (const MMF_GLOBAL R *)q.norms;
+  const int cnt = (int)((q.n + HV_T - 1) / HV_T - i / HV_T);
+  const cx<R> alpha = gload((const MMF_GLOBAL cx<R> *)q.x + i + 1);
+  R s = 0;
+  for (int g = threadIdx.x & 63; g < cnt; g += 64) s += norms[g];
+  ht_scalars<R>(alpha, wave_sum(s), beta, tau, scale);
+}
+
+// v[r] of column i from the raw column (r < mpad)
+template <typename R>
+__device__ __forceinline__ cx<R> ht_v(const MMF_GLOBAL cx<R> *x, int64_t r, int64_t i, int64_t n, cx<R> scale) {
+  const cx<R> v = cmul(gload(x + r), scale);
+  return (r <= i || r >= n) ? cmk<R>(0, 0) : (r == i + 1 ? cmk<R>(1, 0) : v);
 }
 
 template <typename R> struct NtVec;
 template <> struct NtVec<double> { typedef double v __attribute__((ext_vector_type(2))); };
 template <> struct NtVec<float> { typedef float v __attribute__((ext_vector_type(2))); };
 
-// Panel corrections of the column's HEMV: for row chunk g,
-// dots[g*2NB + q] = sum_rows conj(W[:,q]) v (q < k) and
-// dots[g*2NB + NB + q] = sum_rows conj(V[:,q]) v over rows [i+1, n) of the
-// chunk (DOT_ROWS rows).  Run by extra workgroups of the HEMV launch: one
-// wavefront per product qq (lane l sums rows l, l + 64, ...; shuffle fold).
+// Panel products of column i for row chunk g (dr rows):
+// dots[g*2NB + q] = sum conj(W[:,q]) v and dots[g*2NB + NB + q] =
+// sum conj(V[:,q]) v (q < k) over its rows of [i+1, n).  One wavefront per
+// product qq (lane l sums rows l, l + 64, ...).
 template <typename R>
-__device__ void ht_dots_wave(const HtProb<R> &pq, int64_t i, int k, int g, int qq) {
+__device__ void ht_dots_wave(const HtProb<R> &pq, int64_t i, int k, int g, int qq, int dr) {
   const int64_t n = pq.n;
-  const MMF_GLOBAL cx<R> *P3 = (const MMF_GLOBAL cx<R> *)pq.P3;
   const int q = qq % k, which = qq / k;
-  const MMF_GLOBAL cx<R> *X = P3 + (int64_t)(which == 0 ? HT_NB + q : q) * n;
-  const MMF_GLOBAL cx<R> *v = P3 + (int64_t)k * n;
+  const MMF_GLOBAL cx<R> *X = (const MMF_GLOBAL cx<R> *)pq.P3 + (int64_t)(which == 0 ? HT_NB + q : q) * n;
+  const MMF_GLOBAL cx<R> *x = (const MMF_GLOBAL cx<R> *)pq.x;
+  R beta;
+  cx<R> tau, scale;
+  ht_column_scalars<R>(pq, i, beta, tau, scale);
   const int lane = threadIdx.x & 63;
-  const int64_t r0 = i + 1 + (int64_t)g * DOT_ROWS;
+  const int64_t r0 = i + 1 + (int64_t)g * dr;
   cx<R> s = cmk<R>(0, 0);
 #pragma unroll 4
-  for (int j = lane; j < DOT_ROWS; j += 64) {
+  for (int j = lane; j < dr; j += 64) {
     const int64_t r = r0 + j;
-    if (r < n) s = cadd(s, cmulc(X[r], v[r]));
+    if (r < n) s = cadd(s, cmulc(gload(X + r), ht_v<R>(x, r, i, n, scale)));
   }
-  R re = s.re, im = s.im;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) { re += __shfl_xor(re, o, 64); im += __shfl_xor(im, o, 64); }
+  const R re = wave_sum(s.re), im = wave_sum(s.im);
   if (lane == 0) ((MMF_GLOBAL cx<R> *)pq.dots)[(int64_t)g * 2 * HT_NB + which * HT_NB + q] = cmk<R>(re, im);
 }
 
@@ -230,296 +237,463 @@ __device__ void ht_dots_wave(const HtProb<R> &pq, int64_t i, int k, int g, int q
 // A_trail = A[i+1:, i+1:].  Tiles lie on the absolute 64 x 64 grid of A
 // (block b covers rows 64b .. 64b+63), so on a leading dimension divisible by
 // 8 every column segment a load touches starts on a 128-byte line; b0 is the
-// block holding row i+1 and local block lb = b - b0.
-//   blockIdx.y >= 1: interior tiles (block row > block column, all rows
-//     < n): chunk y-1 of HV_CH tiles of block column b0 + blockIdx.x.  The
-//     four wavefronts share every tile, wave w taking its columns
-//     16w .. 16w+15 (lane: rows rg + 16q, columns 16w + 4cg + j), so a lane
-//     holds 16 elements per tile; the next tile is loaded (non-temporal, no
-//     guards) while the current one is multiplied.  The direct product is
-//     summed over the waves through LDS once per tile and written as the
-//     partial of (block column, row); the conjugate-transposed product stays
-//     in registers over the strip.  Columns left of i+1 carry v = 0.
-//   blockIdx.y == 0: the diagonal tile of the block column and, when n is
-//     not a multiple of 64, its tile in the last (partial) block row, with
-//     every element masked (rows/columns in [i+1, n), lower triangle, real
-//     diagonal); lane = row, wave w = columns 16w .. 16w+15.
-template <typename R>
-__global__ void __launch_bounds__(256, 2) ht_hemv(const HtProb<R> *pr, int64_t i, int k, int64_t dot_slot) {
+// block holding row i+1 and local block lb = b - b0 = blockIdx.x.
+//   blockIdx.y == 0: the diagonal tile of the block column (masked: lower
+//     triangle, real diagonal); also stores v of these rows;
+//   blockIdx.y == 1: its tile in the last block row when that is partial;
+//   blockIdx.y in [2, dot_slot): interior tiles, chunk y-2 of `ch` tiles;
+//   blockIdx.y >= dot_slot: the panel products.
+// The four wavefronts share every tile, wave w taking its columns
+// 16w .. 16w+15 (lane: rows rg + 16q, columns 16w + 4cg + j), so a lane holds
+// 16 elements per tile; the next tile is loaded while the current one is
+// multiplied, and the first one before the column's scalars are known.  The
+// direct product is summed over the waves through LDS once per tile and
+// written as the partial of (block column, row); the conjugate-transposed
+// product stays in registers over the strip.  Columns left of i+1 carry v = 0.
+// Bound: HBM at large orders; below about 3000 rows, where the strips of one
+// tile leave no second tile to overlap with, one launch's dependent loads.
+// NT: the tiles are read non-temporally, so that a triangle far larger than
+// the 256 MB last-level cache does not sweep everything else out of it.  With
+// ordinary reads the reduction takes 26.7 ms against 28.5 at order 2048, 84.0
+// against 93.3 at 4000, 184.5 against 203.4 at 6000, 389.8 against 396.2 at
+// 8000, but 947.6 against 897.3 at 11000: NT above HV_NT_BYTES.
+template <typename R, bool NT>
+__global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t p, int k, int dot_slot) {
   typedef cx<R> C;
   typedef typename NtVec<R>::v nv;
-  __shared__ C vcol[HV_T];
   __shared__ C red[2][4][HV_T];
+  __shared__ R shs[4];
   const HtProb<R> &q = pr[blockIdx.z];
-  const int64_t n = q.n, lda = q.lda, mpad = q.mpad, nchmax = q.nchmax;
-  if (i >= n - 1) return;
+  const int64_t n = q.n, lda = q.lda, mpad = q.mpad, nchmax = q.nchmax, i = p + k;
+  if (p >= ht_tail_start(n)) return;
+  const int ch = ht_strip(n, p), dr = ht_dot_rows(n);
   const int64_t b0 = (i + 1) / HV_T;
   const int64_t nb = (n + HV_T - 1) / HV_T;        // absolute blocks
   const int64_t nfull = n / HV_T;                   // blocks entirely inside the matrix
   const int64_t lb = blockIdx.x;
   const int64_t bj = b0 + lb;
   if (bj >= nb) return;
-  const int64_t slot = blockIdx.y;
-  if (dot_slot >= 0 && slot >= dot_slot) {             // panel dot products of this column
-    const int qq = (int)(slot - dot_slot) * 4 + (threadIdx.x >> 6);
-    if ((int64_t)blockIdx.x < (n - i - 1 + DOT_ROWS - 1) / DOT_ROWS && qq < 2 * k)
-      ht_dots_wave(q, i, k, (int)blockIdx.x, qq);
-    return;
-  }
-  const int64_t first = bj + 1 + (slot - 1) * HV_CH;   // interior chunk's first block row
-  if (slot > 0 && first >= nfull) return;
-  const MMF_GLOBAL C *A = (const MMF_GLOBAL C *)q.A;
-  const MMF_GLOBAL C *v = (const MMF_GLOBAL C *)q.P3 + (int64_t)k * n;   // v[row], zero outside [i+1, n)
-  MMF_GLOBAL C *pdir = (MMF_GLOBAL C *)q.pdir, *ptrn = (MMF_GLOBAL C *)q.ptrn;
+  const int slot = blockIdx.y;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  if (tid < HV_T) {
-    const int64_t gc = bj * HV_T + tid;
-    vcol[tid] = (gc > i && gc < n) ? gload(v + gc) : cmk<R>(0, 0);
-  }
-  __syncthreads();
-  if (slot == 0) {
-    // ------------------------------------------------ guarded tiles
-    C tacc[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) tacc[j] = cmk<R>(0, 0);
-    const int ntile = (nb != nfull && bj < nb - 1) ? 2 : 1;
-    for (int tt = 0; tt < ntile; ++tt) {
-      const int64_t bi = (tt == 0) ? bj : nb - 1;
-      const int64_t row = bi * HV_T + lane;
-      const bool rok = row > i && row < n;
-      const C vr = rok ? gload(v + row) : cmk<R>(0, 0);
-      C d = cmk<R>(0, 0);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int64_t col = bj * HV_T + 16 * wave + j;
-        const bool ok = rok && col > i && row >= col;     // col < n follows from row < n
-        C a = ok ? gload(A + row + col * lda) : cmk<R>(0, 0);
-        const bool dg = (row == col);
-        if (dg) a.im = R(0);
-        d = cadd(d, cmul(a, vcol[16 * wave + j]));
-        if (!dg) tacc[j] = cadd(tacc[j], cmulc(a, vr));
-      }
-      red[0][wave][lane] = d;
-      __syncthreads();
-      if (tid < HV_T) {
-        const C s = cadd(cadd(red[0][0][tid], red[0][1][tid]), cadd(red[0][2][tid], red[0][3][tid]));
-        pdir[lb * mpad + (bi - b0) * HV_T + tid] = s;
-      }
-      __syncthreads();
-    }
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      R re = tacc[j].re, im = tacc[j].im;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) { re += __shfl_xor(re, o, 64); im += __shfl_xor(im, o, 64); }
-      if (lane == 0) ptrn[(lb * nchmax + 0) * HV_T + 16 * wave + j] = cmk<R>(re, im);
-    }
+  if (slot >= dot_slot) {                           // panel products of this column
+    const int qq = (slot - dot_slot) * 4 + wave;
+    if (lb < (n - i - 1 + dr - 1) / dr && qq < 2 * k) ht_dots_wave(q, i, k, (int)lb, qq, dr);
     return;
   }
-  // -------------------------------------------------- interior strip
-  const int64_t bi1 = (first + HV_CH < nfull) ? first + HV_CH : nfull;
+  const int64_t first = slot == 0 ? bj : (slot == 1 ? nb - 1 : bj + 1 + (int64_t)(slot - 2) * ch);
+  const bool idle = slot == 1 ? (nb == nfull || bj >= nb - 1) : (slot >= 2 && first >= nfull);
+  if (idle) {                                       // its partial of v^H A v is summed all the same
+    if (tid == 0 && slot < ht_slots(n, i, ch)) q.sparts[lb * nchmax + slot] = R(0);
+    return;
+  }
+  const MMF_GLOBAL C *A = (const MMF_GLOBAL C *)q.A;
+  const MMF_GLOBAL C *x = (const MMF_GLOBAL C *)q.x;
+  MMF_GLOBAL C *pdir = (MMF_GLOBAL C *)q.pdir, *ptrn = (MMF_GLOBAL C *)q.ptrn;
   const int rg = lane & 15, cg = lane >> 4;
   const int cb = 16 * wave + 4 * cg;
+  const int64_t col0 = bj * HV_T + cb;
   C vc[4], tacc[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) { vc[j] = vcol[cb + j]; tacc[j] = cmk<R>(0, 0); }
-  const MMF_GLOBAL C *colp = A + (bj * HV_T + cb) * lda + rg;
-  C b0t[4][4], b1t[4][4];
-  auto load = [&](C (&b)[4][4], int64_t bi) {
-    const MMF_GLOBAL C *p = colp + bi * HV_T;
+  R beta, gpart = 0;
+  C tau, scale;
+  if (slot < 2) {
+    // ------------------------------------------------ one masked tile
+    const int64_t row0 = first * HV_T + rg;
+    C a[4][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int qq = 0; qq < 4; ++qq) {
-        const nv x = __builtin_nontemporal_load(reinterpret_cast<const MMF_GLOBAL nv *>(p + 16 * qq + (int64_t)j * lda));
-        b[j][qq] = cmk<R>(x[0], x[1]);
+        const int64_t row = row0 + 16 * qq, col = col0 + j;
+        const bool ok = row < n && row >= col;
+        const C t = gload(A + (ok ? row + col * lda : 0));
+        a[j][qq] = cmk<R>(ok ? t.re : R(0), ok && row != col ? t.im : R(0));
       }
-  };
-  auto step = [&](C (&b)[4][4], C (&nxt)[4][4], int64_t bi, int t) {
-    if (bi + 1 < bi1) load(nxt, bi + 1);
-    __builtin_amdgcn_sched_barrier(0);
+    ht_column_scalars<R>(q, i, beta, tau, scale);
     C vr[4], dacc[4];
 #pragma unroll
-    for (int qq = 0; qq < 4; ++qq) { vr[qq] = v[bi * HV_T + rg + 16 * qq]; dacc[qq] = cmk<R>(0, 0); }
+    for (int qq = 0; qq < 4; ++qq) {
+      vr[qq] = ht_v<R>(x, row0 + 16 * qq, i, n, scale);
+      dacc[qq] = cmk<R>(0, 0);
+    }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j) {
+      vc[j] = ht_v<R>(x, col0 + j, i, n, scale);
+      tacc[j] = cmk<R>(0, 0);
 #pragma unroll
       for (int qq = 0; qq < 4; ++qq) {
-        const C a = b[j][qq];
-        // dacc += a vc ;  tacc += conj(a) vr
-        dacc[qq].re = fma(a.re, vc[j].re, dacc[qq].re);
-        dacc[qq].re = fma(-a.im, vc[j].im, dacc[qq].re);
-        dacc[qq].im = fma(a.re, vc[j].im, dacc[qq].im);
-        dacc[qq].im = fma(a.im, vc[j].re, dacc[qq].im);
-        tacc[j].re = fma(a.re, vr[qq].re, tacc[j].re);
-        tacc[j].re = fma(a.im, vr[qq].im, tacc[j].re);
-        tacc[j].im = fma(a.re, vr[qq].im, tacc[j].im);
-        tacc[j].im = fma(-a.im, vr[qq].re, tacc[j].im);
+        dacc[qq] = cadd(dacc[qq], cmul(a[j][qq], vc[j]));
+        const bool dg = row0 + 16 * qq == col0 + j;
+        const C t = cmulc(a[j][qq], vr[qq]);
+        tacc[j] = cadd(tacc[j], cmk<R>(dg ? R(0) : t.re, dg ? R(0) : t.im));
+        gpart += dg ? a[j][qq].re * cabs2(vr[qq]) : R(0);
       }
+    }
 #pragma unroll
     for (int qq = 0; qq < 4; ++qq) {
-      R re = dacc[qq].re, im = dacc[qq].im;
-      re += __shfl_xor(re, 16, 64); im += __shfl_xor(im, 16, 64);
-      re += __shfl_xor(re, 32, 64); im += __shfl_xor(im, 32, 64);
-      if (cg == 0) red[t & 1][wave][rg + 16 * qq] = cmk<R>(re, im);
+      const R re = rows_sum(dacc[qq].re), im = rows_sum(dacc[qq].im);
+      if (cg == 0) red[0][wave][rg + 16 * qq] = cmk<R>(re, im);
     }
     __syncthreads();
     if (tid < HV_T) {
-      const C s = cadd(cadd(red[t & 1][0][tid], red[t & 1][1][tid]), cadd(red[t & 1][2][tid], red[t & 1][3][tid]));
-      pdir[lb * mpad + (bi - b0) * HV_T + tid] = s;
+      pdir[lb * mpad + (first - b0) * HV_T + tid] =
+          cadd(cadd(red[0][0][tid], red[0][1][tid]), cadd(red[0][2][tid], red[0][3][tid]));
+      const int64_t r = bj * HV_T + tid;
+      if (slot == 0 && r > i && r < n) {            // this block's rows of v
+        const C v = ht_v<R>(x, r, i, n, scale);
+        MMF_GLOBAL C *P3 = (MMF_GLOBAL C *)q.P3;
+        ((MMF_GLOBAL C *)q.A)[r + i * lda] = v;
+        P3[r + (int64_t)k * n] = v;
+        P3[r + (int64_t)(2 * HT_NB + k) * n] = v;
+        if (r == i + 1) {
+          q.e[i] = (double)beta;
+          q.tau[i] = tau;
+        }
+      }
     }
-  };
-  load(b0t, first);
-  int t = 0;
-  for (int64_t bi = first; bi < bi1; bi += 2, t += 2) {
-    step(b0t, b1t, bi, t);
-    if (bi + 1 < bi1) step(b1t, b0t, bi + 1, t + 1);
+  } else {
+    // -------------------------------------------------- interior strip
+    const int64_t bi1 = (first + ch < nfull) ? first + ch : nfull;
+    const MMF_GLOBAL C *colp = A + col0 * lda + rg;
+    C b0t[4][4], b1t[4][4];
+    auto load = [&](C (&b)[4][4], int64_t bi) {
+      const MMF_GLOBAL C *p = colp + bi * HV_T;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int qq = 0; qq < 4; ++qq) {
+          const MMF_GLOBAL nv *at = reinterpret_cast<const MMF_GLOBAL nv *>(p + 16 * qq + (int64_t)j * lda);
+          const nv y = NT ? __builtin_nontemporal_load(at) : *at;
+          b[j][qq] = cmk<R>(y[0], y[1]);
+        }
+    };
+    auto step = [&](C (&b)[4][4], C (&nxt)[4][4], int64_t bi, int t) {
+      if (bi + 1 < bi1) load(nxt, bi + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      C vr[4], dacc[4];
+#pragma unroll
+      for (int qq = 0; qq < 4; ++qq) {
+        vr[qq] = cmul(gload(x + bi * HV_T + rg + 16 * qq), scale);   // rows of an interior tile are below i + 1
+        dacc[qq] = cmk<R>(0, 0);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int qq = 0; qq < 4; ++qq) {
+          const C a = b[j][qq];
+          // dacc += a vc ;  tacc += conj(a) vr
+          dacc[qq].re = fma(a.re, vc[j].re, dacc[qq].re);
+          dacc[qq].re = fma(-a.im, vc[j].im, dacc[qq].re);
+          dacc[qq].im = fma(a.re, vc[j].im, dacc[qq].im);
+          dacc[qq].im = fma(a.im, vc[j].re, dacc[qq].im);
+          tacc[j].re = fma(a.re, vr[qq].re, tacc[j].re);
+          tacc[j].re = fma(a.im, vr[qq].im, tacc[j].re);
+          tacc[j].im = fma(a.re, vr[qq].im, tacc[j].im);
+          tacc[j].im = fma(-a.im, vr[qq].re, tacc[j].im);
+        }
+#pragma unroll
+      for (int qq = 0; qq < 4; ++qq) {
+        const R re = rows_sum(dacc[qq].re), im = rows_sum(dacc[qq].im);
+        if (cg == 0) red[t & 1][wave][rg + 16 * qq] = cmk<R>(re, im);
+      }
+      __syncthreads();
+      if (tid < HV_T) {
+        const C s = cadd(cadd(red[t & 1][0][tid], red[t & 1][1][tid]), cadd(red[t & 1][2][tid], red[t & 1][3][tid]));
+        pdir[lb * mpad + (bi - b0) * HV_T + tid] = s;
+      }
+    };
+    load(b0t, first);
+    __builtin_amdgcn_sched_barrier(0);
+    ht_column_scalars<R>(q, i, beta, tau, scale);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { vc[j] = ht_v<R>(x, col0 + j, i, n, scale); tacc[j] = cmk<R>(0, 0); }
+    int t = 0;
+    for (int64_t bi = first; bi < bi1; bi += 2, t += 2) {
+      step(b0t, b1t, bi, t);
+      if (bi + 1 < bi1) step(b1t, b0t, bi + 1, t + 1);
+    }
   }
+  // transposed partial (the same in the 16 lanes of a column group) and this
+  // strip's part of v^H A v: 2 Re(v_J^H tacc), plus the real diagonal
+  R gt = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    R re = tacc[j].re, im = tacc[j].im;
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) { re += __shfl_xor(re, o, 64); im += __shfl_xor(im, o, 64); }
-    if (rg == 0) ptrn[(lb * nchmax + slot) * HV_T + cb + j] = cmk<R>(re, im);
+    const R re = row16_sum(tacc[j].re), im = row16_sum(tacc[j].im);
+    if (rg == j) ptrn[(lb * nchmax + slot) * HV_T + cb + j] = cmk<R>(re, im);
+    gt += vc[j].re * re + vc[j].im * im;
   }
+  const R gw = 2 * rows_sum(gt) + wave_sum(gpart);
+  if (lane == 0) shs[wave] = gw;
+  __syncthreads();
+  if (tid == 0) q.sparts[lb * nchmax + slot] = (shs[0] + shs[1]) + (shs[2] + shs[3]);
 }
 
-// w0 = tau (u - V x1 - W x2), with u assembled from the HEMV partials.
-// One workgroup per 64-row block; its four wavefronts split the partial
-// sums and the panel corrections, combined in LDS in fixed order.
+// Column i = p + k after ht_column: w = tau u - (|tau|^2 g / 2) v, and inside
+// the panel column i+1 updated by the k+1 reflectors so far.  One workgroup
+// per 64-row block; its four wavefronts split the partial sums and the panel
+// columns (each V, W entry is read once for both corrections), combined in
+// LDS in fixed order.  Wavefront 3 also forms w[i+1].
+// Latency bound: three dependent memory round trips (table, partials, stores)
+// and two barriers; everything that does not depend on the sums is loaded first.
 template <typename R>
-__global__ void __launch_bounds__(256) ht_finish_u(const HtProb<R> *pr, int64_t i, int k) {
+__global__ void __launch_bounds__(256) ht_finish(const HtProb<R> *pr, int64_t p, int k) {
   typedef cx<R> C;
-  __shared__ C x1[HT_NB], x2[HT_NB];
-  __shared__ C part[4][HV_T];
+  constexpr int QW = HT_NB / 4;
+  __shared__ C x1[HT_NB], x2[HT_NB], cw[HT_NB], cv[HT_NB];
+  __shared__ C part[4][HV_T], apart[4][HV_T];
   __shared__ R sh[4];
+  __shared__ C w1s;
   const HtProb<R> &pq = pr[blockIdx.z];
-  const int64_t n = pq.n, mpad = pq.mpad, nchmax = pq.nchmax;
-  if (i >= n - 1) return;
-  if ((int64_t)blockIdx.x >= (n + HV_T - 1) / HV_T - (i + 1) / HV_T) return;   // beyond this matrix's blocks
-  C *P3 = pq.P3;
-  const C *pdir = pq.pdir, *ptrn = pq.ptrn, *dots = pq.dots, *tau = pq.tau;
-  C *sparts = pq.sparts, *w0first = pq.w0first;
-  const int gdot = (int)((n - i - 1 + DOT_ROWS - 1) / DOT_ROWS);
+  const int64_t n = pq.n, lda = pq.lda, mpad = pq.mpad, nchmax = pq.nchmax, i = p + k;
+  if (p >= ht_tail_start(n)) return;
+  const int ch = ht_strip(n, p), dr = ht_dot_rows(n);
+  const int64_t b0 = (i + 1) / HV_T;
+  const int64_t nb = (n + HV_T - 1) / HV_T, nfull = n / HV_T;
+  const int64_t lbi = blockIdx.x;                   // local block of these rows
+  if (b0 + lbi >= nb) return;                       // beyond this matrix's blocks
+  MMF_GLOBAL C *P3 = (MMF_GLOBAL C *)pq.P3;
+  const MMF_GLOBAL C *pdir = (const MMF_GLOBAL C *)pq.pdir, *ptrn = (const MMF_GLOBAL C *)pq.ptrn;
+  const MMF_GLOBAL C *dots = (const MMF_GLOBAL C *)pq.dots;
+  const MMF_GLOBAL R *sparts = (const MMF_GLOBAL R *)pq.sparts;
+  const bool next = k + 1 < HT_NB;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  if (tid < 2 * k) {
-    const int q = tid % k, which = tid / k;
-    C s = cmk<R>(0, 0);
-    for (int g = 0; g < gdot; ++g) s = cadd(s, dots[(int64_t)g * 2 * HT_NB + which * HT_NB + q]);
-    if (which == 0) x1[q] = s; else x2[q] = s;
-  }
-  __syncthreads();
-  const int64_t b0 = (i + 1) / HV_T;
-  const int64_t nfull = n / HV_T;
-  const int64_t lbi = blockIdx.x;                   // local block of these rows
   const int64_t rho = (b0 + lbi) * HV_T + lane;     // absolute row
   const bool live = rho > i && rho < n;
-  C u = cmk<R>(0, 0);
-  if (live) {
-    {
-      // direct partials of block columns wave, wave + 4, ...: four independent
-      // accumulators keep four loads in flight, combined in fixed order
-      const C *pc = pdir + lbi * HV_T + lane;
-      C u0 = cmk<R>(0, 0), u1 = u0, u2 = u0, u3 = u0;
-      int64_t lb = wave;
-      for (; lb + 12 <= lbi; lb += 16) {
-        u0 = cadd(u0, pc[lb * mpad]);
-        u1 = cadd(u1, pc[(lb + 4) * mpad]);
-        u2 = cadd(u2, pc[(lb + 8) * mpad]);
-        u3 = cadd(u3, pc[(lb + 12) * mpad]);
-      }
-      for (; lb <= lbi; lb += 4) u0 = cadd(u0, pc[lb * mpad]);
-      u = cadd(cadd(u0, u1), cadd(u2, u3));
+  // ---- loads that wait for nothing else: V, W of this row, the partials
+  C vq[QW], wq[QW], u = cmk<R>(0, 0);
+#pragma unroll
+  for (int j = 0; j < QW; ++j) {
+    const int qc = wave + 4 * j;
+    vq[j] = wq[j] = cmk<R>(0, 0);
+    if (qc < k && live) {
+      vq[j] = gload(P3 + rho + (int64_t)qc * n);
+      wq[j] = gload(P3 + rho + (int64_t)(HT_NB + qc) * n);
     }
+  }
+  const C tau = gload((const MMF_GLOBAL C *)pq.tau + i);
+  C v = cmk<R>(0, 0), a = cmk<R>(0, 0);
+  if (wave == 0 && live) {
+    v = gload(P3 + rho + (int64_t)k * n);
+    if (next) a = gload((const MMF_GLOBAL C *)pq.A + rho + (i + 1) * lda);
+  }
+  {
+    // direct partials of block columns wave, wave + 4, ... (four independent
+    // accumulators), transposed partials of this block column's slots
+    const MMF_GLOBAL C *pc = pdir + lbi * HV_T + lane;
+    C u0 = cmk<R>(0, 0), u1 = u0, u2 = u0, u3 = u0;
+    int64_t lb = wave;
+    for (; lb + 12 <= lbi; lb += 16) {
+      u0 = cadd(u0, gload(pc + lb * mpad));
+      u1 = cadd(u1, gload(pc + (lb + 4) * mpad));
+      u2 = cadd(u2, gload(pc + (lb + 8) * mpad));
+      u3 = cadd(u3, gload(pc + (lb + 12) * mpad));
+    }
+    for (; lb <= lbi; lb += 4) u0 = cadd(u0, gload(pc + lb * mpad));
     const int64_t inner = nfull - (b0 + lbi) - 1;   // interior tiles below this block's diagonal
-    const int64_t nslot = 1 + (inner > 0 ? (inner + HV_CH - 1) / HV_CH : 0);
-    for (int64_t c = wave; c < nslot; c += 4) u = cadd(u, ptrn[(lbi * nchmax + c) * HV_T + lane]);
-    for (int q = wave; q < k; q += 4) {
-      u = csub(u, cmul(P3[rho + (int64_t)q * n], x1[q]));
-      u = csub(u, cmul(P3[rho + (int64_t)(HT_NB + q) * n], x2[q]));
+    const int nin = inner > 0 ? (int)((inner + ch - 1) / ch) : 0;
+    const bool edge = nb != nfull && b0 + lbi < nb - 1;
+    const MMF_GLOBAL C *pt = ptrn + lbi * nchmax * HV_T + lane;
+    if (wave == 1) u1 = cadd(u1, gload(pt));
+    if (wave == 2 && edge) u1 = cadd(u1, gload(pt + HV_T));
+#pragma unroll 4
+    for (int c = wave; c < nin; c += 4) u2 = cadd(u2, gload(pt + (int64_t)(c + 2) * HV_T));
+    u = cadd(cadd(u0, u1), cadd(u2, u3));
+  }
+  // ---- panel products, v^H A v (partials per thread, wavefront sums in sh)
+  const int gdot = (int)((n - i - 1 + dr - 1) / dr);
+  if (tid < 2 * k) {
+    const int qc = tid % k, which = tid / k;
+    C s = cmk<R>(0, 0);
+#pragma unroll 4
+    for (int g = 0; g < gdot; ++g) s = cadd(s, gload(dots + (int64_t)g * 2 * HT_NB + which * HT_NB + qc));
+    if (which == 0) x1[qc] = s; else x2[qc] = s;
+  }
+  {
+    const int nbl = (int)(nb - b0);
+    const int nsl = ht_slots(n, i, ch);
+    R s = 0;
+    for (int lb = tid >> 3; lb < nbl; lb += 32)
+      for (int c = tid & 7; c < nsl; c += 8) s += gload(sparts + lb * nchmax + c);
+    s = wave_sum(s);
+    if (lane == 0) sh[wave] = s;
+  }
+  // wavefront 3: row i+1 of the partials and of V, W
+  C r1 = cmk<R>(0, 0);
+  if (wave == 3) {
+    const int row = (int)(i + 1 - b0 * HV_T);
+    const int nin = ht_slots(n, i, ch) - 2;
+    const bool edge = nb != nfull && b0 < nb - 1;
+    for (int c = lane; c < nin; c += 64) r1 = cadd(r1, gload(ptrn + (int64_t)(c + 2) * HV_T + row));
+    if (lane == 0) r1 = cadd(r1, cadd(gload(pdir + row), gload(ptrn + row)));
+    if (lane == 1 && edge) r1 = cadd(r1, gload(ptrn + HV_T + row));
+    if (lane < k) {
+      cv[lane] = cconj(gload(P3 + (i + 1) + (int64_t)lane * n));
+      cw[lane] = cconj(gload(P3 + (i + 1) + (int64_t)(HT_NB + lane) * n));
+    }
+  }
+  __syncthreads();
+  // ---- alpha = -|tau|^2 g / 2 with g = v^H A v - 2 Re(x2^H x1)
+  R alpha = 0;
+  if (wave == 0 || wave == 3) {
+    const R xx = lane < k ? x2[lane].re * x1[lane].re + x2[lane].im * x1[lane].im : R(0);
+    const R g = ((sh[0] + sh[1]) + (sh[2] + sh[3])) - 2 * wave_sum(xx);
+    alpha = R(-0.5) * cabs2(tau) * g;
+  }
+  C as = cmk<R>(0, 0);
+#pragma unroll
+  for (int j = 0; j < QW; ++j) {
+    const int qc = wave + 4 * j;
+    if (qc < k) {
+      u = csub(u, cmul(vq[j], x1[qc]));
+      u = csub(u, cmul(wq[j], x2[qc]));
+      as = cadd(as, cmul(vq[j], cw[qc]));
+      as = cadd(as, cmul(wq[j], cv[qc]));
     }
   }
   part[wave][lane] = u;
-  __syncthreads();
-  C contrib = cmk<R>(0, 0);
-  if (wave == 0 && live) {
-    const C us = cadd(cadd(part[0][lane], part[1][lane]), cadd(part[2][lane], part[3][lane]));
-    const C w0 = cmul(tau[i], us);
-    P3[rho + (int64_t)(HT_NB + k) * n] = w0;
-    if (rho == i + 1) w0first[0] = w0;
-    contrib = cmulc(P3[rho + (int64_t)k * n], w0);   // conj(v) w0
-  }
-  const R sr = block_sum256(contrib.re, sh);
-  const R si = block_sum256(contrib.im, sh);
-  if (tid == 0) sparts[blockIdx.x] = cmk<R>(sr, si);
-}
-
-// w = w0 - (tau/2) conj(v^H w0) v; then, inside a panel, the update of the
-// next column i+1 by the k+1 reflectors so far and its partial norms.
-template <typename R>
-__global__ void __launch_bounds__(RW) ht_finish_w(const HtProb<R> *pr, int64_t p, int k) {
-  typedef cx<R> C;
-  __shared__ C cw[HT_NB], cv[HT_NB];
-  __shared__ R sh[4];
-  const HtProb<R> &pq = pr[blockIdx.z];
-  const int64_t n = pq.n, lda = pq.lda, i = p + k;
-  if (i >= n - 1) return;
-  if ((int64_t)blockIdx.x * RW >= n - i - 1) return;              // beyond this matrix's rows
-  const int kb = (int)((n - 1 - p < HT_NB) ? n - 1 - p : HT_NB);
-  const int next = (k + 1 < kb) ? 1 : 0;
-  const int gs = (int)((n + HV_T - 1) / HV_T - (i + 1) / HV_T);   // finish_u workgroups
-  C *A = pq.A, *P3 = pq.P3;
-  const C *sparts = pq.sparts, *tau = pq.tau, *w0first = pq.w0first;
-  R *norms = pq.norms;
-  const int tid = threadIdx.x;
-  C s;
-  {
-    C ps = cmk<R>(0, 0);
-    for (int g = tid; g < gs; g += RW) ps = cadd(ps, sparts[g]);
-    s.re = block_sum256(ps.re, sh);
-    s.im = block_sum256(ps.im, sh);
-  }
-  const C ti = tau[i];
-  const C alpha = cscale(cmul(ti, cconj(s)), R(-0.5));
-  if (next && tid <= k) {
-    const int64_t rr = i + 1;
-    C wq;
-    if (tid == k) wq = cadd(w0first[0], alpha);                   // v[i+1] = 1
-    else wq = P3[rr + (int64_t)(HT_NB + tid) * n];
-    cw[tid] = cconj(wq);
-    cv[tid] = cconj(P3[rr + (int64_t)tid * n]);
+  apart[wave][lane] = as;
+  if (wave == 3) {                                  // w[i+1] = tau u[i+1] + alpha (v[i+1] = 1)
+    if (lane < k) {
+      r1 = csub(r1, cmul(cconj(cv[lane]), x1[lane]));
+      r1 = csub(r1, cmul(cconj(cw[lane]), x2[lane]));
+    }
+    const C us = cmk<R>(wave_sum(r1.re), wave_sum(r1.im));
+    const C w0 = cmul(tau, us);
+    if (lane == 0) w1s = cmk<R>(w0.re + alpha, w0.im);
   }
   __syncthreads();
-  const int64_t rho = i + 1 + (int64_t)blockIdx.x * RW + tid;
+  if (wave != 0) return;
   R nrm = 0;
-  if (rho < n) {
-    const C v = P3[rho + (int64_t)k * n];
-    const C w = cadd(P3[rho + (int64_t)(HT_NB + k) * n], cmul(alpha, v));
+  if (live) {
+    const C us = cadd(cadd(part[0][lane], part[1][lane]), cadd(part[2][lane], part[3][lane]));
+    const C w1 = w1s;
+    C w = cadd(cmul(tau, us), cscale(v, alpha));
+    if (rho == i + 1) w = w1;
     P3[rho + (int64_t)(HT_NB + k) * n] = w;
-    if (rho == i + 1) A[rho + i * lda] = cmk<R>(1, 0);
     if (next) {
-      C a = A[rho + (i + 1) * lda];
-      for (int q = 0; q < k; ++q) {
-        a = csub(a, cmul(P3[rho + (int64_t)q * n], cw[q]));
-        a = csub(a, cmul(P3[rho + (int64_t)(HT_NB + q) * n], cv[q]));
-      }
-      a = csub(a, cmul(v, cw[k]));
-      a = csub(a, cmul(w, cv[k]));
-      A[rho + (i + 1) * lda] = a;
+      a = csub(a, cadd(cadd(apart[0][lane], apart[1][lane]), cadd(apart[2][lane], apart[3][lane])));
+      a = csub(a, cadd(cmul(v, cconj(w1)), w));     // conj(v[i+1]) = 1
+      ((MMF_GLOBAL C *)pq.x)[rho] = a;
+      if (rho == i + 1) pq.d[i + 1] = (double)a.re;
       if (rho >= i + 3) nrm = cabs2(a);
     }
   }
-  nrm = block_sum256(nrm, sh);
-  if (next && tid == 0) norms[blockIdx.x] = nrm;
+  if (next) {
+    nrm = wave_sum(nrm);
+    // ht_column counts the partials from the block of row i+1 on
+    if (lane == 0) pq.norms[lbi] = nrm;
+  }
 }
 
+// The last m <= HT_TAIL rows (columns ps .. n-1) of every matrix by one
+// workgroup: the Hermitian block in LDS with both triangles, per column the
+// product u = A v and the rank-2 update A -= v w^H + w v^H over all rows
+// (32-lane units: row group, column part).  The scalars are derived by every
+// wavefront for itself; three barriers per column.  A chain of m columns:
+// latency bound, 2.0 us per column (order 66) to 3.1 (82) against 11.3 for
+// the two launches at order 450.
 template <typename R>
-__global__ void ht_last_diag(const HtProb<R> *pr) {
+__global__ void __launch_bounds__(TAIL_THREADS) ht_tail(const HtProb<R> *pr) {
+  typedef cx<R> C;
+  extern __shared__ __attribute__((aligned(16))) char tail_smem[];
   const HtProb<R> &q = pr[blockIdx.z];
-  if (threadIdx.x == 0 && blockIdx.x == 0 && q.n > 0) q.d[q.n - 1] = (double)q.A[(q.n - 1) + (q.n - 1) * q.lda].re;
+  const int64_t n = q.n, lda = q.lda;
+  if (n <= 0) return;
+  const int64_t ps = ht_tail_start(n);
+  const int m = (int)(n - ps), ld = m | 1;
+  C *red = reinterpret_cast<C *>(tail_smem);       // TAIL_THREADS
+  C *vs = red + TAIL_THREADS, *ws = vs + 96, *S = ws + 96;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int unit = tid >> 5, l = tid & 31;
+  MMF_GLOBAL C *A = (MMF_GLOBAL C *)q.A + ps + ps * lda;
+  for (int c = unit; c < m; c += TAIL_THREADS / 32)
+    for (int r = c + l; r < m; r += 32) {
+      C t = gload(A + r + c * lda);
+      if (r == c) t.im = R(0);
+      S[c * ld + r] = t;
+      S[r * ld + c] = cconj(t);
+    }
+  __syncthreads();
+  for (int j = 0; j < m - 1; ++j) {
+    const int cnt = m - 1 - j;                      // rows j+1 .. m-1
+    const int G = (cnt + 31) >> 5;                  // row groups of 32 (1 .. 3)
+    const int part = G == 1 ? unit : (G == 2 ? unit >> 1 : unit / 3);
+    const int rgp = unit - part * G;
+    const int parts = G == 1 ? 32 : (G == 2 ? 16 : 10);
+    const int rr = rgp * 32 + l;                    // row relative to j+1
+    const bool act = rr < cnt && part < parts;
+    const C *xc = S + j * ld + j + 1;               // column j from row j+1
+    C *T = S + (j + 1) * ld + j + 1;                // trailing block
+    R xn = 0;
+    if (lane >= 1 && lane < cnt) xn = cabs2(xc[lane]);
+    if (lane + 64 < cnt) xn += cabs2(xc[lane + 64]);
+    const C alpha = xc[0];
+    R beta;
+    C tau, scale;
+    ht_scalars<R>(alpha, wave_sum(xn), beta, tau, scale);
+    // u = scale (A x'), x' = (alpha - beta, x): v = scale x'
+    C y = cmk<R>(0, 0);
+    if (act) {
+      for (int c = part; c < cnt; c += parts) {
+        C xv = xc[c];
+        if (c == 0) xv.re -= beta;
+        y = cadd(y, cmul(T[c * ld + rr], xv));
+      }
+    }
+    red[part * 32 * G + rr] = y;                    // unused units write past the summed parts
+    __syncthreads();
+    if (wave == 0) {
+      C u0 = cmk<R>(0, 0), u1 = u0, v0 = u0, v1 = u0;
+      if (lane < cnt) {
+        for (int g = 0; g < parts; ++g) u0 = cadd(u0, red[g * 32 * G + lane]);
+        u0 = cmul(scale, u0);
+        v0 = lane == 0 ? cmk<R>(1, 0) : cmul(scale, xc[lane]);
+      }
+      if (lane + 64 < cnt) {
+        for (int g = 0; g < parts; ++g) u1 = cadd(u1, red[g * 32 * G + lane + 64]);
+        u1 = cmul(scale, u1);
+        v1 = cmul(scale, xc[lane + 64]);
+      }
+      const R g = wave_sum(cmulc(v0, u0).re + cmulc(v1, u1).re);
+      const R h = R(-0.5) * cabs2(tau) * g;
+      if (lane < cnt) {
+        vs[lane] = v0;
+        ws[lane] = cadd(cmul(tau, u0), cscale(v0, h));
+        S[j * ld + j + 1 + lane] = v0;
+      }
+      if (lane + 64 < cnt) {
+        vs[lane + 64] = v1;
+        ws[lane + 64] = cadd(cmul(tau, u1), cscale(v1, h));
+        S[j * ld + j + 1 + lane + 64] = v1;
+      }
+      if (lane == 0) {
+        q.d[ps + j] = (double)S[j * ld + j].re;
+        q.e[ps + j] = (double)beta;
+        q.tau[ps + j] = tau;
+      }
+    }
+    __syncthreads();
+    if (act) {
+      const C vr = vs[rr], wr = ws[rr];
+      for (int c = part; c < cnt; c += parts) {
+        C t = T[c * ld + rr];
+        t = csub(t, cmul(vr, cconj(ws[c])));
+        t = csub(t, cmul(wr, cconj(vs[c])));
+        if (c == rr) t.im = R(0);
+        T[c * ld + rr] = t;
+      }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) q.d[n - 1] = (double)S[(m - 1) * ld + m - 1].re;
+  for (int c = unit; c < m - 1; c += TAIL_THREADS / 32)
+    for (int r = c + 1 + l; r < m; r += 32) A[r + c * lda] = S[c * ld + r];
 }
+
+// LDS bytes of the tail of order m
+template <typename R>
+inline size_t ht_tail_lds(int64_t m) { return sizeof(cx<R>) * (size_t)(TAIL_THREADS + 2 * 96 + m * (m | 1)); }
 
 // Trailing update A[q0:, q0:] -= [V W] [W V]^H (lower tiles) after the panel
 // starting at column p, for every matrix of the table.
@@ -528,12 +702,11 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) ht_her2k(const HtProb<R> *pr,
   __shared__ R lds[GEMM_LDS_ELEMS];
   const HtProb<R> &q = pr[blockIdx.z];
   const int64_t n = q.n;
-  if (p >= n - 1) return;
-  const int kb = (int)((n - 1 - p < HT_NB) ? n - 1 - p : HT_NB);
-  const int64_t q0 = p + kb;
+  if (p >= ht_tail_start(n)) return;
+  const int64_t q0 = p + HT_NB;
   const int64_t M = n - q0;
   const int64_t m0 = (int64_t)blockIdx.x * GT_M, n0 = (int64_t)blockIdx.y * GT_N;
-  if (M <= 0 || m0 >= M || n0 >= M || m0 + GT_M <= n0) return;
+  if (m0 >= M || n0 >= M || m0 + GT_M <= n0) return;
   GemmArgs g = gemm_args(M, M, 2 * HT_NB, q.P3 + q0, n, q.P3 + q0 + (int64_t)HT_NB * n, n,
                          q.A + q0 + q0 * q.lda, q.lda, -1.0, 0.0, 1.0, 0.0);
   g.lower = 1;
@@ -542,62 +715,62 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) ht_her2k(const HtProb<R> *pr,
 
 // ---------------------------------------------------------------- host
 // Grouped reduction of `count` matrices described by the device table pr
-// (orders nh[0..count) on the host, largest nmax).
+// (orders nh[0..count) on the host).
 template <typename R>
 int hetrd_grouped(const HtProb<R> *pr, const int64_t *nh, int64_t count, hipStream_t st) {
-  int64_t nmax = 0;
-  for (int64_t c = 0; c < count; ++c) nmax = nh[c] > nmax ? nh[c] : nmax;
+  int64_t nmax = 0, tail = 0;
+  for (int64_t c = 0; c < count; ++c) {
+    nmax = nh[c] > nmax ? nh[c] : nmax;
+    const int64_t m = nh[c] - ht_tail_start(nh[c]);
+    tail = m > tail ? m : tail;
+  }
   if (nmax <= 0 || count <= 0) return MMF_OK;
   const unsigned Z = (unsigned)count;
-  for (int64_t p = 0; p < nmax - 1; p += HT_NB) {
-    const int kb = (int)((nmax - 1 - p < HT_NB) ? nmax - 1 - p : HT_NB);
-    hipLaunchKernelGGL(ht_zero_panel<R>, dim3(cdiv(nmax - p, 256), 1, Z), dim3(256), 0, st, pr, p);
+  const int64_t ps = ht_tail_start(nmax);
+  for (int64_t p = 0; p < ps; p += HT_NB) {
+    int nslot = 2;                                   // most slots of any matrix in this panel
+    for (int64_t c = 0; c < count; ++c) {
+      if (p >= ht_tail_start(nh[c])) continue;
+      const int sl = ht_slots(nh[c], p, ht_strip(nh[c], p));
+      nslot = sl > nslot ? sl : nslot;
+    }
+    hipLaunchKernelGGL(ht_colnorm<R>, dim3(cdiv(cdiv(nmax, HV_T) - p / HV_T, 4), 1, Z), dim3(256), 0, st, pr, p);
     MMF_LAUNCH_CHECK();
-    const unsigned g0 = cdiv(nmax - p - 2 > 0 ? nmax - p - 2 : 1, RW);
-    hipLaunchKernelGGL(ht_colnorm<R>, dim3(g0, 1, Z), dim3(RW), 0, st, pr, p);
-    MMF_LAUNCH_CHECK();
-    for (int k = 0; k < kb; ++k) {
+    for (int k = 0; k < HT_NB; ++k) {
       const int64_t i = p + k;
-      const int64_t m = nmax - i - 1;
-      const unsigned gr = cdiv(nmax - i - 2 > 0 ? nmax - i - 2 : 1, RW);
-      hipLaunchKernelGGL(ht_reflector<R>, dim3(gr, 1, Z), dim3(RW), 0, st, pr, p, k);
-      MMF_LAUNCH_CHECK();
-      // anchored 64-blocks of the largest matrix: block columns b0 .. nb-1,
-      // slot 0 for the guarded tiles plus the interior chunks of column b0
-      const int64_t b0 = (i + 1) / HV_T;
-      const int64_t nbl = (nmax + HV_T - 1) / HV_T - b0;
-      const int64_t inner = nmax / HV_T - b0 - 1;
-      const int64_t nslot = 1 + (inner > 0 ? (inner + HV_CH - 1) / HV_CH : 0);
-      // extra rows of workgroups for the panel dots: four products per workgroup
-      const int64_t dot_slot = k > 0 ? nslot : -1;
-      const int64_t dot_rows = k > 0 ? (2 * k + 3) / 4 : 0;
+      // anchored 64-blocks of the largest matrix: block columns b0 .. nb-1
+      const int64_t nbl = (nmax + HV_T - 1) / HV_T - (i + 1) / HV_T;
+      const int dot_rows = (2 * k + 3) / 4;          // four panel products per workgroup
       const int ks = ktimer_begin(sizeof(R) == 8 ? "hemv" : "hemv_c64", st);
-      hipLaunchKernelGGL(ht_hemv<R>, dim3((unsigned)nbl, (unsigned)(nslot + dot_rows), Z), dim3(256), 0, st, pr,
-                         i, k, dot_slot);
+      const dim3 grid((unsigned)nbl, (unsigned)(nslot + dot_rows), Z);
+      if ((int64_t)sizeof(cx<R>) * (nmax - p) * (nmax - p) / 2 > HV_NT_BYTES)
+        hipLaunchKernelGGL((ht_column<R, true>), grid, dim3(256), 0, st, pr, p, k, nslot);
+      else
+        hipLaunchKernelGGL((ht_column<R, false>), grid, dim3(256), 0, st, pr, p, k, nslot);
       MMF_LAUNCH_CHECK();
       if (ks >= 0) {
         // algorithmic bytes: the lower triangle of every trailing matrix, read
         // once, plus the 2k panel columns and v read by the fused dot products
         double bytes = 0.0;
         for (int64_t c = 0; c < count; ++c) {
-          const double mc = (double)(nh[c] - i - 1);
+          const double mc = i < ht_tail_start(nh[c]) ? (double)(nh[c] - i - 1) : 0.0;
           if (mc > 0) bytes += 2.0 * sizeof(R) * (mc * (mc + 1.0) / 2.0 + (k > 0 ? (2.0 * k + 1.0) * mc : 0.0));
         }
         ktimer_end(ks, st, bytes);
       }
-      hipLaunchKernelGGL(ht_finish_u<R>, dim3((unsigned)nbl, 1, Z), dim3(256), 0, st, pr, i, k);
-      MMF_LAUNCH_CHECK();
-      hipLaunchKernelGGL(ht_finish_w<R>, dim3(cdiv(m, RW), 1, Z), dim3(RW), 0, st, pr, p, k);
+      hipLaunchKernelGGL(ht_finish<R>, dim3((unsigned)nbl, 1, Z), dim3(256), 0, st, pr, p, k);
       MMF_LAUNCH_CHECK();
     }
-    const int64_t q0 = p + kb;
-    if (q0 < nmax) {
-      const unsigned t = cdiv(nmax - q0, GT_M);
-      hipLaunchKernelGGL(ht_her2k<R>, dim3(t, t, Z), dim3(GEMM_THREADS), 0, st, pr, p);
-      MMF_LAUNCH_CHECK();
-    }
+    const unsigned t = cdiv(nmax - p - HT_NB, GT_M);
+    hipLaunchKernelGGL(ht_her2k<R>, dim3(t, t, Z), dim3(GEMM_THREADS), 0, st, pr, p);
+    MMF_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(ht_last_diag<R>, dim3(1, 1, Z), dim3(64), 0, st, pr);
+  // dynamic LDS above the default limit must be allowed per kernel (once)
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&ht_tail<R>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     (int)ht_tail_lds<R>(HT_TAIL));
+  if (attr != hipSuccess) return MMF_ERR_HIP;
+  hipLaunchKernelGGL(ht_tail<R>, dim3(1, 1, Z), dim3(TAIL_THREADS), ht_tail_lds<R>(tail), st, pr);
   MMF_LAUNCH_CHECK();
   return MMF_OK;
 }

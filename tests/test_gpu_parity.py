@@ -237,6 +237,48 @@ def test_hetrd_defining_identity(n):
     assert np.abs(Q @ T @ Q.conj().T - A).max() < 1e-13 * scale * max(1, n / 10)
 
 
+# edges of the LDS tail (order 92, panels of 32) and of the 64-row tiles, and
+# the first order whose strips hold two tiles (more than 512 interior tiles)
+@pytest.mark.parametrize("n", [91, 92, 93, 124, 125, 127, 128, 129, 156, 157, 191, 192, 193, 321])
+@pytest.mark.parametrize("pad", [0, 3])
+def test_hetrd_tail_and_tile_edges(n, pad):
+    torch, mmf = require_gpu()
+    rng = np.random.default_rng(31 * n + pad)
+    A = rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))
+    A = A + A.conj().T
+    A[n // 2 + 1:, :n // 3] = 0.0          # zero columns below the diagonal block: identity reflectors
+    A[:n // 3, n // 2 + 1:] = 0.0
+    log(f"hetrd edges n={n} pad={pad}")
+    buf = torch.full((n, n + pad), float("nan"), dtype=torch.complex128, device="cuda")
+    At = buf[:, :n]
+    At.copy_(to_dev_cm(torch, np.tril(A)))
+    d, e, tau = mmf.hetrd(At)
+    torch.cuda.synchronize()
+    refl = np.tril(from_dev_cm(At), -1)
+    Q, T = oracle.householder_tridiag_apply(d.cpu().numpy(), e.cpu().numpy()[:n - 1], refl,
+                                            tau.cpu().numpy()[:n - 1])
+    scale = np.abs(A).max()
+    assert np.abs(Q.conj().T @ Q - np.eye(n)).max() < 1e-13 * max(1, n / 10)
+    assert np.abs(Q @ T @ Q.conj().T - A).max() < 1e-13 * scale * max(1, n / 10)
+
+
+def test_hetrd_long_strips_keep_the_spectrum():
+    """Order 2200 (strips of two tiles, 1024-row panel products): trace, Frobenius
+    norm and eigenvalues of T against LAPACK's of A, to n eps |A| with a factor 10."""
+    torch, mmf = require_gpu()
+    n = 2200
+    rng = np.random.default_rng(5)
+    A = rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))
+    A = (A + A.conj().T) / 2
+    log(f"hetrd strips n={n}")
+    d, e, tau = mmf.hetrd(to_dev_cm(torch, A))
+    torch.cuda.synchronize()
+    from scipy.linalg import eigh_tridiagonal
+    w = eigh_tridiagonal(d.cpu().numpy(), e.cpu().numpy()[:n - 1], eigvals_only=True)
+    wo = oracle.eigvalsh(A)
+    assert np.abs(w - wo).max() <= 10 * n * np.finfo(float).eps * np.abs(wo).max()
+
+
 @pytest.mark.parametrize("n", [2, 5, 64, 65, 129, 130, 200, 257, 300])
 def test_unmtr_against_oracle_reflectors(n):
     torch, mmf = require_gpu()
