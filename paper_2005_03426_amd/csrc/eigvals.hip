@@ -49,8 +49,8 @@ inline EvWs ev_ws(int64_t n, bool c64, bool two, void *base) {
     w.Ac = nullptr;
     w.tau = cv.take<mmf_z>(N);
     w.AB = cv.take<mmf_z>(N * LDAB);
-    w.V2 = cv.take<mmf_z>(N * BW);
-    w.tau2 = cv.take<mmf_z>(N);
+    w.V2 = cv.take<mmf_z>(N * 2 * BW);
+    w.tau2 = cv.take<mmf_z>(2 * N);
     w.stage_bytes = he2hb_ws_bytes(n);
   } else {
     w.Ac = nullptr;

@@ -16,8 +16,7 @@
 // [r0, r0 + BW) and rows up to r0 + 2 BW - 1: the band array keeps 2 BW rows.
 // Tasks (s, k) and (s + 1, k - 2) touch disjoint columns, and every task reads
 // only columns finished by earlier ones, so step t runs all tasks with
-// k = t - 2 s at once (one workgroup each, blocks in LDS) and reproduces the
-// sequential order exactly.
+// k = t - 2 s at once and reproduces the sequential order exactly.
 //
 // Back-transformation Phi = Q2 Z with Q2 = prod_s prod_k H_{s,k}: reflectors of
 // one sweep commute (disjoint rows), and H_{s,k} only has to precede
@@ -44,14 +43,22 @@ struct HsProb {
 };
 
 // ---------------------------------------------------------------- chase
-constexpr int CH_THREADS = 512;           // threads per chase task (8 wavefronts)
-constexpr int CH_Q = CH_THREADS / 64;     // row / column groups of the block products
-constexpr int CH_W = BW / CH_Q;           // entries per group
+constexpr int CH_THREADS = 512;           // threads per workgroup (8 wavefronts)
+constexpr int CH_Q = CH_THREADS / 64;     // column groups of a block, one wavefront each
+constexpr int CH_W = BW / CH_Q;           // columns per group
+
+// Value of lane u, in every lane (u uniform).
+__device__ __forceinline__ double lane_get(double v, int u) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), u),
+                          __builtin_amdgcn_readlane(__double2loint(v), u));
+}
+__device__ __forceinline__ cd lane_get(cd v, int u) { return cmake(lane_get(v.re, u), lane_get(v.im, u)); }
+
 // Householder vector of x held by the 64 lanes of one wavefront (lane i: x_i,
 // len <= BW entries): H^H x = beta e0, beta real, v_0 = 1.  The identity
 // (tau = 0) when x is already real e0.
 __device__ inline cd wave_larfg(cd xi, int i, int len, cd &tau, double &beta) {
-  const double are = __shfl(xi.re, 0, 64), aim = __shfl(xi.im, 0, 64);
+  const double are = lane_get(xi.re, 0), aim = lane_get(xi.im, 0);
   const double xn2 = wave_sum((i >= 1 && i < len) ? cabs2(xi) : 0.0);
   tau = cmake(0.0, 0.0);
   beta = are;
@@ -66,6 +73,35 @@ __device__ inline cd wave_larfg(cd xi, int i, int len, cd &tau, double &beta) {
   return (i < len) ? cmul(xi, scale) : cmake(0.0, 0.0);
 }
 
+// Sums over the 64 lanes of the eight complex numbers p[0 .. 7] of every lane:
+// halves and rows of lanes are folded pairwise with permlane swaps (two values
+// share the lanes after each fold), the last 16 lanes by DPP; 21 double adds
+// instead of 96.  On return row rw (16 lanes) of w[m] holds, in all its lanes,
+// the real (rw < 2) or imaginary part of the sum of p[m + 4 (rw & 1)].
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ double fold32(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ double fold16(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+#else
+__device__ inline double fold32(double a, double b) { return a + b; }
+__device__ inline double fold16(double a, double b) { return a + b; }
+#endif
+__device__ __forceinline__ void wave_sum8(const cd (&p)[CH_W], double (&w)[4]) {
+  static_assert(CH_W == 8, "eight columns per wavefront");
+  double t[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) t[c] = fold32(p[c].re, p[c].im);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) w[m] = row16_sum(fold16(t[m], t[m + 4]));
+}
+
 // Tasks of step t for a problem of order n: sweeps smin .. smax (none when
 // smin > smax).
 __host__ __device__ inline void hb_step_range(int64_t n, int64_t t, int64_t &smin, int64_t &smax) {
@@ -77,204 +113,26 @@ __host__ __device__ inline void hb_step_range(int64_t n, int64_t t, int64_t &smi
   smin = num > 0 ? (num + den - 1) / den : 0;
 }
 
-// LDS of one chase task (the blocks D_k, E_k and the reflector vectors).
-struct ChaseSh {
-  cd D[BW][BW + 1];
-  cd E[BW][BW + 1];
-  cd vs[BW], v2[BW], wv[BW], zz[BW], red[CH_Q][BW], red2[CH_Q][BW];
-  cd tsh[2];
-  double bsh[2];
-};
-
-constexpr int CH_NE = BW * BW / CH_THREADS;   // block entries per thread
-
-// Global loads of the lower band of D_k and of the block E_k (task (s, k))
-// into registers: thread tid holds entries tid + CH_THREADS q2 (row entry % 64,
-// column entry / 64).
-__device__ __forceinline__ void chase_load(const HsProb &P, int64_t s, int64_t k, cd (&dreg)[CH_NE],
-                                           cd (&ereg)[CH_NE]) {
-  const int64_t n = P.n;
-  const int64_t r0 = s + 1 + k * BW;
-  const MMF_GLOBAL cd *AB = (const MMF_GLOBAL cd *)P.AB;
-  const int L = (int)((n - r0 < BW) ? n - r0 : BW);
-  const int64_t e0 = r0 + L;
-  const bool hasE = e0 <= n - 1;
-  const int Le = hasE ? (int)((n - e0 < BW) ? n - e0 : BW) : 0;
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int q2 = 0; q2 < CH_NE; ++q2) {
-    const int e = tid + CH_THREADS * q2, ii = e & 63, jj = e >> 6;
-    dreg[q2] = (ii >= jj && ii < L) ? gload(AB + (ii - jj) + (r0 + jj) * (int64_t)LDAB) : cmake(0.0, 0.0);
-    ereg[q2] = (hasE && ii < Le) ? gload(AB + (BW + ii - jj) + (r0 + jj) * (int64_t)LDAB) : cmake(0.0, 0.0);
-  }
-}
-
-// Task (s, k) of the chase of problem P, run by the whole workgroup.  Thread
-// (i, q) = (tid % 64, tid / 64); the scalar work (reflectors, sums over 64
-// entries) stays in wavefront 0.  With compact storage only the current
-// reflector of each sweep is kept (slot s).
-__device__ __forceinline__ void chase_task(const HsProb &P, int64_t s, int64_t k, ChaseSh &sh) {
-  cd (&D)[BW][BW + 1] = sh.D;
-  cd (&E)[BW][BW + 1] = sh.E;
-  cd *vs = sh.vs, *v2 = sh.v2, *wv = sh.wv, *zz = sh.zz;
-  cd (&red)[CH_Q][BW] = sh.red;
-  cd (&red2)[CH_Q][BW] = sh.red2;
-  cd *tsh = sh.tsh;
-  double *bsh = sh.bsh;
-  const int64_t n = P.n;
-  const int64_t r0 = s + 1 + k * BW;
-  MMF_GLOBAL cd *AB = (MMF_GLOBAL cd *)P.AB, *V2 = (MMF_GLOBAL cd *)P.V2, *tau2 = (MMF_GLOBAL cd *)P.tau2;
-  const int L = (int)((n - r0 < BW) ? n - r0 : BW);
-  const int tid = threadIdx.x, i = tid & 63, q = tid >> 6;
-  const int64_t voff = P.compact ? s * BW : hb_voff(n, k) + s * BW;
-  const int64_t toff = P.compact ? s : hb_voff(n, k) / BW + s;
-  const int64_t e0 = r0 + L;
-  const bool hasE = e0 <= n - 1;          // uniform (then L = BW)
-  const int Le = hasE ? (int)((n - e0 < BW) ? n - e0 : BW) : 0;
-
-  // ---- all global loads first: column s or the current reflector, the lower
-  // band of D_k, the block E_k
-  MMF_GLOBAL cd *col = AB + s * (int64_t)LDAB;
-  cd xi = cmake(0.0, 0.0);
-  if (q == 0) xi = (k == 0) ? ((i < L) ? gload(col + 1 + i) : cmake(0.0, 0.0)) : gload(V2 + voff + i);
-  constexpr int NE = CH_NE;
-  cd dreg[NE], ereg[NE];
-  chase_load(P, s, k, dreg, ereg);
-  // ---- current reflector H = H_{s,k} (wavefront 0)
-  if (q == 0) {
-    if (k == 0) {
-      cd tau;
-      double beta;
-      const cd v = wave_larfg(xi, i, L, tau, beta);
-      vs[i] = v;
-      V2[voff + i] = v;
-      if (i < L) col[1 + i] = (i == 0) ? cmake(beta, 0.0) : cmake(0.0, 0.0);
-      if (i == 0) { tau2[toff] = tau; tsh[0] = tau; }
-    } else {
-      vs[i] = xi;
-      if (i == 0) tsh[0] = tau2[toff];
-    }
-  }
-  // D is kept as the full Hermitian block (the upper triangle mirrored, the
-  // diagonal real, zero past L) so that y = D v needs no branch
-#pragma unroll
-  for (int q2 = 0; q2 < NE; ++q2) {
-    const int e = tid + CH_THREADS * q2, ii = e & 63, jj = e >> 6;
-    if (ii > jj) {
-      D[ii][jj] = dreg[q2];
-      D[jj][ii] = cconj(dreg[q2]);
-    } else if (ii == jj) {
-      D[ii][ii] = cmake(dreg[q2].re, 0.0);
-    }
-    E[ii][jj] = ereg[q2];
-  }
-  __syncthreads();
-  const cd tau = tsh[0];
-  // ---- y = D v, z = E v (row i, column group q); y_i = sum_j conj(D[j][i]) v_j
-  // reads consecutive entries across the wavefront
-  {
-    cd py = cmake(0.0, 0.0), pz = cmake(0.0, 0.0);
-#pragma unroll
-    for (int c = 0; c < CH_W; ++c) {
-      const int jj = CH_W * q + c;
-      const cd vj = vs[jj];
-      py = cadd(py, cmulc(D[jj][i], vj));
-      pz = cadd(pz, cmul(E[i][jj], vj));
-    }
-    red[q][i] = py;
-    red2[q][i] = pz;
-  }
-  __syncthreads();
-  // ---- w = tau y - (|tau|^2 gamma / 2) v, gamma = v^H y;  zz = tau z (wavefront 0)
-  if (q == 0) {
-    cd y = red[0][i], z = red2[0][i];
-#pragma unroll
-    for (int g = 1; g < CH_Q; ++g) { y = cadd(y, red[g][i]); z = cadd(z, red2[g][i]); }
-    const cd v = vs[i];
-    const double gamma = wave_sum(i < L ? cmulc(v, y).re : 0.0);
-    const double h = 0.5 * cabs2(tau) * gamma;
-    const cd ty = cmul(tau, y);
-    wv[i] = cmake(ty.re - h * v.re, ty.im - h * v.im);
-    zz[i] = cmul(tau, z);
-  }
-  __syncthreads();
-  // ---- D <- D - w v^H - v w^H (lower band to AB); E <- E - (tau z) v^H.
-  // The thread's entries of D_k and E_k are still in dreg / ereg (the LDS
-  // copy of D differs only in the imaginary part of the diagonal, which the
-  // update drops), its row is ii = i for every q2.
-  {
-    const cd wvi = wv[i], vsi = vs[i], zzi = zz[i];
-#pragma unroll
-    for (int q2 = 0; q2 < NE; ++q2) {
-      const int e = tid + CH_THREADS * q2, ii = e & 63, jj = e >> 6;
-      const cd vj = vs[jj];
-      if (ii >= jj && ii < L) {
-        cd d = csub(dreg[q2], cadd(cmul(wvi, cconj(vj)), cmul(vsi, cconj(wv[jj]))));
-        if (ii == jj) d.im = 0.0;
-        AB[(ii - jj) + (r0 + jj) * (int64_t)LDAB] = d;
-      }
-      if (hasE) {
-        ereg[q2] = csub(ereg[q2], cmul(zzi, cconj(vj)));
-        E[ii][jj] = ereg[q2];
-      }
-    }
-  }
-  if (!hasE) return;                      // uniform: no block below
-  __syncthreads();
-  // ---- H_{s,k+1} from the first column of E (wavefront 0)
-  if (q == 0) {
-    const cd x = (i < Le) ? E[i][0] : cmake(0.0, 0.0);
-    cd t1 = cmake(0.0, 0.0);
-    double b1 = x.re;
-    cd v = (i == 0) ? cmake(1.0, 0.0) : cmake(0.0, 0.0);
-    if (Le >= 2) v = wave_larfg(x, i, Le, t1, b1);
-    v2[i] = v;
-    if (i == 0) { tsh[1] = t1; bsh[0] = b1; }
-  }
-  __syncthreads();
-  const cd tau1 = tsh[1];
-  const double beta1 = bsh[0];
-  const bool active = (Le >= 2) && (tau1.re != 0.0 || tau1.im != 0.0);     // uniform
-  if (active) {
-    // u_j = v2^H E[:, j] (column j = i, row group q)
-    cd p = cmake(0.0, 0.0);
-#pragma unroll
-    for (int c = 0; c < CH_W; ++c) p = cadd(p, cmulc(v2[CH_W * q + c], E[CH_W * q + c][i]));
-    red[q][i] = p;
-    __syncthreads();
-    if (q == 0) {
-      cd u = red[0][i];
-#pragma unroll
-      for (int g = 1; g < CH_Q; ++g) u = cadd(u, red[g][i]);
-      wv[i] = cmulc(tau1, u);
-    }
-    __syncthreads();
-  }
-  {
-    const cd v2i = v2[i];
-#pragma unroll
-    for (int q2 = 0; q2 < NE; ++q2) {
-      const int e = tid + CH_THREADS * q2, ii = e & 63, jj = e >> 6;
-      if (ii < Le) {
-        cd x = ereg[q2];
-        if (active) {
-          if (jj == 0) x = (ii == 0) ? cmake(beta1, 0.0) : cmake(0.0, 0.0);
-          else x = csub(x, cmul(v2i, wv[jj]));
-        }
-        AB[(BW + ii - jj) + (r0 + jj) * (int64_t)LDAB] = x;
-      }
-    }
-  }
-  const int64_t voff1 = P.compact ? s * BW : hb_voff(n, k + 1) + s * BW;
-  const int64_t toff1 = P.compact ? s : hb_voff(n, k + 1) / BW + s;
-  if (q == 0) V2[voff1 + i] = v2[i];
-  if (tid == 0) tau2[toff1] = tau1;
-}
-
 // One step of the pipelined chase: task (s, k = t - 2 s) for s = smin + blockIdx.x
-// of problem blockIdx.z.
+// of problem blockIdx.z, its diagonal block D_k in workgroup y = 0 and the
+// block E_k below it in workgroup y = 1 (disjoint entries; both only read the
+// current reflector H = H_{s,k}; for k = 0 each forms it from column s, which
+// no task writes: beta goes straight to e[s]).
+//
+// The 2 n steps are a chain, one launch each, so a step's latency is what
+// counts.  A wavefront owns 8 columns of its 64 x 64 block in registers (lane =
+// row) and every sum over rows or columns stays inside the wavefront (DPP and
+// permlane folds, lane reads) except the product with v, whose 8 partials per
+// row meet in LDS behind the kernel's only barrier; from there every wavefront
+// computes the scalars and vectors it needs for itself.  Splitting D and E
+// over two CUs halves the bytes each CU has to load and store.
+// One workgroup per task, both blocks staged in LDS, wavefront 0 doing the
+// scalar work behind six barriers, took 10.2 us a step at order 12816 (launch
+// included, of which about 2.4 us for an empty kernel); this form takes 6.4.
 __global__ void __launch_bounds__(CH_THREADS) hb_chase(const HsProb *pr, int64_t t) {
-  __shared__ ChaseSh sh;
+  __shared__ cd red[CH_Q][BW];
+  __shared__ double ty[2 * BW];                 // D: transposed product, (re, im) per row
+  __shared__ cd col0[BW];                       // E: its first column
   const HsProb &P = pr[blockIdx.z];
   const int64_t n = P.n;
   int64_t smin, smax;
@@ -282,16 +140,122 @@ __global__ void __launch_bounds__(CH_THREADS) hb_chase(const HsProb *pr, int64_t
   const int64_t s = smin + blockIdx.x;
   if (s > smax) return;
   const int64_t k = t - 2 * s;
-  if (k < 0 || s + 1 + k * BW > n - 1) return;
-  chase_task(P, s, k, sh);
+  const int64_t r0 = s + 1 + k * BW;
+  if (k < 0 || r0 > n - 1) return;
+  const bool below = blockIdx.y != 0;           // this workgroup's block: E_k (else D_k)
+  const int L = (int)((n - r0 < BW) ? n - r0 : BW);
+  const int64_t e0 = r0 + L;
+  const int Le = (int)((n - e0 < BW) ? n - e0 : BW);
+  if (below && Le <= 0) return;                 // no block below (else L = BW)
+  MMF_GLOBAL cd *AB = (MMF_GLOBAL cd *)P.AB, *V2 = (MMF_GLOBAL cd *)P.V2, *tau2 = (MMF_GLOBAL cd *)P.tau2;
+  const int tid = threadIdx.x, i = tid & 63, q = tid >> 6;
+  const int j0 = CH_W * q;                      // first column of this wavefront
+  // reflector slots: all kept, or (eigenvalues only) two per sweep in turn
+  const int64_t toff = P.compact ? 2 * s + (k & 1) : hb_voff(n, k) / BW + s;
+  // ---- loads: H (or column s), this wavefront's columns of the block
+  cd v = (k == 0) ? gload(AB + s * (int64_t)LDAB + 1 + (i < L ? i : 0)) : gload(V2 + toff * BW + i);
+  cd tau = (k == 0) ? cmake(0.0, 0.0) : gload(tau2 + toff);
+  MMF_GLOBAL cd *blk = AB + (r0 + j0) * (int64_t)LDAB + (below ? BW : 0) + i - j0;   // column c at c (LDAB - 1)
+  cd x[CH_W];
+#pragma unroll
+  for (int c = 0; c < CH_W; ++c) {
+    const bool ok = below ? i < Le : (i >= j0 + c && i < L);
+    x[c] = cmake(0.0, 0.0);
+    if (ok) x[c] = gload(blk + c * (LDAB - 1));
+  }
+  if (k == 0) {
+    if (i >= L) v = cmake(0.0, 0.0);
+    double beta;
+    v = wave_larfg(v, i, L, tau, beta);
+    if (!below && q == 0) {
+      V2[toff * BW + i] = v;
+      if (i == 0) { tau2[toff] = tau; P.e[s] = beta; }
+    }
+  }
+  cd vj[CH_W];
+#pragma unroll
+  for (int c = 0; c < CH_W; ++c) vj[c] = lane_get(v, j0 + c);
+  // ---- product with v: this row's part of the wavefront's columns
+  cd py = cmake(0.0, 0.0);
+  if (!below) {
+    cd pt[CH_W];                                // strictly lower part, transposed
+#pragma unroll
+    for (int c = 0; c < CH_W; ++c) {
+      if (i == j0 + c) x[c].im = 0.0;
+      py = cadd(py, cmul(x[c], vj[c]));
+      pt[c] = i > j0 + c ? cmulc(x[c], v) : cmake(0.0, 0.0);
+    }
+    double w[4];
+    wave_sum8(pt, w);
+    if ((i & 15) == 0) {
+      const int rw = i >> 4;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) ty[2 * (j0 + m + 4 * (rw & 1)) + (rw >> 1)] = w[m];
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < CH_W; ++c) py = cadd(py, cmul(x[c], vj[c]));
+    if (q == 0) col0[i] = x[0];
+  }
+  red[q][i] = py;
+  __syncthreads();
+  cd y = red[0][i];
+#pragma unroll
+  for (int g = 1; g < CH_Q; ++g) y = cadd(y, red[g][i]);
+  if (!below) {
+    // ---- w = tau y - (|tau|^2 gamma / 2) v, gamma = v^H y;  D <- D - w v^H - v w^H
+    y = cadd(y, cmake(ty[2 * i], ty[2 * i + 1]));
+    const double h = 0.5 * cabs2(tau) * wave_sum(cmulc(v, y).re);
+    const cd t1 = cmul(tau, y);
+    const cd wi = cmake(t1.re - h * v.re, t1.im - h * v.im);
+#pragma unroll
+    for (int c = 0; c < CH_W; ++c) {
+      const cd wj = lane_get(wi, j0 + c);
+      cd d = csub(x[c], cadd(cmul(wi, cconj(vj[c])), cmul(v, cconj(wj))));
+      if (i == j0 + c) d.im = 0.0;
+      if (i >= j0 + c && i < L) blk[c * (LDAB - 1)] = d;
+    }
+    return;
+  }
+  // ---- E <- E H; H_{s,k+1} from its first column (conj(v_0) = 1);  E <- H_{s,k+1}^H E
+  const cd zz = cmul(tau, y);
+  const cd first = csub(col0[i], zz);
+  cd tau1 = cmake(0.0, 0.0);
+  double beta1 = 0.0;
+  cd v2 = (i == 0) ? cmake(1.0, 0.0) : cmake(0.0, 0.0);
+  if (Le >= 2) v2 = wave_larfg(first, i, Le, tau1, beta1);
+  const bool active = tau1.re != 0.0 || tau1.im != 0.0;     // uniform
+#pragma unroll
+  for (int c = 0; c < CH_W; ++c) x[c] = csub(x[c], cmul(zz, cconj(vj[c])));
+  if (active) {
+    cd pu[CH_W];
+    double w[4];
+#pragma unroll
+    for (int c = 0; c < CH_W; ++c) pu[c] = cmulc(v2, x[c]);
+    wave_sum8(pu, w);
+#pragma unroll
+    for (int c = 0; c < CH_W; ++c) {
+      const cd u = cmake(lane_get(w[c & 3], 16 * (c >> 2)), lane_get(w[c & 3], 32 + 16 * (c >> 2)));
+      x[c] = csub(x[c], cmul(v2, cmulc(tau1, u)));
+    }
+    if (q == 0) x[0] = (i == 0) ? cmake(beta1, 0.0) : cmake(0.0, 0.0);
+  }
+  if (i < Le) {
+#pragma unroll
+    for (int c = 0; c < CH_W; ++c) blk[c * (LDAB - 1)] = x[c];
+  }
+  if (q == 0) {
+    const int64_t toff1 = P.compact ? 2 * s + ((k + 1) & 1) : hb_voff(n, k + 1) / BW + s;
+    V2[toff1 * BW + i] = v2;
+    if (i == 0) tau2[toff1] = tau1;
+  }
 }
 
 __global__ void hb_extract(const HsProb *pr) {
   const HsProb &P = pr[blockIdx.z];
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= P.n) return;
-  P.d[c] = P.AB[c * (int64_t)LDAB].re;
-  if (c < P.n - 1) P.e[c] = P.AB[1 + c * (int64_t)LDAB].re;
+  P.d[c] = P.AB[c * (int64_t)LDAB].re;          // e was written by the sweeps
 }
 
 // Grouped chase of `count` problems in the device table pr (orders nh[] on the host).
@@ -318,7 +282,7 @@ int hb2st_grouped(const HsProb *pr, const int64_t *nh, int64_t count, hipStream_
         if (hi - lo + 1 > width) width = hi - lo + 1;
       }
       if (width <= 0) continue;
-      hipLaunchKernelGGL(hb_chase, dim3((unsigned)width, 1, Z), dim3(CH_THREADS), 0, st, pr, t);
+      hipLaunchKernelGGL(hb_chase, dim3((unsigned)width, 2, Z), dim3(CH_THREADS), 0, st, pr, t);
       MMF_LAUNCH_CHECK();
     }
   }
@@ -363,8 +327,8 @@ int hb_band_from_dense_run(int64_t n, const mmf_z *A, int64_t lda, int64_t b, mm
   return MMF_OK;
 }
 
-// Batch (eigenvalues only): compact reflector storage, V2[c] holds n[c] x BW
-// and tau2[c] n[c] entries.
+// Batch (eigenvalues only): compact reflector storage, V2[c] holds n[c] x 2 BW
+// and tau2[c] 2 n[c] entries.
 int hb2st_batched(int64_t count, const int64_t *n, mmf_z *const *AB, mmf_z *const *V2, mmf_z *const *tau2,
                   double *const *d, double *const *e, void *table, hipStream_t st) {
   std::vector<HsProb> h((size_t)count);

@@ -140,3 +140,19 @@ def test_two_stage_eigvalsh_batched(monkeypatch, thr):
         wg = w.cpu().numpy()
         assert np.all(np.diff(wg) >= 0)
         assert np.abs(wg - wo).max() <= 1e-10 * max(1.0, np.abs(wo).max()), H.shape[0]
+
+
+@pytest.mark.parametrize("n", [2, 3, 64, 65, 66, 128, 129, 130, 192, 193, 257])
+def test_two_stage_eigvalsh_task_edges(two_stage, n):
+    """Eigenvalues only (two reflector slots per sweep, used in turn) at the
+    orders where a chase task's blocks have one, 63 or 64 rows; two matrices
+    of different orders share every launch.  Tolerance n eps |A| times 10."""
+    torch, mmf = require_gpu()
+    Hs = [_herm(n, 40 + n), _herm(max(2, n - 1), 41 + n)]
+    log(f"two-stage eigvalsh edges n={n}")
+    ws, info = mmf.eigvalsh_batched([to_dev_cm(torch, H) for H in Hs])
+    torch.cuda.synchronize()
+    assert not info.any().item()
+    for H, w in zip(Hs, ws):
+        wo = oracle.eigvalsh(H)
+        assert np.abs(w.cpu().numpy() - wo).max() <= 10 * max(n, 10) * np.finfo(float).eps * np.abs(wo).max()
