@@ -77,6 +77,10 @@ template <typename R>
 __device__ inline cx<R> cmulc(cx<R> a, cx<R> b) {
   return cmk<R>(a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re);
 }
+// x - a b in four fused operations (not left to contraction: the same bits wherever it is used)
+__device__ inline cd cfnma(cd x, cd a, cd b) {
+  return cmake(fma(a.im, b.im, fma(-a.re, b.re, x.re)), fma(-a.im, b.re, fma(-a.re, b.im, x.im)));
+}
 template <typename R>
 __device__ inline cx<R> cconj(cx<R> a) { return cmk<R>(a.re, -a.im); }
 template <typename R>
@@ -152,6 +156,31 @@ __device__ __forceinline__ float rows_sum(float v) {
   swap32(__float_as_int(v), a, b);
   return __int_as_float(a) + __int_as_float(b);
 }
+
+// Value of lane u, in every lane (u uniform).
+__device__ __forceinline__ double lane_get(double v, int u) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), u),
+                          __builtin_amdgcn_readlane(__double2loint(v), u));
+}
+__device__ __forceinline__ cd lane_get(cd v, int u) { return cmake(lane_get(v.re, u), lane_get(v.im, u)); }
+
+// Folds of two values: the lower (fold32: lanes < 32, fold16: even rows of 16)
+// lanes receive a summed over both halves, the others b.
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ double lanes_fold32(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ double lanes_fold16(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+#else
+__device__ inline double lanes_fold32(double a, double b) { return a + b; }
+__device__ inline double lanes_fold16(double a, double b) { return a + b; }
+#endif
 
 // Wavefront-wide sum (all 64 lanes active), the same value in every lane.
 __device__ __forceinline__ double wave_sum(double v) { return rows_sum(row16_sum(v)); }

@@ -47,13 +47,6 @@ constexpr int CH_THREADS = 512;           // threads per workgroup (8 wavefronts
 constexpr int CH_Q = CH_THREADS / 64;     // column groups of a block, one wavefront each
 constexpr int CH_W = BW / CH_Q;           // columns per group
 
-// Value of lane u, in every lane (u uniform).
-__device__ __forceinline__ double lane_get(double v, int u) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), u),
-                          __builtin_amdgcn_readlane(__double2loint(v), u));
-}
-__device__ __forceinline__ cd lane_get(cd v, int u) { return cmake(lane_get(v.re, u), lane_get(v.im, u)); }
-
 // Householder vector of x held by the 64 lanes of one wavefront (lane i: x_i,
 // len <= BW entries): H^H x = beta e0, beta real, v_0 = 1.  The identity
 // (tau = 0) when x is already real e0.
@@ -78,28 +71,13 @@ __device__ inline cd wave_larfg(cd xi, int i, int len, cd &tau, double &beta) {
 // share the lanes after each fold), the last 16 lanes by DPP; 21 double adds
 // instead of 96.  On return row rw (16 lanes) of w[m] holds, in all its lanes,
 // the real (rw < 2) or imaginary part of the sum of p[m + 4 (rw & 1)].
-#if defined(__HIP_DEVICE_COMPILE__)
-__device__ __forceinline__ double fold32(double a, double b) {
-  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-__device__ __forceinline__ double fold16(double a, double b) {
-  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-#else
-__device__ inline double fold32(double a, double b) { return a + b; }
-__device__ inline double fold16(double a, double b) { return a + b; }
-#endif
 __device__ __forceinline__ void wave_sum8(const cd (&p)[CH_W], double (&w)[4]) {
   static_assert(CH_W == 8, "eight columns per wavefront");
   double t[8];
 #pragma unroll
-  for (int c = 0; c < 8; ++c) t[c] = fold32(p[c].re, p[c].im);
+  for (int c = 0; c < 8; ++c) t[c] = lanes_fold32(p[c].re, p[c].im);
 #pragma unroll
-  for (int m = 0; m < 4; ++m) w[m] = row16_sum(fold16(t[m], t[m + 4]));
+  for (int m = 0; m < 4; ++m) w[m] = row16_sum(lanes_fold16(t[m], t[m + 4]));
 }
 
 // Tasks of step t for a problem of order n: sweeps smin .. smax (none when

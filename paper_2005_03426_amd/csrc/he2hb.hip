@@ -36,7 +36,10 @@
 
 namespace mmf {
 
-constexpr int QR_ROWS = 256;      // rows per workgroup of the panel factorization
+constexpr int QR_ROWS = 64;       // rows per row block of the panel factorization (lane = row)
+constexpr int QR_REP = 8;         // most row blocks per workgroup
+constexpr int QR_SETS = 8;        // column sets (wavefronts) per workgroup
+constexpr int QR_WGS = 128;       // workgroups up to which each has one row block
 constexpr int64_t HEMM_KC = 1024; // K slice of the A22 V product
 constexpr int64_t PAN_KC = 128;   // row slice of the panel products V^H V, V^H X
 
@@ -108,67 +111,103 @@ __device__ inline cd *hb_p3(const HbProb &P, int64_t c0) {
   return P.ws.P3 + ((c0 / BW) & 1) * P.ws.p3stride;
 }
 
-// Zero the three panel slots of P3 (rows q0 .. n-1).
-__global__ void hb_zero_p3(const HbProb *pr, int64_t c0) {
-  const HbProb &P = pr[blockIdx.z];
-  HbPanel pp;
-  if (!hb_panel(P, c0, pp)) return;
-  const int64_t r = pp.q0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= P.n) return;
-  cd *P3 = hb_p3(P, c0);
-  for (int c = 0; c < 3 * BW; ++c) P3[r + (int64_t)c * P.n] = cmake(0.0, 0.0);
+// Row blocks per workgroup of the panel factorization of m rows: one until
+// QR_WGS workgroups, then more (every workgroup reads the partial sums of all
+// the others, up to 1 KB each).
+__host__ __device__ inline int hb_qr_rep(int64_t m) {
+  const int64_t rep = (m + QR_ROWS * QR_WGS - 1) / (QR_ROWS * QR_WGS);
+  return (int)(rep < 1 ? 1 : (rep > QR_REP ? QR_REP : rep));
+}
+__host__ __device__ inline int64_t hb_qr_wgs(int64_t m) {
+  const int64_t rows = (int64_t)QR_ROWS * hb_qr_rep(m);
+  return (m + rows - 1) / rows;
 }
 
-// One launch per panel column j = 0 .. nr (workgroup w owns rows q0 + 256 w ..).
-// With x~ the part of column j below row rj = q0 + j and
+// One launch per panel column j = 0 .. nr (workgroup w owns its row blocks from
+// q0 on).  With x~ the part of column j below row rj = q0 + j and
 // v_j = (1, s x~), s = 1 / (alpha - beta), the product v_j^H P[:, c] equals
 // P[rj, c] + conj(s) (x~^H P[:, c]); so the launch for column j forms the
 // partial sums g[c] = x~^H P[:, c] (c >= j; g[j] = |x~|^2) while beta and s
 // are still unknown, and publishes row rj of the panel.  The next launch
 // derives beta, tau, s from the summed partials in every workgroup, scales its
-// rows of column j into v_j (stored below the band and in the V slots of P3),
-// applies H_j^H to the panel columns right of j, and forms the partials of
-// column j + 1.  Partials and the published row alternate between two buffers.
-__global__ void __launch_bounds__(QR_ROWS) hb_qr_step(const HbProb *pr, int64_t c0, int j) {
-  __shared__ double bre[QR_ROWS][17], bim[QR_ROWS][17];
-  __shared__ cd psum[16][16];
-  __shared__ cd gs[BW], d[BW], gq[4][BW];
+// rows of column j into v_j (stored below the band and, with the zeros above
+// it, in the V slots of P3), applies H_j^H to the panel columns right of j,
+// and forms the partials of column j + 1.  Partials and the published row
+// alternate between two buffers.
+//
+// A chain of 64 launches per panel, latency bound: a wavefront holds 64 rows
+// (lane = row) by every eighth column from j on in registers, loads them
+// before the sums are known, and reduces over its rows with lane folds.  Staging every product in 70 KB
+// of LDS instead (256 rows per workgroup, three barriers per 16 columns) took
+// 15.0 us a launch at order 12168 and 19.4 at 8 x 5376 beside the update of
+// the previous panel; this form takes 12.3 and 18.4 (7.8 and 9.8 alone; fewer
+// workgroups of the update at a time, 256 to 448, left it at 12.2).
+__global__ void __launch_bounds__(64 * QR_SETS, 4) hb_qr_step(const HbProb *pr, int64_t c0, int j) {
+  __shared__ cd psum[QR_SETS][BW];
+  __shared__ cd xps[QR_REP][QR_ROWS], xjs[QR_REP][QR_ROWS];
   const HbProb &P = pr[blockIdx.z];
   HbPanel pp;
   if (!hb_panel(P, c0, pp) || j > pp.nr) return;
-  const int64_t nwg = (pp.m + QR_ROWS - 1) / QR_ROWS;
+  const int64_t nwg = hb_qr_wgs(pp.m);
   if ((int64_t)blockIdx.x >= nwg) return;
+  const int rep = hb_qr_rep(pp.m);
   const int64_t n = P.n, lda = P.lda, q0 = pp.q0;
-  const int bw = pp.bw, nr = pp.nr;
-  MMF_GLOBAL cd *A = (MMF_GLOBAL cd *)P.A;
+  const int nr = pp.nr;
+  MMF_GLOBAL cd *A = (MMF_GLOBAL cd *)P.A + c0 * lda;
   const HbWs &ws = P.ws;
-  const int tid = threadIdx.x;
-  const int64_t r = q0 + (int64_t)blockIdx.x * QR_ROWS + tid;
+  const int tid = threadIdx.x, lane = tid & 63, cs = tid >> 6;   // column set cs: columns j + cs + 8 cc
+  const int64_t rb = q0 + (int64_t)blockIdx.x * QR_ROWS * rep + lane;
   const int wr = j & 1, rd = wr ^ 1;
   MMF_GLOBAL cd *gw = (MMF_GLOBAL cd *)ws.gpart + (int64_t)wr * ws.nwg * BW;
   MMF_GLOBAL cd *gr = (MMF_GLOBAL cd *)ws.gpart + (int64_t)rd * ws.nwg * BW;
   MMF_GLOBAL cd *pw = (MMF_GLOBAL cd *)ws.prow + wr * BW, *prd = (MMF_GLOBAL cd *)ws.prow + rd * BW;
-  cd vown = cmake(0.0, 0.0);                // this row's entry of v_{j-1}
-  if (j >= 1) {
-    // ---- reflector jp = j - 1 from the previous launch's sums
-    const int jp = j - 1;
-    const int64_t rjp = q0 + jp;
-    {
-      // four threads per column sum interleaved partials, then fixed-order combine
-      const int c = tid & 63, qp = tid >> 6;
-      cd sum = cmake(0.0, 0.0);
-      if (c >= jp && c < bw) {
-#pragma unroll 4
-        for (int64_t w = qp; w < nwg; w += 4) sum = cadd(sum, gr[w * BW + c]);
-      }
-      gq[qp][c] = sum;
+  MMF_GLOBAL cd *p3 = (MMF_GLOBAL cd *)hb_p3(P, c0);
+  const int jp = j - 1;
+  const int64_t rj = q0 + j, rjp = rj - 1;
+  const bool last = j >= nr;                    // uniform: no partials after the last reflector
+  const int ncol = BW - j - cs;                 // columns of this set: 8 cc < ncol
+  // ---- loads that wait for nothing: this wavefront's columns of the first row
+  // block, the raw columns j - 1 and j of all its row blocks
+  cd xv[BW / QR_SETS];
+  auto load = [&](int64_t r) {
+#pragma unroll
+    for (int cc = 0; cc < 8; ++cc) {
+      xv[cc] = cmake(0.0, 0.0);
+      if (8 * cc < ncol && r < n) xv[cc] = gload(A + r + (j + cs + 8 * cc) * lda);
     }
-    __syncthreads();
-    if (tid < BW) gs[tid] = cadd(cadd(gq[0][tid], gq[1][tid]), cadd(gq[2][tid], gq[3][tid]));
-    __syncthreads();
-    const double xn2 = gs[jp].re;
-    const cd alpha = prd[jp];
-    cd tj = cmake(0.0, 0.0), sc = cmake(0.0, 0.0);
+  };
+  load(rb);
+  if (cs == 0) {
+    for (int u = 0; u < rep; ++u) {
+      const int64_t r = rb + (int64_t)QR_ROWS * u;
+      const bool in = r < n;
+      xps[u][lane] = (j >= 1 && in) ? gload(A + r + jp * lda) : cmake(0.0, 0.0);
+      xjs[u][lane] = (j < BW && in) ? gload(A + r + j * lda) : cmake(0.0, 0.0);
+    }
+  }
+  if (j >= 1) {
+    // partials of the previous launch: thread = column, every eighth workgroup
+    cd sum = cmake(0.0, 0.0);
+    if (lane >= jp) {
+#pragma unroll 4
+      for (int64_t w = cs; w < nwg; w += QR_SETS) sum = cadd(sum, gload(gr + w * BW + lane));
+    }
+    psum[cs][lane] = sum;
+  } else if (nr < BW) {
+    // a panel with fewer than BW reflectors (m <= BW rows): its other V columns vanish
+    for (int c = nr + cs; c < BW; c += QR_SETS)
+      if (blockIdx.x == 0 && q0 + lane < n) {
+        p3[q0 + lane + (int64_t)c * n] = cmake(0.0, 0.0);
+        p3[q0 + lane + (int64_t)(2 * BW + c) * n] = cmake(0.0, 0.0);
+      }
+  }
+  __syncthreads();
+  cd tj = cmake(0.0, 0.0), sc = cmake(0.0, 0.0), dl = cmake(0.0, 0.0);
+  if (j >= 1) {
+    // ---- reflector jp from the sums
+    const int u = lane & 7;
+    const double xn2 = wave_sum(lane < 8 ? psum[u][jp].re : 0.0);
+    const cd alpha = gload(prd + jp);
     double beta = alpha.re;
     if (xn2 > 0.0 || alpha.im != 0.0) {
       const double nrm = sqrt(alpha.re * alpha.re + alpha.im * alpha.im + xn2);
@@ -178,76 +217,71 @@ __global__ void __launch_bounds__(QR_ROWS) hb_qr_step(const HbProb *pr, int64_t 
       const double den = am.re * am.re + am.im * am.im;
       sc = cmake(am.re / den, -am.im / den);
     }
-    if (tid < BW) {
-      // d[c] = conj(tau) (P[rjp, c] + conj(s) g[c])
-      d[tid] = (tid >= j && tid < bw) ? cmulc(tj, cadd(prd[tid], cmulc(sc, gs[tid]))) : cmake(0.0, 0.0);
-    }
     if (blockIdx.x == 0 && tid == 0) {
       ((MMF_GLOBAL cd *)P.tau)[c0 + jp] = tj;
       ((MMF_GLOBAL double *)ws.beta)[jp] = beta;
     }
-    __syncthreads();
-    if (r < n && r >= rjp) {
-      cd v = cmake(1.0, 0.0);
-      if (r > rjp) {
-        v = cmul(A[r + (c0 + jp) * lda], sc);
-        A[r + (c0 + jp) * lda] = v;
-      }
-      MMF_GLOBAL cd *p3 = (MMF_GLOBAL cd *)hb_p3(P, c0);
-      p3[r + (int64_t)jp * n] = v;
-      p3[r + (int64_t)(2 * BW + jp) * n] = v;
-      vown = v;
-    }
+    // d[c] = conj(tau) (P[rjp, c] + conj(s) g[c]): lane cc < 8 (of each row of
+    // 16) the cc-th column of this set, lane 15 column j, two partials per row
+    const int cmine = (lane & 15) == 15 ? j : j + cs + 8 * (lane & 15);
+    const int c1 = cmine < BW ? cmine : BW - 1;
+    const int g2 = 2 * (lane >> 4);
+    const cd pc = gload(prd + c1);
+    const cd a = cadd(psum[g2][c1], psum[g2 + 1][c1]);
+    dl = cmulc(tj, cadd(pc, cmulc(sc, cmake(rows_sum(a.re), rows_sum(a.im)))));
   }
-  // ---- update of columns j .. bw-1 by reflector j - 1 (j >= 1), fused with
-  // the partials of column j (g[c] = x~^H P[:, c], c >= j, x~ = column j below
-  // row rj), 16 columns per chunk held in registers
-  const bool upd = j >= 1 && r < n && r >= q0 + j - 1;
-  const bool last = j >= nr;                 // uniform: no partials after the last reflector
-  const int64_t rj = q0 + j;
-  const bool live = !last && r < n && r > rj;
-  cd xr = cmake(0.0, 0.0);
-  for (int cb = j; cb < bw; cb += 16) {
-    cd xv[16];
-#pragma unroll
-    for (int cc = 0; cc < 16; ++cc)
-      xv[cc] = (cb + cc < bw && r < n && (upd || live || r == rj)) ? A[r + (c0 + cb + cc) * lda] : cmake(0.0, 0.0);
-    if (upd) {
-#pragma unroll
-      for (int cc = 0; cc < 16; ++cc) {
-        if (cb + cc < bw) {
-          xv[cc] = csub(xv[cc], cmul(vown, d[cb + cc]));
-          A[r + (c0 + cb + cc) * lda] = xv[cc];
-        }
+  // ---- update of columns j .. by reflector j - 1 (j >= 1), fused with the
+  // partials of column j (g[c] = x~^H P[:, c], c >= j)
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int u = 0; u < rep; ++u) {
+    const int64_t r = rb + (int64_t)QR_ROWS * u;
+    if (u > 0) load(r);
+    cd v = cmake(0.0, 0.0), xr = xjs[u][lane];
+    if (j >= 1 && r < n) {
+      v = r > rjp ? cmul(xps[u][lane], sc) : cmake(r == rjp ? 1.0 : 0.0, 0.0);
+      if (cs == 0) {
+        if (r > rjp) A[r + jp * lda] = v;
+        p3[r + (int64_t)jp * n] = v;
+        p3[r + (int64_t)(2 * BW + jp) * n] = v;
       }
+      // every wavefront forms column j for its sums; it must be, bit for bit,
+      // the column that is stored and becomes v_j (where a panel of low rank
+      // cancels, the two would otherwise have different norms): the same lane's
+      // d and the same fused operations
+      xr = cfnma(xr, v, lane_get(dl, 15));
+#pragma unroll
+      for (int cc = 0; cc < 8; ++cc)
+        if (8 * cc < ncol) {
+          const cd d = lane_get(dl, cc);
+          xv[cc] = cfnma(xv[cc], v, d);
+          if (r >= rjp) A[r + (j + cs + 8 * cc) * lda] = xv[cc];
+        }
     }
-    if (last) continue;                      // uniform
-    if (cb == j) xr = xv[0];
+    if (last) continue;                          // uniform
     if (r == rj) {
 #pragma unroll
-      for (int cc = 0; cc < 16; ++cc)
-        if (cb + cc < bw) pw[cb + cc] = xv[cc];
+      for (int cc = 0; cc < 8; ++cc)
+        if (8 * cc < ncol) pw[j + cs + 8 * cc] = xv[cc];
     }
+    // sums over the 64 rows of the 8 products, folded pairwise
+    const cd xl = (r > rj && r < n) ? xr : cmake(0.0, 0.0);
 #pragma unroll
-    for (int cc = 0; cc < 16; ++cc) {
-      const cd pp2 = (live && cb + cc < bw) ? cmulc(xr, xv[cc]) : cmake(0.0, 0.0);
-      bre[tid][cc] = pp2.re;
-      bim[tid][cc] = pp2.im;
+    for (int m = 0; m < 4; ++m)
+      if (8 * m < ncol) {                        // uniform
+        const cd p0 = cmulc(xl, xv[m]), p1 = cmulc(xl, xv[m + 4]);
+        acc[m] += row16_sum(lanes_fold16(lanes_fold32(p0.re, p0.im), lanes_fold32(p1.re, p1.im)));
+      }
+  }
+  if (last) return;
+  // row of lanes rw holds the real (rw < 2) or imaginary part of column cc = m + 4 (rw & 1)
+  if ((lane & 15) == 0) {
+    const int rw = lane >> 4;
+    MMF_GLOBAL double *gd = (MMF_GLOBAL double *)(gw + blockIdx.x * BW);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int c = j + cs + 8 * (m + 4 * (rw & 1));
+      if (c < BW) gd[2 * c + (rw >> 1)] = acc[m];
     }
-    __syncthreads();
-    {
-      const int cc = tid & 15, g = tid >> 4;
-      double sr = 0.0, si = 0.0;
-      for (int q = 0; q < 16; ++q) { sr += bre[16 * g + q][cc]; si += bim[16 * g + q][cc]; }
-      psum[g][cc] = cmake(sr, si);
-    }
-    __syncthreads();
-    if (tid < 16 && cb + tid < bw) {
-      cd sum = cmake(0.0, 0.0);
-      for (int g = 0; g < 16; ++g) sum = cadd(sum, psum[g][tid]);
-      gw[blockIdx.x * BW + cb + tid] = sum;
-    }
-    __syncthreads();
   }
 }
 
@@ -563,13 +597,14 @@ int he2hb_grouped(const HbProb *pr, const int64_t *nh, int64_t count, hipStream_
       const int nrc = (int)((mc - 1 < bwc) ? mc - 1 : bwc);
       nrmax = nrc > nrmax ? nrc : nrmax;
     }
-    const unsigned nwg = cdiv(m, QR_ROWS), ntile = cdiv(m, GT_M);
+    const unsigned ntile = cdiv(m, GT_M);
+    // (a smaller problem may have more, but at most QR_WGS unless the largest has more)
+    const int64_t wgs = hb_qr_wgs(m);
+    const unsigned nwg = (unsigned)(hb_qr_rep(m) > 1 && wgs < QR_WGS ? QR_WGS : wgs);
     const unsigned nks = cdiv(m, HEMM_KC), npk = cdiv(m, PAN_KC);
-    hipLaunchKernelGGL(hb_zero_p3, dim3(cdiv(m, 256), 1, Z), dim3(256), 0, st, pr, c0);
-    MMF_LAUNCH_CHECK_OR(release());
     // panel factorization: one launch per column
     for (int j = 0; j <= nrmax; ++j) {
-      hipLaunchKernelGGL(hb_qr_step, dim3(nwg, 1, Z), dim3(QR_ROWS), 0, st, pr, c0, j);
+      hipLaunchKernelGGL(hb_qr_step, dim3(nwg, 1, Z), dim3(64 * QR_SETS), 0, st, pr, c0, j);
       MMF_LAUNCH_CHECK_OR(release());
     }
     hipLaunchKernelGGL(hb_gram, dim3(npk, 1, Z), dim3(GEMM_THREADS), 0, st, pr, c0);

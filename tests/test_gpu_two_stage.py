@@ -156,3 +156,47 @@ def test_two_stage_eigvalsh_task_edges(two_stage, n):
     for H, w in zip(Hs, ws):
         wo = oracle.eigvalsh(H)
         assert np.abs(w.cpu().numpy() - wo).max() <= 10 * max(n, 10) * np.finfo(float).eps * np.abs(wo).max()
+
+
+@pytest.mark.parametrize("n,dup", [(66, 1), (127, 2), (128, 1), (129, 3), (192, 64), (193, 5)])
+def test_two_stage_panel_edges(two_stage, n, dup):
+    """Panel factorization at the edges of its 64-row blocks, with panel rows
+    that vanish from row `dup` on (identity reflectors, |x| = 0).  Eigenvalues
+    against those of the two blocks (n eps |A| times 10)."""
+    torch, mmf = require_gpu()
+    log(f"two-stage panel edges n={n} dup={dup}")
+    H = _herm(n, 70 + n)
+    H[dup:, :dup] = 0.0
+    H[:dup, dup:] = 0.0
+    wo = np.sort(np.concatenate([oracle.eigvalsh(H[:dup, :dup]), oracle.eigvalsh(H[dup:, dup:])]))
+    ws, info = mmf.eigvalsh_batched([to_dev_cm(torch, H)])
+    torch.cuda.synchronize()
+    assert not info.any().item()
+    assert np.abs(ws[0].cpu().numpy() - wo).max() <= 10 * n * np.finfo(float).eps * np.abs(wo).max()
+
+
+@pytest.mark.parametrize("n", [300, 2300, 8300])
+def test_two_stage_low_rank_panels(two_stage, n):
+    """A diagonal matrix with one dense block of order 100, seen through a
+    Householder similarity: off-diagonal panels of rank two, whose columns
+    cancel after two reflectors.  At 8300 a workgroup of the panel
+    factorization has two row blocks.  Eigenvalues known (n eps |A| times 10)."""
+    torch, mmf = require_gpu()
+    log(f"two-stage low rank n={n}")
+    k = n - 100
+    S, d = _herm(100, 71), np.arange(k, dtype=float) / k
+    wo = np.sort(np.concatenate([d, oracle.eigvalsh(S)]))
+    H = torch.zeros((n, n), dtype=torch.complex128, device="cuda")
+    H.diagonal()[:k] = torch.from_numpy(d).cuda().to(torch.complex128)
+    H[k:, k:] = torch.from_numpy(S).cuda()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    v = torch.randn(n, dtype=torch.complex128, device="cuda", generator=g)
+    v /= torch.linalg.vector_norm(v)
+    Hv = H @ v
+    H += (-2 * torch.outer(v, Hv.conj()) - 2 * torch.outer(Hv, v.conj())
+          + 4 * (v.conj() @ Hv) * torch.outer(v, v.conj()))
+    ws, info = mmf.eigvalsh_batched([H.T.contiguous()])
+    torch.cuda.synchronize()
+    assert not info.any().item()
+    assert np.abs(ws[0].cpu().numpy() - wo).max() <= 10 * n * np.finfo(float).eps * np.abs(wo).max()
