@@ -35,12 +35,13 @@
 
 namespace mmf {
 
-constexpr int DC_LEAF = 64;
+constexpr int DC_LEAF = 16;
 constexpr int DC_CNT = 5;     // per merge: K, rotations, deflated, top-only, top-only + mixed columns
 constexpr double DC_EPS = DBL_EPSILON;
 
 struct DcWs {
   double *dw, *lam, *T1, *T2;
+  double *es, *scl;           // scaled off-diagonal; the power of two and its reciprocal
   double *ds, *zs, *dn, *zn, *ddef, *rc, *rs, *lamt, *zhat, *rho;
   int32_t *src, *ndidx, *dfidx, *rp, *rj, *lamo, *colmap, *cnt;   // cnt: [DC_CNT * n] per merge
   int32_t *ctype, *perm;      // child type of each column (1 top, 2 bottom, 3 both); T1/T2 slot of each kept column
@@ -53,6 +54,8 @@ inline DcWs stedc_ws(int64_t n, void *base) {
   const size_t N = (size_t)(n > 0 ? n : 1);
   w.dw = cv.take<double>(N);
   w.lam = cv.take<double>(N);
+  w.es = cv.take<double>(N);
+  w.scl = cv.take<double>(2);
   w.T1 = cv.take<double>(N * N);
   w.T2 = cv.take<double>(N * N);
   w.ds = cv.take<double>(N);
@@ -86,6 +89,7 @@ struct DcProb {
   int32_t h;
   int32_t sec_max, leaf_max;     // iteration caps: secular steps per root, QL steps per eigenvalue
   double *d;
+  const double *e0;              // caller's off-diagonal; the kernels use e = w.es
   const double *e;
   double *Z;
   int32_t *info;
@@ -122,120 +126,146 @@ __device__ inline bool dc_is_boundary(int64_t x, int64_t n, int64_t L) {
   return j >= 1 && j < L && dc_b(j, n, L) == x;
 }
 
-// dw = d with |e_{k-1}| taken from d_{k-1} and d_k at every boundary k
-// (one thread per row; boundaries are at least one leaf apart).
+// Status word cleared and the power of two that brings the largest entry to
+// [1/2, 1): the merges form squares and reciprocals of differences, which a
+// matrix of norm 1e-150 or 1e150 would push out of range.  Exact, so that any
+// other matrix gives the same bits with and without it.
+__global__ void __launch_bounds__(1024) dc_scale(const DcProb *pr) {
+  __shared__ double sh[16];
+  const DcProb &q = pr[blockIdx.z];
+  const int64_t n = q.n;
+  double m = 0.0;
+  for (int64_t i = threadIdx.x; i < n; i += 1024) {
+    m = fmax(m, fabs(q.d[i]));
+    if (i < n - 1) m = fmax(m, fabs(q.e0[i]));
+  }
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int g = 1; g < 16; ++g) m = fmax(m, sh[g]);
+  int ex = 0;
+  if (m > 0.0 && m <= DBL_MAX) (void)frexp(m, &ex);
+  ex = ex > 1000 ? 1000 : (ex < -1000 ? -1000 : ex);
+  q.w.scl[0] = ldexp(1.0, -ex);
+  q.w.scl[1] = ldexp(1.0, ex);
+  *q.info = 0;
+}
+
+// es = e and dw = d scaled, with |e_{k-1}| taken from d_{k-1} and d_k at every
+// boundary k (one thread per row; boundaries are at least one leaf apart).
 __global__ void dc_tear(const DcProb *pr) {
   const DcProb &q = pr[blockIdx.z];
   const int64_t n = q.n, L = q.L;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  double v = q.d[i];
-  if (dc_is_boundary(i + 1, n, L)) v -= fabs(q.e[i]);       // i = k - 1
-  if (dc_is_boundary(i, n, L)) v -= fabs(q.e[i - 1]);       // i = k
+  const double sc = q.w.scl[0];
+  double v = q.d[i] * sc;
+  if (dc_is_boundary(i + 1, n, L)) v -= fabs(q.e0[i] * sc);       // i = k - 1
+  if (dc_is_boundary(i, n, L)) v -= fabs(q.e0[i - 1] * sc);       // i = k
   q.w.dw[i] = v;
+  if (i < n - 1) q.w.es[i] = q.e0[i] * sc;
 }
 
 // ------------------------------------------------------------------ leaves
 // One wavefront per leaf: implicit QL with Wilkinson shifts (the textbook
 // symmetric tridiagonal QL iteration: Bowdler, Martin, Reinsch and Wilkinson,
-// Numer. Math. 11 (1968), the tql2 procedure; Golub and Van Loan, Sec. 8.3);
-// every lane runs the scalar recurrence (identical values) and rotates its
-// own row of Z.
+// Numer. Math. 11 (1968), the tql2 procedure; Golub and Van Loan, Sec. 8.3).
+// Lane i holds d_i and e_i; every lane runs the scalar recurrence (identical
+// values, d_i and e_i fetched by lane reads) and rotates its own row of Z.
+// The rotations are one chain of about 1.3 m^2 steps, so a step's latency and
+// the leaf size are what counts.  With d and e in LDS behind barriers, hypot
+// and two divisions a step, leaves of up to 64 took 797 us at order 82 and
+// 1430 at 1715; this form 419 and 728.  Whole solves with leaves of 64 / 32 /
+// 16 (each halving adds a merge level, about 0.1 ms at small orders): order 82
+// 1.35 / 1.14 / 1.13 ms, dressed qubit (450) 7.06 / 6.62 / 6.51 ms, order 1715
+// 26.7 / 26.3 / 26.2 ms, band window 12816 259 ms each.
 __global__ void __launch_bounds__(64) dc_leaf(const DcProb *pr) {
-  __shared__ double dd[DC_LEAF], ee[DC_LEAF];
-  __shared__ double Zl[DC_LEAF * DC_LEAF];
+  __shared__ double Zl[DC_LEAF * 64];               // column c, row r at 64 c + r
   __shared__ int perm[DC_LEAF];
   const DcProb &q = pr[blockIdx.z];
   const int64_t n = q.n, L = q.L, ldz = q.ldz;
   if ((int64_t)blockIdx.x >= L || n <= 0) return;
   const double *dw = q.w.dw, *e = q.e;
   double *Z = q.Z, *lam = q.w.lam;
-  int32_t *info = q.info;
   const int64_t s = dc_b(blockIdx.x, n, L);
   const int m = (int)(dc_b(blockIdx.x + 1, n, L) - s);
   const int r = threadIdx.x;
-  if (r < m) {
-    dd[r] = dw[s + r];
-    ee[r] = (r < m - 1) ? e[s + r] : 0.0;
-  }
-  for (int c = 0; c < m; ++c) Zl[c * DC_LEAF + r] = (c == r) ? 1.0 : 0.0;
+  double dd = r < m ? dw[s + r] : 0.0;
+  double ee = r < m - 1 ? e[s + r] : 0.0;
+  for (int c = 0; c < m; ++c) Zl[c * 64 + r] = (c == r) ? 1.0 : 0.0;
+  if (r < DC_LEAF) perm[r] = r;
   __syncthreads();
   bool fail = false;
   for (int l = 0; l < m; ++l) {
     int iter = 0;
     while (true) {
-      int mm = l;
-      while (mm < m - 1) {
-        const double tst = fabs(dd[mm]) + fabs(dd[mm + 1]);
-        if (fabs(ee[mm]) <= DC_EPS * tst) break;
-        ++mm;
-      }
+      // first negligible e from l on (e_{m-1} = 0)
+      const bool neg = fabs(ee) <= DC_EPS * (fabs(dd) + fabs(__shfl_down(dd, 1, 64)));
+      const uint64_t mask = __ballot(neg && r < m - 1) >> l;
+      const int mm = mask ? l + __builtin_ctzll(mask) : m - 1;
       if (mm == l) break;
       if (++iter > q.leaf_max) { fail = true; break; }
-      double g = (dd[l + 1] - dd[l]) / (2.0 * ee[l]);
+      const double dl = lane_get(dd, l), el = lane_get(ee, l);
+      double g = (lane_get(dd, l + 1) - dl) / (2.0 * el);
       double rr = hypot(g, 1.0);
-      g = dd[mm] - dd[l] + ee[l] / (g + copysign(rr, g));
+      g = lane_get(dd, mm) - dl + el / (g + copysign(rr, g));
       double sn = 1.0, c = 1.0, p = 0.0;
+      double zc = Zl[mm * 64 + r];                  // column i + 1 of this row
+      int i = mm - 1;
       bool restart = false;
-      for (int i = mm - 1; i >= l; --i) {
-        const double f = sn * ee[i];
-        const double b = c * ee[i];
-        rr = hypot(f, g);
-        __syncthreads();
-        ee[i + 1] = rr;
-        __syncthreads();
-        if (rr == 0.0) {
-          const double dv = dd[i + 1] - p;
-          __syncthreads();
-          dd[i + 1] = dv;
-          ee[mm] = 0.0;
-          __syncthreads();
-          restart = true;
-          break;
+      for (; i >= l; --i) {
+        const double ei = lane_get(ee, i), di = lane_get(dd, i), di1 = lane_get(dd, i + 1);
+        const double zi = Zl[i * 64 + r];
+        const double f = sn * ei;
+        const double b = c * ei;
+        const double h = fma(f, f, g * g);
+        if (h > 1e-280 && h < 1e280) {              // uniform
+          const double ri = rsqrt(h);
+          rr = h * ri;
+          sn = f * ri;
+          c = g * ri;
+        } else {
+          rr = hypot(f, g);
+          if (rr == 0.0) {
+            if (r == i + 1) { dd -= p; ee = 0.0; }
+            if (r == mm) ee = 0.0;
+            restart = true;
+            break;
+          }
+          sn = f / rr;
+          c = g / rr;
         }
-        sn = f / rr;
-        c = g / rr;
-        g = dd[i + 1] - p;
-        rr = (dd[i] - g) * sn + 2.0 * c * b;
+        if (r == i + 1) ee = rr;
+        g = di1 - p;
+        rr = (di - g) * sn + 2.0 * c * b;
         p = sn * rr;
-        const double nd = g + p;
-        __syncthreads();
-        dd[i + 1] = nd;
-        __syncthreads();
+        if (r == i + 1) dd = g + p;
         g = c * rr - b;
-        if (r < m) {
-          const double zi1 = Zl[(i + 1) * DC_LEAF + r];
-          const double zi = Zl[i * DC_LEAF + r];
-          Zl[(i + 1) * DC_LEAF + r] = sn * zi + c * zi1;
-          Zl[i * DC_LEAF + r] = c * zi - sn * zi1;
-        }
+        Zl[(i + 1) * 64 + r] = sn * zi + c * zc;
+        zc = c * zi - sn * zc;
       }
+      Zl[(i + 1) * 64 + r] = zc;
       if (restart) continue;
-      const double dl = dd[l] - p;
-      __syncthreads();
-      dd[l] = dl;
-      ee[l] = g;
-      ee[mm] = 0.0;
-      __syncthreads();
+      if (r == l) { dd -= p; ee = g; }
+      if (r == mm) ee = 0.0;
     }
     if (fail) break;
   }
-  if (fail && r == 0) *info = MMF_ERR_NO_CONVERGENCE;
+  if (fail && r == 0) *q.info = MMF_ERR_NO_CONVERGENCE;
   // ascending order (selection by rank; ties by index)
+  int rank = 0;
+  for (int j = 0; j < m; ++j) {
+    const double u = lane_get(dd, j);
+    rank += (u < dd) || (u == dd && j < r);
+  }
   if (r < m) {
-    const double v = dd[r];
-    int rank = 0;
-    for (int j = 0; j < m; ++j) {
-      const double u = dd[j];
-      rank += (u < v) || (u == v && j < r);
-    }
-    perm[rank] = r;
+    perm[rank < m ? rank : m - 1] = r;
+    lam[s + (rank < m ? rank : m - 1)] = dd;
   }
   __syncthreads();
-  if (r < m) {
-    lam[s + r] = dd[perm[r]];
-    for (int c = 0; c < m; ++c) Z[(s + r) + (s + c) * ldz] = Zl[perm[c] * DC_LEAF + r];
-  }
+  if (r < m)
+    for (int c = 0; c < m; ++c) Z[(s + r) + (s + c) * ldz] = Zl[perm[c] * 64 + r];
 }
 
 // ------------------------------------------------------------------ merge: prepare
@@ -297,20 +327,17 @@ __global__ void dc_zero_off(const DcProb *pr, int lev, int64_t Gmax) {
 }
 
 // ------------------------------------------------------------------ merge: deflation scan
-// One wavefront per merge.  The scan over the m entries is sequential (each
-// test involves the last kept entry), so the whole wavefront walks it in
-// lockstep: chunks of 64 entries are read at once (one per lane) and taken
-// entry by entry with lane broadcasts; the current last kept entry (its z, d
-// and child type) stays in registers; lane 0 writes the results.  Each kept
-// column's child type is final when it is kept (only the later entry of a
-// rotated pair changes type), so the slots of the kept columns grouped
-// [top only | both | bottom only] are then formed in parallel, 64 at a time.
-__device__ inline double lane_bcast(double v, int u) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), u);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), u);
-  return __hiloint2double(hi, lo);
-}
-
+// One wavefront per merge.  The scan is sequential only where it rotates:
+// each test involves the last kept entry, which a rotation changes.  Chunks of
+// 64 entries are read at once (one per lane, the next chunk ahead); if no
+// kept entry of a chunk forms a close pair with the kept entry before it, the
+// whole chunk is taken in parallel (slots by ballots), otherwise entry by
+// entry with lane broadcasts.  The current last kept entry (its z, d and child
+// type) stays in registers.  Each kept column's child type is final when it is
+// kept (only the later entry of a rotated pair changes type), so the slots of
+// the kept columns grouped [top only | both | bottom only] are then formed in
+// parallel, 64 at a time.  Entry by entry throughout took 995 us a level at
+// order 12816 (85 at 450), this form 47.
 __global__ void __launch_bounds__(64) dc_deflate(const DcProb *pr, int lev, int64_t Gmax) {
   const DcProb &P = pr[blockIdx.x / Gmax];
   const int64_t g = blockIdx.x % Gmax;
@@ -323,6 +350,7 @@ __global__ void __launch_bounds__(64) dc_deflate(const DcProb *pr, int lev, int6
   const int64_t s = q.s, m = q.m;
   const int lane = threadIdx.x;
   const bool w0 = lane == 0;
+  const uint64_t below = (1ull << lane) - 1;
   const double rh = rho[s];
   double dmax = fmax(fabs(ds[s]), fabs(ds[s + m - 1]));
   const double tol = 8.0 * DC_EPS * fmax(dmax, rh);
@@ -330,31 +358,71 @@ __global__ void __launch_bounds__(64) dc_deflate(const DcProb *pr, int lev, int6
   int64_t prev = -1;
   double zp = 0.0, dp = 0.0;                       // z, d of the last kept entry
   int32_t tp = 0;                                  // its child type
+  // close pair (a Givens rotation of z_a, z_b leaves |(d_b - d_a) c s| <= tol):
+  // z of a kept entry is at least 8 eps, so the products cannot underflow
+  auto close = [&](double za, double da, double zb, double db) {
+    return fabs((db - da) * za * zb) <= tol * fma(za, za, zb * zb);
+  };
+  double zn = lane < m ? zs[s + lane] : 0.0, dn = lane < m ? ds[s + lane] : 0.0;
+  int32_t tn = lane < m ? ctype[s + lane] : 0;
   for (int64_t j0 = 0; j0 < m; j0 += 64) {
-    const int64_t jl = j0 + lane;
-    const double zl = jl < m ? zs[s + jl] : 0.0;
-    const double dl = jl < m ? ds[s + jl] : 0.0;
-    const int32_t tl = jl < m ? ctype[s + jl] : 0;
+    const double zl = zn, dl = dn;
+    const int32_t tl = tn;
     const int nu = (int)((m - j0 < 64) ? m - j0 : 64);
+    {
+      const int64_t jn = j0 + 64 + lane;
+      zn = jn < m ? zs[s + jn] : 0.0;
+      dn = jn < m ? ds[s + jn] : 0.0;
+      tn = jn < m ? ctype[s + jn] : 0;
+    }
+    const bool kept = lane < nu && !(rh * fabs(zl) <= tol);
+    const uint64_t mk = __ballot(kept), md = __ballot(lane < nu && !kept);
+    const uint64_t before = mk & below;
+    const int pl = before ? 63 - __builtin_clzll(before) : 0;
+    const double zq = __shfl(zl, pl, 64), dq = __shfl(dl, pl, 64);
+    const int32_t tq = __shfl(tl, pl, 64);
+    const double zb = before ? zq : zp, db = before ? dq : dp;
+    const int32_t tb = before ? tq : tp;
+    const bool has = kept && (before || prev >= 0);
+    if (__ballot(has && close(zb, db, zl, dl)) == 0) {
+      if (lane < nu && !kept) dfidx[s + ND + __popcll(md & below)] = (int32_t)(j0 + lane);
+      ND += __popcll(md);
+      if (mk) {
+        // every kept entry settles the kept entry before it
+        const int32_t base = prev >= 0 ? K : K - 1;
+        if (has) {
+          const int32_t pos = base + __popcll(before);
+          ndidx[s + pos] = (int32_t)(before ? j0 + pl : prev);
+          perm[s + pos] = tb;                      // child type for now, slot below
+        }
+        c1 += __popcll(__ballot(has && tb == 1));
+        c3 += __popcll(__ballot(has && tb == 3));
+        K = base + __popcll(mk);
+        const int last = 63 - __builtin_clzll(mk);
+        prev = j0 + last;
+        zp = lane_get(zl, last);
+        dp = lane_get(dl, last);
+        tp = __builtin_amdgcn_readlane(tl, last);
+      }
+      continue;
+    }
     for (int u = 0; u < nu; ++u) {
       const int64_t j = j0 + u;
-      const double zj = lane_bcast(zl, u);
+      const double zj = lane_get(zl, u);
       if (rh * fabs(zj) <= tol) {
         if (w0) dfidx[s + ND] = (int32_t)j;
         ++ND;
         continue;
       }
-      const double dj = lane_bcast(dl, u);
+      const double dj = lane_get(dl, u);
       const int32_t tj = __builtin_amdgcn_readlane(tl, u);
       if (prev < 0) {
         prev = j; zp = zj; dp = dj; tp = tj;
         continue;
       }
-      double sv = zp, cv = zj;
-      const double tt = hypot(cv, sv);
-      cv /= tt;
-      sv /= tt;
-      if (fabs((dj - dp) * cv * sv) <= tol) {
+      if (close(zp, dp, zj, dj)) {
+        const double tt = hypot(zj, zp);
+        const double cv = zj / tt, sv = zp / tt;
         const double dpn = cv * cv * dp + sv * sv * dj, djn = sv * sv * dp + cv * cv * dj;
         if (w0) {
           zs[s + j] = tt;
@@ -401,7 +469,6 @@ __global__ void __launch_bounds__(64) dc_deflate(const DcProb *pr, int lev, int6
     const int32_t k = k0 + lane;
     const int32_t t = k < K ? perm[s + k] : 0;
     const uint64_t b1 = __ballot(t == 1), b3 = __ballot(t == 3), b2 = __ballot(k < K && t != 1 && t != 3);
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     if (k < K) {
       const int32_t pos = t == 1 ? p1 + __popcll(b1 & below)
                                  : (t == 3 ? p3 + __popcll(b3 & below) : p2 + __popcll(b2 & below));
@@ -454,10 +521,13 @@ __global__ void dc_rotate(const DcProb *pr, int lev) {
 
 // Gathers the non-deflated columns (in d order, at their kept-column slots)
 // into T1[:, 0:K] and the deflated ones into T1[:, K:m].  Workgroup (row tile
-// x, y = merge g * nch + column chunk): a chunk of 256 output columns, thread
-// = row, the column indices uniform per iteration.
-constexpr int DC_GCOLS = 256;
-__global__ void dc_gather(const DcProb *pr, int lev, int64_t nch) {
+// x, y = merge g * nch + column chunk): a chunk of 64 output columns, their
+// column pairs looked up once into LDS (three dependent reads each), thread =
+// row.  Chunks of 256 columns with the look-up in the copy loop took 131 us a
+// level at order 450 (403 at 12816), this form 19 (154).
+constexpr int DC_GCOLS = 64;
+__global__ void __launch_bounds__(256) dc_gather(const DcProb *pr, int lev, int64_t nch) {
+  __shared__ int32_t cfrom[DC_GCOLS], cto[DC_GCOLS];
   const DcProb &P = pr[blockIdx.z];
   const int64_t g = blockIdx.y / nch, ch = blockIdx.y % nch;
   if (lev > P.h || g >= (P.L >> lev)) return;
@@ -465,25 +535,23 @@ __global__ void dc_gather(const DcProb *pr, int lev, int64_t nch) {
   const int32_t *src = P.w.src, *ndidx = P.w.ndidx, *dfidx = P.w.dfidx, *perm = P.w.perm;
   const int32_t *cnt = P.w.cnt;
   const MergeGeom q = dc_geom(n, P.L, lev, g);
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t o0 = ch * DC_GCOLS;
-  if (r >= q.m || o0 >= q.m) return;
+  const int64_t r0 = (int64_t)blockIdx.x * blockDim.x, o0 = ch * DC_GCOLS;
+  if (r0 >= q.m || o0 >= q.m) return;
   const int64_t s = q.s;
   const int32_t K = cnt[DC_CNT * g];
-  const int64_t o1 = (o0 + DC_GCOLS < q.m) ? o0 + DC_GCOLS : q.m;
+  const int nc = (int)(q.m - o0 < DC_GCOLS ? q.m - o0 : DC_GCOLS);
+  if ((int)threadIdx.x < nc) {
+    const int64_t o = o0 + threadIdx.x;
+    cfrom[threadIdx.x] = (int32_t)s + (o < K ? src[s + ndidx[s + o]] : src[s + dfidx[s + (o - K)]]);
+    cto[threadIdx.x] = (int32_t)s + (o < K ? perm[s + o] : (int32_t)o);
+  }
+  __syncthreads();
+  const int64_t r = r0 + threadIdx.x;
+  if (r >= q.m) return;
   const double *zrow = P.Z + (s + r);
   double *trow = P.w.T1 + (s + r);
-  for (int64_t o = o0; o < o1; ++o) {
-    int64_t from, to;
-    if (o < K) {
-      from = s + src[s + ndidx[s + o]];
-      to = s + perm[s + o];
-    } else {
-      from = s + src[s + dfidx[s + (o - K)]];
-      to = s + o;
-    }
-    trow[to * n] = zrow[from * ldz];
-  }
+#pragma unroll 8
+  for (int c = 0; c < nc; ++c) trow[cto[c] * n] = zrow[cfrom[c] * ldz];
 }
 
 // ------------------------------------------------------------------ merge: secular equation
@@ -657,7 +725,8 @@ __global__ void __launch_bounds__(256) dc_vectors(const DcProb *pr, int lev) {
 // Final ascending position of every eigenvalue of the merge (roots first in
 // the tie order, then deflated values by index), eigenvalue output and the
 // destination column of every T1 column.
-__global__ void dc_final_pos(const DcProb *pr, int lev) {
+__global__ void __launch_bounds__(256) dc_final_pos(const DcProb *pr, int lev) {
+  __shared__ double vals[256];
   const DcProb &P = pr[blockIdx.z];
   const int64_t g = blockIdx.y;
   if (lev > P.h || g >= (P.L >> lev)) return;
@@ -667,18 +736,31 @@ __global__ void dc_final_pos(const DcProb *pr, int lev) {
   int32_t *colmap = P.w.colmap;
   const MergeGeom q = dc_geom(P.n, P.L, lev, g);
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= q.m) return;
+  if ((int64_t)blockIdx.x * blockDim.x >= q.m) return;
   const int64_t s = q.s;
   const int K = cnt[DC_CNT * g];
   auto val = [&](int64_t x) -> double {
     return x < K ? dn[s + lamo[s + x]] + lamt[s + x] : ddef[s + (x - K)];
   };
-  const double v = val(e);
+  // ranks by counting, 256 values at a time staged in LDS (each thread looking
+  // every value up for itself: 691 us a level at order 12816, this form 99)
+  const double v = e < q.m ? val(e) : 0.0;
   int64_t pos = 0;
-  for (int64_t x = 0; x < q.m; ++x) {
-    const double u = val(x);
-    pos += (u < v) || (u == v && x < e);
+  for (int64_t x0 = 0; x0 < q.m; x0 += 256) {
+    __syncthreads();
+    if (x0 + threadIdx.x < q.m) vals[threadIdx.x] = val(x0 + threadIdx.x);
+    __syncthreads();
+    const int nx = (int)(q.m - x0 < 256 ? q.m - x0 : 256);
+    const int me = (int)(e - x0 < 0 ? 0 : (e - x0 > 256 ? 256 : e - x0));   // x < e <=> x - x0 < me
+    int cl = 0;
+#pragma unroll 8
+    for (int x = 0; x < nx; ++x) {
+      const double u = vals[x];
+      cl += (u < v) || (u == v && x < me);
+    }
+    pos += cl;
   }
+  if (e >= q.m) return;
   lam[s + pos] = v;
   colmap[s + e] = (int32_t)(s + pos);
 }
@@ -707,9 +789,11 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) dc_gemm(const DcProb *pr, int
   gemm_tile<false, A_N, B_N>(a, m0, n0, lds);
 }
 
-__global__ void dc_copy_def(const DcProb *pr, int lev) {
+// Deflated columns K + 64 ch .. of merge g (y = g * nch + ch) to their final
+// positions, thread = row.
+__global__ void __launch_bounds__(256) dc_copy_def(const DcProb *pr, int lev, int64_t nch) {
   const DcProb &P = pr[blockIdx.z];
-  const int64_t g = blockIdx.y;
+  const int64_t g = blockIdx.y / nch, ch = blockIdx.y % nch;
   if (lev > P.h || g >= (P.L >> lev)) return;
   const int64_t n = P.n, ldz = P.ldz;
   const int32_t *cnt = P.w.cnt, *colmap = P.w.colmap;
@@ -717,20 +801,18 @@ __global__ void dc_copy_def(const DcProb *pr, int lev) {
   double *Z = P.Z;
   const MergeGeom q = dc_geom(n, P.L, lev, g);
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t k0 = cnt[DC_CNT * g] + ch * DC_GCOLS;
   if (r >= q.m) return;
-  const int K = cnt[DC_CNT * g];
-  for (int64_t k = K; k < q.m; ++k)
+  const int64_t k1 = k0 + DC_GCOLS < q.m ? k0 + DC_GCOLS : q.m;
+#pragma unroll 8
+  for (int64_t k = k0; k < k1; ++k)
     Z[(q.s + r) + (int64_t)colmap[q.s + k] * ldz] = T1[(q.s + r) + (q.s + k) * n];
 }
 
 __global__ void dc_copy_out(const DcProb *pr) {
   const DcProb &P = pr[blockIdx.z];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < P.n) P.d[i] = P.w.lam[i];
-}
-
-__global__ void dc_info_init(const DcProb *pr) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *pr[blockIdx.z].info = 0;
+  if (i < P.n) P.d[i] = P.w.lam[i] * P.w.scl[1];
 }
 
 // ------------------------------------------------------------------ host
@@ -764,7 +846,7 @@ int stedc_grouped(const DcProb *pr, const int64_t *nh, int64_t count, hipStream_
     }
   }
   const unsigned Z = (unsigned)count;
-  hipLaunchKernelGGL(dc_info_init, dim3(1, 1, Z), dim3(64), 0, st, pr);
+  hipLaunchKernelGGL(dc_scale, dim3(1, 1, Z), dim3(1024), 0, st, pr);
   MMF_LAUNCH_CHECK();
   hipLaunchKernelGGL(dc_tear, dim3(cdiv(nmax, 256), 1, Z), dim3(256), 0, st, pr);
   MMF_LAUNCH_CHECK();
@@ -815,7 +897,7 @@ int stedc_grouped(const DcProb *pr, const int64_t *nh, int64_t count, hipStream_
     hipLaunchKernelGGL(dc_gemm, dim3(cdiv(maxm, GT_M), cdiv(maxm, GT_N), (unsigned)(Gmax * count)),
                        dim3(GEMM_THREADS), 0, st, pr, lev, Gmax);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(dc_copy_def, rows, dim3(256), 0, st, pr, lev);
+    hipLaunchKernelGGL(dc_copy_def, dim3(cdiv(maxm, 256), (unsigned)(Gmax * nch), Z), dim3(256), 0, st, pr, lev, nch);
     MMF_LAUNCH_CHECK();
   }
   hipLaunchKernelGGL(dc_copy_out, dim3(cdiv(nmax, 256), 1, Z), dim3(256), 0, st, pr);
@@ -831,7 +913,7 @@ inline DcProb dc_prob(int64_t n, double *d, const double *e, double *Z, int64_t 
   q.leaf_max = lim.leaf_iters;
   q.h = dc_depth(n);
   q.L = (int64_t)1 << q.h;
-  q.d = d; q.e = e; q.Z = Z; q.info = info;
+  q.d = d; q.e0 = e; q.e = w.es; q.Z = Z; q.info = info;
   q.w = w;
   return q;
 }

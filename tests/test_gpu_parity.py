@@ -173,6 +173,32 @@ def test_stedc_random(n):
     assert np.abs(Z.T @ Z - np.eye(n)).max() <= 1e-12 * max(1, math.log2(n + 1))
 
 
+# leaves of 16 rows, deflation chunks of 64, gather chunks of 64 columns
+@pytest.mark.parametrize("n", [15, 16, 17, 31, 32, 33, 63, 65, 127, 129, 255, 257])
+@pytest.mark.parametrize("scale", [1.0, 1e-150, 1e150])
+def test_stedc_leaf_and_chunk_edges(n, scale):
+    """Random tridiagonals, every other matrix with runs of equal diagonal
+    entries and tiny couplings (rotations beside plain deflation); scales at
+    which squares under- and overflow."""
+    torch, mmf = require_gpu()
+    rng = np.random.default_rng(n)
+    d, e = rng.normal(size=n), rng.normal(size=n - 1)
+    if n % 2:
+        d, e = np.round(d), np.where(np.arange(n - 1) % 3 == 0, 1e-12, e)
+    d, e = d * scale, e * scale
+    log(f"stedc edges n={n} scale={scale}")
+    wg, Zt, info = mmf.stedc(torch.from_numpy(d.copy()).cuda(), torch.from_numpy(e.copy()).cuda())
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    w, Z = wg.cpu().numpy() / scale, from_dev_cm(Zt)
+    T = (np.diag(d) + np.diag(e, 1) + np.diag(e, -1)) / scale
+    wo, _ = oracle.tridiag_eigh(d / scale, e / scale)
+    tol = 20 * n * np.finfo(float).eps * max(1.0, np.abs(wo).max())
+    assert np.abs(w - wo).max() <= tol
+    assert np.abs(T @ Z - Z * w).max() <= tol
+    assert np.abs(Z.T @ Z - np.eye(n)).max() <= 20 * n * np.finfo(float).eps
+
+
 @pytest.mark.parametrize("kind", ["glued", "constant", "wilkinson", "zero_offdiag", "floquet", "glued_2000",
                                   "mixed_2000"])
 def test_stedc_structured(kind):
@@ -327,6 +353,15 @@ def test_eigh_random_hermitian(n):
     rng = np.random.default_rng(1000 + n)
     A = rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))
     log(f"eigh random n={n}")
+    _check_eigh((A + A.conj().T) / 2)
+
+
+# slice lengths of the back-transformation's split-K products change here
+@pytest.mark.parametrize("n", [1024, 1025, 2049])
+def test_eigh_split_k_edges(n):
+    rng = np.random.default_rng(n)
+    A = rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))
+    log(f"eigh split-K n={n}")
     _check_eigh((A + A.conj().T) / 2)
 
 
