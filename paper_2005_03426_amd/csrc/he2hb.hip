@@ -33,6 +33,7 @@
 #include "gemm_core.h"
 #include "stages.h"
 #include "table.h"
+#include "wy.h"
 
 namespace mmf {
 
@@ -317,36 +318,24 @@ __global__ void __launch_bounds__(256) hb_sum_sp(const HbProb *pr, int64_t c0) {
   P.ws.Sp[e] = cadd(s0, s1);
 }
 
-// T of the panel (upper triangular BW x BW) from the summed Gram partials
-// (four partial sums per element of the recurrence); the betas go to the
-// band block R, reflectors of length one get tau = 0.
-__global__ void __launch_bounds__(256) hb_tmat(const HbProb *pr, int64_t c0) {
-  __shared__ cd T[BW][BW + 1];
-  __shared__ cd part[4][BW];
+// T of the panel (upper triangular BW x BW) from the summed Gram partials; the
+// betas go to the band block R, reflectors of length one get tau = 0.
+__global__ void __launch_bounds__(WY_THREADS) hb_tmat(const HbProb *pr, int64_t c0) {
+  static_assert(BW == WY_N, "one factor per panel");
+  __shared__ cd G[BW][WY_LD], T[BW][WY_LD];
+  __shared__ cd tau[BW];
   const HbProb &P = pr[blockIdx.z];
   HbPanel pp;
   if (!hb_panel(P, c0, pp)) return;
   const int nr = pp.nr;
   const HbWs &ws = P.ws;
   const int tid = threadIdx.x;
-  for (int e = tid; e < BW * BW; e += 256) T[e % BW][e / BW] = ws.Sp[e];
+#pragma unroll 8
+  for (int e = tid; e < BW * BW; e += WY_THREADS) G[e & 63][e >> 6] = ws.Sp[e];
+  if (tid < BW) tau[tid] = tid < nr ? P.tau[c0 + tid] : cmake(0.0, 0.0);
   __syncthreads();
-  const int r = tid & 63, qp = tid >> 6;
-  for (int kk = 0; kk < BW; ++kk) {
-    cd s = cmake(0.0, 0.0);
-    if (r < kk && kk < nr)
-      for (int j = r + qp; j < kk; j += 4) s = cadd(s, cmul(T[r][j], T[j][kk]));
-    part[qp][r] = s;
-    __syncthreads();
-    if (qp == 0) {
-      const cd tk = kk < nr ? P.tau[c0 + kk] : cmake(0.0, 0.0);
-      if (r < kk) T[r][kk] = cscale(cmul(tk, cadd(cadd(part[0][r], part[1][r]), cadd(part[2][r], part[3][r]))), -1.0);
-      else if (r == kk) T[r][kk] = tk;
-      else T[r][kk] = cmake(0.0, 0.0);
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < BW * BW; e += 256) ws.T[e] = T[e % BW][e / BW];
+  wy_tfactor<double>(G, T, tau);
+  for (int e = tid; e < BW * BW; e += WY_THREADS) ws.T[e] = T[e & 63][e >> 6];
   if (tid < nr) P.A[(c0 + BW + tid) + (c0 + tid) * P.lda] = cmake(ws.beta[tid], 0.0);
   if (tid >= nr && tid < pp.bw) P.tau[c0 + tid] = cmake(0.0, 0.0);
 }

@@ -28,10 +28,17 @@
 #include "twostage.h"
 #include "gemm_core.h"
 #include "table.h"
+#include "wy.h"
 
 namespace mmf {
 
-constexpr int BT_KCHUNK = 2048;   // rows per split-K slice
+// Rows per split-K slice of the products V^H Phi and V^H V: the output of
+// V^H Phi has only NB / 64 row tiles, so small orders need short slices to fill
+// the chip (one slice of 2048 at order 1715: 54 workgroups, 112 us a product; slices
+// of 256: 48), large ones have tiles enough and pay for partials.
+__host__ __device__ inline int64_t bt_kchunk(int64_t n) {
+  return n <= 1024 ? 128 : (n <= 2048 ? 256 : (n <= 4096 ? 512 : (n <= 8192 ? 1024 : 2048)));
+}
 
 template <typename R>
 struct BtWs {
@@ -59,7 +66,7 @@ inline BtWs<R> unmtr_ws(int64_t n, void *base, int64_t nc = -1) {
   BtWs<R> w;
   const int64_t ncol = nc >= 0 ? nc : n;
   w.nblk = n > 1 ? (n - 1 + NB - 1) / NB : 0;
-  w.nsplit = (n + BT_KCHUNK - 1) / BT_KCHUNK;
+  w.nsplit = (n + bt_kchunk(n) - 1) / bt_kchunk(n);
   if (w.nsplit < 1) w.nsplit = 1;
   w.Vp = cv.take<cx<R>>((size_t)(w.nblk ? bt_off<NB>(n, w.nblk) : 1));
   w.VpT = cv.take<cx<R>>((size_t)(w.nblk ? bt_off<NB>(n, w.nblk) : 1));
@@ -88,21 +95,26 @@ struct BtProb {
 };
 
 // Clean copy of block b = blockIdx.y: Vb[r', q] (r' = 0..mb-1 is row p+1+r'),
-// reflector p+q; one thread per row writes all NB columns.
+// reflector p+q; thread = row, 16 columns per workgroup (blockIdx.x = row tile
+// times the NB / 16 column chunks).
+constexpr int BT_PCOLS = 16;
 template <typename R, int NB>
-__global__ void bt_pack(const BtProb<R> *pr) {
+__global__ void __launch_bounds__(256) bt_pack(const BtProb<R> *pr) {
   const BtProb<R> &P = pr[blockIdx.z];
   const int64_t b = blockIdx.y;
   if (b >= P.nblk) return;
   const int64_t n = P.n, p = b * NB;
   const int kb = (int)((n - 1 - p < NB) ? n - 1 - p : NB);
   const int64_t mb = n - p - 1;
-  const int64_t rr = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int q0 = (int)(blockIdx.x % (NB / BT_PCOLS)) * BT_PCOLS;
+  const int64_t rr = (int64_t)(blockIdx.x / (NB / BT_PCOLS)) * 256 + threadIdx.x;
   if (rr >= mb) return;
   const int64_t row = p + 1 + rr;
   cx<R> *Vb = P.Vp + bt_off<NB>(n, b);
   cx<R> *Vt = P.VpT + bt_off<NB>(n, b);
-  for (int q = 0; q < NB; ++q) {
+#pragma unroll
+  for (int c = 0; c < BT_PCOLS; ++c) {
+    const int q = q0 + c;
     const int64_t i = p + q;
     cx<R> v = cmk<R>(0, 0);
     if (q < kb) {
@@ -115,8 +127,7 @@ __global__ void bt_pack(const BtProb<R> *pr) {
 }
 
 // Split-K slices of W1 = Vb^H Phi[p+1:, :] for block b: blockIdx.x = slice z
-// times the two 64-row tiles of W1; slice z covers rows [z*BT_KCHUNK, ...) of
-// the block; result to Wpart + z*NB*n.
+// times the 64-row tiles of W1; slice z covers rows [z kc, ...) of the block; result to Wpart + z*NB*n.
 template <typename R, int NB>
 __global__ void __launch_bounds__(GEMM_THREADS, 2) bt_splitk(const BtProb<R> *pr, int64_t b) {
   __shared__ R lds[GEMM_LDS_ELEMS];
@@ -125,13 +136,13 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) bt_splitk(const BtProb<R> *pr
   const int64_t n = P.n, p = b * NB, mb = n - p - 1;
   const int64_t z = blockIdx.x / (NB / GT_M);              // slice
   const int64_t m0 = (blockIdx.x % (NB / GT_M)) * GT_M;     // row tile of W1
-  const int64_t k0 = z * BT_KCHUNK;
+  const int64_t kc = bt_kchunk(n), k0 = z * kc;
   const int64_t n0 = (int64_t)blockIdx.y * GT_N;
   const int64_t nc = P.nc;
   if (k0 >= mb || n0 >= nc) return;
   // V^H from its explicit copy (A_N reads whole columns)
   const cx<R> *Vt = P.VpT + bt_off<NB>(n, b);
-  GemmArgs s = gemm_args(NB, nc, (mb - k0 < BT_KCHUNK) ? mb - k0 : BT_KCHUNK, Vt + k0 * (int64_t)NB, NB,
+  GemmArgs s = gemm_args(NB, nc, (mb - k0 < kc) ? mb - k0 : kc, Vt + k0 * (int64_t)NB, NB,
                          P.Phi + (p + 1) + k0, P.ldphi, P.Wpart + z * NB * nc, NB, 1.0, 0.0, 0.0, 0.0);
   gemm_tile_t<R, true, A_N, B_N>(s, m0, n0, lds);
 }
@@ -150,10 +161,10 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) bt_gram(const BtProb<R> *pr) 
   const int64_t z = blockIdx.y;
   if (b >= P.nblk || ti > tj) return;
   const int64_t n = P.n, p = b * NB, mb = n - p - 1;
-  const int64_t k0 = z * BT_KCHUNK;
+  const int64_t kc = bt_kchunk(n), k0 = z * kc;
   if (k0 >= mb) return;
   const cx<R> *Vb = P.Vp + bt_off<NB>(n, b);
-  GemmArgs s = gemm_args(NB, NB, (mb - k0 < BT_KCHUNK) ? mb - k0 : BT_KCHUNK, Vb + k0, mb, Vb + k0,
+  GemmArgs s = gemm_args(NB, NB, (mb - k0 < kc) ? mb - k0 : kc, Vb + k0, mb, Vb + k0,
                          mb, P.Gpart + (b * P.nsplit + z) * NB * NB, NB, 1.0, 0.0, 0.0, 0.0);
   gemm_tile_t<R, true, A_C, B_N>(s, (int64_t)ti * GT_M, (int64_t)tj * GT_N, lds);
 }
@@ -169,7 +180,7 @@ __global__ void bt_gram_sum(const BtProb<R> *pr) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (int64_t)NB * NB) return;
   const int64_t mb = P.n - b * NB - 1;
-  const int64_t ns = (mb + BT_KCHUNK - 1) / BT_KCHUNK;
+  const int64_t ns = (mb + bt_kchunk(P.n) - 1) / bt_kchunk(P.n);
   cx<R> *G = P.Gpart + b * P.nsplit * NB * NB;
   cx<R> s = G[e];
   for (int64_t z = 1; z < ns; ++z) s = cadd(s, G[z * NB * NB + e]);
@@ -177,13 +188,14 @@ __global__ void bt_gram_sum(const BtProb<R> *pr) {
 }
 
 // T of one 64-wide quarter h of block b (blockIdx.x = (NB/64) b + h) from the
-// diagonal block of its Gram matrix (one wavefront; thread = row of T); the
-// quarter's rows left of its diagonal block are zero.
+// diagonal block of its Gram matrix; the quarter's rows left of its diagonal
+// block are zero.
 template <typename R, int NB>
-__global__ void __launch_bounds__(64) bt_tmat(const BtProb<R> *pr) {
-  constexpr int H = 64, Q = NB / 64;
-  __shared__ cx<R> G[H][H];
-  __shared__ cx<R> T[H][H];
+__global__ void __launch_bounds__(WY_THREADS) bt_tmat(const BtProb<R> *pr) {
+  constexpr int H = WY_N, Q = NB / H;
+  __shared__ cx<R> G[H][WY_LD];
+  __shared__ cx<R> T[H][WY_LD];
+  __shared__ cx<R> tau[H];
   const BtProb<R> &P = pr[blockIdx.z];
   const int64_t b = blockIdx.x / Q;
   const int h = (int)(blockIdx.x % Q);
@@ -191,40 +203,37 @@ __global__ void __launch_bounds__(64) bt_tmat(const BtProb<R> *pr) {
   const int64_t n = P.n;
   const int64_t p = b * NB;
   const int kb = (int)((n - 1 - p < NB) ? n - 1 - p : NB);
-  int kh = kb - h * H;
-  kh = kh < 0 ? 0 : (kh > H ? H : kh);
-  const int r = threadIdx.x;
+  const int kh = kb - h * H;                         // reflectors of this quarter (may be <= 0)
+  const int tid = threadIdx.x;
   const cx<R> *Gs = P.Gpart + b * P.nsplit * NB * NB;
-  for (int c = 0; c < H; ++c) {
+#pragma unroll 8
+  for (int e = tid; e < H * H; e += WY_THREADS) {
+    const int r = e & 63, c = e >> 6;
     G[r][c] = Gs[(h * H + r) + (int64_t)(h * H + c) * NB];
-    T[r][c] = cmk<R>(0, 0);
   }
+  if (tid < H) tau[tid] = tid < kh ? P.tau[p + h * H + tid] : cmk<R>(0, 0);
   __syncthreads();
-  for (int k = 0; k < kh; ++k) {
-    const cx<R> tk = P.tau[p + h * H + k];
-    // T[r,k] = -tau_k sum_{j<k} T[r,j] G[j,k]   (r < k)
-    cx<R> s = cmk<R>(0, 0);
-    if (r < k)
-      for (int j = r; j < k; ++j) s = cadd(s, cmul(T[r][j], G[j][k]));
-    __syncthreads();
-    if (r < k) T[r][k] = cscale(cmul(tk, s), R(-1));
-    if (r == k) T[r][k] = tk;
-    __syncthreads();
-  }
+  wy_tfactor<R>(G, T, tau);
   cx<R> *Tb = P.Tm + b * NB * NB;
-  for (int c = 0; c < H; ++c) Tb[(h * H + r) + (int64_t)(h * H + c) * NB] = T[r][c];
-  for (int c = 0; c < h * H; ++c) Tb[(h * H + r) + (int64_t)c * NB] = cmk<R>(0, 0);
+  for (int e = tid; e < H * H; e += WY_THREADS) {
+    const int r = e & 63, c = e >> 6;
+    Tb[(h * H + r) + (int64_t)(h * H + c) * NB] = T[r][c];
+  }
+  for (int e = tid; e < H * H * h; e += WY_THREADS)
+    Tb[(h * H + (e & 63)) + (int64_t)(e >> 6) * NB] = cmk<R>(0, 0);
 }
 
 // Join of neighbouring L x L pieces of T (L = 64, 128, ...; each already
 // complete): pair j of block b covers rows/columns o1 = 2 j L .. and
 // o2 = o1 + L ..; the upper-right piece is T_12 = -T_1 (V_1^H V_2) T_2.  A
-// workgroup forms a 64-column slab s of X = G_12 T_2 in LDS (thread =
-// element of X), then the same slab of T_12 = -T_1 X.  blockIdx.x =
-// ((b npair) + j) nslab + s with npair = NB / (2 L), nslab = L / 64.
+// workgroup forms a 64-column slab s of X = G_12 T_2 on the matrix cores (kept
+// in the unused lower-left piece of the Gram matrix), then the same slab of
+// T_12 = -T_1 X.  blockIdx.x = ((b npair) + j) nslab + s with
+// npair = NB / (2 L), nslab = L / 64.  Dots of one thread per element took
+// 214 us at L = 64, this form 40.
 template <typename R, int NB>
-__global__ void __launch_bounds__(256) bt_join(const BtProb<R> *pr, int L) {
-  __shared__ cx<R> X[NB / 2][65];
+__global__ void __launch_bounds__(GEMM_THREADS, 2) bt_join(const BtProb<R> *pr, int L) {
+  __shared__ R lds[GEMM_LDS_ELEMS];
   const BtProb<R> &P = pr[blockIdx.z];
   const int npair = NB / (2 * L), nslab = L / 64;
   int64_t idx = blockIdx.x;
@@ -233,22 +242,20 @@ __global__ void __launch_bounds__(256) bt_join(const BtProb<R> *pr, int L) {
   const int j = (int)(idx % npair);
   const int64_t b = idx / npair;
   if (b >= P.nblk) return;
-  const int o1 = 2 * j * L, o2 = o1 + L;
-  const cx<R> *G = P.Gpart + b * P.nsplit * NB * NB;
+  const int64_t o1 = 2 * j * L, o2 = o1 + L;
+  cx<R> *G = P.Gpart + b * P.nsplit * NB * NB;
   cx<R> *Tb = P.Tm + b * NB * NB;
-  for (int e = threadIdx.x; e < L * 64; e += 256) {
-    const int i = e % L, c = e / L, cc = 64 * sl + c;
-    cx<R> s = cmk<R>(0, 0);
-    for (int k = 0; k <= cc; ++k)
-      s = cadd(s, cmul(G[(o1 + i) + (int64_t)(o2 + k) * NB], Tb[(o2 + k) + (int64_t)(o2 + cc) * NB]));
-    X[i][c] = s;
+  cx<R> *X = G + o2 + (o1 + 64 * sl) * NB, *T12 = Tb + o1 + (o2 + 64 * sl) * NB;
+  const GemmArgs gx = gemm_args(L, 64, L, G + o1 + o2 * NB, NB, Tb + o2 + (o2 + 64 * sl) * NB, NB, X, NB, 1.0, 0.0,
+                                0.0, 0.0);
+  for (int i = 0; i < L; i += GT_M) {
+    gemm_tile_t<R, true, A_N, B_N>(gx, i, 0, lds);
+    __syncthreads();
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < L * 64; e += 256) {
-    const int i = e % L, c = e / L;
-    cx<R> s = cmk<R>(0, 0);
-    for (int k = i; k < L; ++k) s = cadd(s, cmul(Tb[(o1 + i) + (int64_t)(o1 + k) * NB], X[k][c]));
-    Tb[(o1 + i) + (int64_t)(o2 + 64 * sl + c) * NB] = cscale(s, R(-1));
+  const GemmArgs gt = gemm_args(L, 64, L, Tb + o1 + o1 * NB, NB, X, NB, T12, NB, -1.0, 0.0, 0.0, 0.0);
+  for (int i = 0; i < L; i += GT_M) {
+    gemm_tile_t<R, true, A_N, B_N>(gt, i, 0, lds);
+    __syncthreads();
   }
 }
 
@@ -276,7 +283,7 @@ __global__ void bt_reduce(const BtProb<R> *pr, int64_t b) {
   const int64_t nc = P.nc;
   if (e >= NB * nc) return;
   const int64_t mb = P.n - b * NB - 1;
-  const int64_t nsl = (mb + BT_KCHUNK - 1) / BT_KCHUNK;
+  const int64_t nsl = (mb + bt_kchunk(P.n) - 1) / bt_kchunk(P.n);
   cx<R> s = cmk<R>(0, 0);
   for (int64_t z = 0; z < nsl; ++z) s = cadd(s, P.Wpart[z * NB * nc + e]);
   P.W2[e] = s;
@@ -334,10 +341,15 @@ int unmtr_grouped(const BtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
   if (ncols <= 0) return MMF_OK;
   const unsigned Z = (unsigned)count;
   const int64_t nblk = nmax > 1 ? (nmax - 1 + NB - 1) / NB : 0;
-  const int64_t nsplit = (nmax + BT_KCHUNK - 1) / BT_KCHUNK;
+  int64_t nsplit = 1;                                 // most slices of any problem
+  for (int64_t c = 0; c < count; ++c) {
+    const int64_t sl = (nh[c] + bt_kchunk(nh[c]) - 1) / bt_kchunk(nh[c]);
+    nsplit = sl > nsplit ? sl : nsplit;
+  }
   // 1. clean copies of every reflector block (Phi may alias V)
   if (nblk > 0 && (phases & 1)) {
-    hipLaunchKernelGGL((bt_pack<R, NB>), dim3(cdiv(nmax - 1, 256), (unsigned)nblk, Z), dim3(256), 0, st, pr);
+    hipLaunchKernelGGL((bt_pack<R, NB>), dim3(cdiv(nmax - 1, 256) * (NB / BT_PCOLS), (unsigned)nblk, Z), dim3(256), 0, st,
+                       pr);
     MMF_LAUNCH_CHECK();
     // 2. T factors: Gram partials, their sum, the 64-wide quarters, then the
     // pairwise joins (64 + 64, 128 + 128, ...)
@@ -348,7 +360,7 @@ int unmtr_grouped(const BtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
     hipLaunchKernelGGL((bt_gram_sum<R, NB>), dim3(cdiv((int64_t)NB * NB, 256), (unsigned)nblk, Z), dim3(256), 0, st,
                        pr);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL((bt_tmat<R, NB>), dim3((unsigned)(Q * nblk), 1, Z), dim3(64), 0, st, pr);
+    hipLaunchKernelGGL((bt_tmat<R, NB>), dim3((unsigned)(Q * nblk), 1, Z), dim3(WY_THREADS), 0, st, pr);
     MMF_LAUNCH_CHECK();
     for (int L = 64; L < NB; L *= 2) {
       hipLaunchKernelGGL((bt_join<R, NB>), dim3((unsigned)(nblk * (NB / (2 * L)) * (L / 64)), 1, Z), dim3(256), 0,
@@ -363,7 +375,11 @@ int unmtr_grouped(const BtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
   // 4. apply blocks last to first (a problem with fewer blocks idles until its last one)
   for (int64_t b = nblk - 1; b >= 0; --b) {
     const int64_t mb = nmax - b * NB - 1;
-    const int64_t nsl = (mb + BT_KCHUNK - 1) / BT_KCHUNK;
+    int64_t nsl = 1;
+    for (int64_t c = 0; c < count; ++c) {
+      const int64_t mc = nh[c] - b * NB - 1, kc = bt_kchunk(nh[c]);
+      if (mc > 0 && (mc + kc - 1) / kc > nsl) nsl = (mc + kc - 1) / kc;
+    }
     hipLaunchKernelGGL((bt_splitk<R, NB>), dim3((unsigned)(nsl * (NB / GT_M)), cdiv(ncols, GT_N), Z),
                        dim3(GEMM_THREADS), 0, st, pr, b);
     MMF_LAUNCH_CHECK();
