@@ -28,7 +28,7 @@
 //     workgroup) and leaves its norm partials.
 // Four launches per column (reflector, product, u, w with the next column)
 // took 18.5 us per column at order 82, 23 at 450 and 31.5 at 1715
-// (profiled); the two take 3.1 (all in the tail), 11.3 and 13.2.
+// (profiled); the two take 3.1 (all in the tail), 10.0 and 11.9.
 // The last HT_TAIL rows of every matrix (all of a smaller one) are reduced by
 // one workgroup in LDS (ht_tail).
 // All sums are over fixed partitions in fixed order (deterministic).
@@ -197,11 +197,25 @@ __device__ __forceinline__ void ht_column_scalars(const HtProb<R> &q, int64_t i,
   ht_scalars<R>(alpha, wave_sum(s), beta, tau, scale);
 }
 
-// v[r] of column i from the raw column (r < mpad)
+// v[r] of column i from the raw column's entry xr
 template <typename R>
-__device__ __forceinline__ cx<R> ht_v(const MMF_GLOBAL cx<R> *x, int64_t r, int64_t i, int64_t n, cx<R> scale) {
-  const cx<R> v = cmul(gload(x + r), scale);
+__device__ __forceinline__ cx<R> ht_v(cx<R> xr, int64_t r, int64_t i, int64_t n, cx<R> scale) {
+  const cx<R> v = cmul(xr, scale);
   return (r <= i || r >= n) ? cmk<R>(0, 0) : (r == i + 1 ? cmk<R>(1, 0) : v);
+}
+
+// d += a vc and t += conj(at) vr (at = a, or zero on the diagonal) in fused
+// operations: the same bits in every form of the product
+template <typename R>
+__device__ __forceinline__ void ht_tile_fma(cx<R> a, cx<R> at, cx<R> vc, cx<R> vr, cx<R> &d, cx<R> &t) {
+  d.re = fma(a.re, vc.re, d.re);
+  d.re = fma(-a.im, vc.im, d.re);
+  d.im = fma(a.re, vc.im, d.im);
+  d.im = fma(a.im, vc.re, d.im);
+  t.re = fma(at.re, vr.re, t.re);
+  t.re = fma(at.im, vr.im, t.re);
+  t.im = fma(at.re, vr.im, t.im);
+  t.im = fma(-at.im, vr.re, t.im);
 }
 
 template <typename R> struct NtVec;
@@ -227,7 +241,7 @@ __device__ void ht_dots_wave(const HtProb<R> &pq, int64_t i, int k, int g, int q
 #pragma unroll 4
   for (int j = lane; j < dr; j += 64) {
     const int64_t r = r0 + j;
-    if (r < n) s = cadd(s, cmulc(gload(X + r), ht_v<R>(x, r, i, n, scale)));
+    if (r < n) s = cadd(s, cmulc(gload(X + r), ht_v<R>(gload(x + r), r, i, n, scale)));
   }
   const R re = wave_sum(s.re), im = wave_sum(s.im);
   if (lane == 0) ((MMF_GLOBAL cx<R> *)pq.dots)[(int64_t)g * 2 * HT_NB + which * HT_NB + q] = cmk<R>(re, im);
@@ -252,12 +266,17 @@ __device__ void ht_dots_wave(const HtProb<R> &pq, int64_t i, int k, int g, int q
 // product stays in registers over the strip.  Columns left of i+1 carry v = 0.
 // Bound: HBM at large orders; below about 3000 rows, where the strips of one
 // tile leave no second tile to overlap with, one launch's dependent loads.
+// Without STRIP (every matrix of the launch has single-tile strips) all tiles
+// take the masked form, which needs no second tile's registers (145 against
+// 240) and loads x ahead too.  With the wide ht_finish: order 450 6.07 -> 5.55
+// ms, 1715 24.8 -> 22.5 ms, 5000 155.4 -> 149.8 ms, 48 matrices 128.2 -> 125.1
+// ms (whole calls).
 // NT: the tiles are read non-temporally, so that a triangle far larger than
 // the 256 MB last-level cache does not sweep everything else out of it.  With
 // ordinary reads the reduction takes 26.7 ms against 28.5 at order 2048, 84.0
 // against 93.3 at 4000, 184.5 against 203.4 at 6000, 389.8 against 396.2 at
 // 8000, but 947.6 against 897.3 at 11000: NT above HV_NT_BYTES.
-template <typename R, bool NT>
+template <typename R, bool NT, bool STRIP>
 __global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t p, int k, int dot_slot) {
   typedef cx<R> C;
   typedef typename NtVec<R>::v nv;
@@ -296,8 +315,9 @@ __global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t
   C vc[4], tacc[4];
   R beta, gpart = 0;
   C tau, scale;
-  if (slot < 2) {
-    // ------------------------------------------------ one masked tile
+  if (!STRIP || slot < 2) {
+    // ------------------------------------------------ one tile, masked; its
+    // entries and the raw x of its rows and columns before the scalars
     const int64_t row0 = first * HV_T + rg;
     C a[4][4];
 #pragma unroll
@@ -309,23 +329,26 @@ __global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t
         const C t = gload(A + (ok ? row + col * lda : 0));
         a[j][qq] = cmk<R>(ok ? t.re : R(0), ok && row != col ? t.im : R(0));
       }
-    ht_column_scalars<R>(q, i, beta, tau, scale);
     C vr[4], dacc[4];
 #pragma unroll
     for (int qq = 0; qq < 4; ++qq) {
-      vr[qq] = ht_v<R>(x, row0 + 16 * qq, i, n, scale);
+      vr[qq] = gload(x + row0 + 16 * qq);
+      vc[qq] = gload(x + col0 + qq);
+    }
+    ht_column_scalars<R>(q, i, beta, tau, scale);
+#pragma unroll
+    for (int qq = 0; qq < 4; ++qq) {
+      vr[qq] = ht_v<R>(vr[qq], row0 + 16 * qq, i, n, scale);
       dacc[qq] = cmk<R>(0, 0);
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      vc[j] = ht_v<R>(x, col0 + j, i, n, scale);
+      vc[j] = ht_v<R>(vc[j], col0 + j, i, n, scale);
       tacc[j] = cmk<R>(0, 0);
 #pragma unroll
       for (int qq = 0; qq < 4; ++qq) {
-        dacc[qq] = cadd(dacc[qq], cmul(a[j][qq], vc[j]));
         const bool dg = row0 + 16 * qq == col0 + j;
-        const C t = cmulc(a[j][qq], vr[qq]);
-        tacc[j] = cadd(tacc[j], cmk<R>(dg ? R(0) : t.re, dg ? R(0) : t.im));
+        ht_tile_fma<R>(a[j][qq], dg ? cmk<R>(0, 0) : a[j][qq], vc[j], vr[qq], dacc[qq], tacc[j]);
         gpart += dg ? a[j][qq].re * cabs2(vr[qq]) : R(0);
       }
     }
@@ -340,7 +363,7 @@ __global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t
           cadd(cadd(red[0][0][tid], red[0][1][tid]), cadd(red[0][2][tid], red[0][3][tid]));
       const int64_t r = bj * HV_T + tid;
       if (slot == 0 && r > i && r < n) {            // this block's rows of v
-        const C v = ht_v<R>(x, r, i, n, scale);
+        const C v = ht_v<R>(gload(x + r), r, i, n, scale);
         MMF_GLOBAL C *P3 = (MMF_GLOBAL C *)q.P3;
         ((MMF_GLOBAL C *)q.A)[r + i * lda] = v;
         P3[r + (int64_t)k * n] = v;
@@ -380,16 +403,7 @@ __global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t
       for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int qq = 0; qq < 4; ++qq) {
-          const C a = b[j][qq];
-          // dacc += a vc ;  tacc += conj(a) vr
-          dacc[qq].re = fma(a.re, vc[j].re, dacc[qq].re);
-          dacc[qq].re = fma(-a.im, vc[j].im, dacc[qq].re);
-          dacc[qq].im = fma(a.re, vc[j].im, dacc[qq].im);
-          dacc[qq].im = fma(a.im, vc[j].re, dacc[qq].im);
-          tacc[j].re = fma(a.re, vr[qq].re, tacc[j].re);
-          tacc[j].re = fma(a.im, vr[qq].im, tacc[j].re);
-          tacc[j].im = fma(a.re, vr[qq].im, tacc[j].im);
-          tacc[j].im = fma(-a.im, vr[qq].re, tacc[j].im);
+          ht_tile_fma<R>(b[j][qq], b[j][qq], vc[j], vr[qq], dacc[qq], tacc[j]);
         }
 #pragma unroll
       for (int qq = 0; qq < 4; ++qq) {
@@ -406,7 +420,7 @@ __global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t
     __builtin_amdgcn_sched_barrier(0);
     ht_column_scalars<R>(q, i, beta, tau, scale);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { vc[j] = ht_v<R>(x, col0 + j, i, n, scale); tacc[j] = cmk<R>(0, 0); }
+    for (int j = 0; j < 4; ++j) { vc[j] = ht_v<R>(gload(x + col0 + j), col0 + j, i, n, scale); tacc[j] = cmk<R>(0, 0); }
     int t = 0;
     for (int64_t bi = first; bi < bi1; bi += 2, t += 2) {
       step(b0t, b1t, bi, t);
@@ -430,18 +444,22 @@ __global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t
 
 // Column i = p + k after ht_column: w = tau u - (|tau|^2 g / 2) v, and inside
 // the panel column i+1 updated by the k+1 reflectors so far.  One workgroup
-// per 64-row block; its four wavefronts split the partial sums and the panel
-// columns (each V, W entry is read once for both corrections), combined in
-// LDS in fixed order.  Wavefront 3 also forms w[i+1].
-// Latency bound: three dependent memory round trips (table, partials, stores)
-// and two barriers; everything that does not depend on the sums is loaded first.
-template <typename R>
-__global__ void __launch_bounds__(256) ht_finish(const HtProb<R> *pr, int64_t p, int k) {
+// per 64-row block.  Parts 0 .. 3 (a wavefront each) split the partial sums
+// and the panel columns (each V, W entry is read once for both corrections),
+// combined in LDS in fixed order; 4 sums the panel products, 5 and 6 the
+// partials of v^H A v, 7 forms w[i+1].
+// Latency bound (table, partials, stores, two barriers), so with WIDE the sums
+// that feed the scalars run beside the row sums, in eight wavefronts: 4.9 us
+// at order 1715 against 6.3 in four wavefronts that each take two parts.  Once
+// there are more workgroups than CUs the narrow form is the faster one (48
+// matrices together: 7.4 us against 9.0); both give the same bits.
+template <typename R, bool WIDE>
+__global__ void __launch_bounds__(WIDE ? 512 : 256) ht_finish(const HtProb<R> *pr, int64_t p, int k) {
   typedef cx<R> C;
   constexpr int QW = HT_NB / 4;
   __shared__ C x1[HT_NB], x2[HT_NB], cw[HT_NB], cv[HT_NB];
   __shared__ C part[4][HV_T], apart[4][HV_T];
-  __shared__ R sh[4];
+  __shared__ R sh[2], xxs;
   __shared__ C w1s;
   const HtProb<R> &pq = pr[blockIdx.z];
   const int64_t n = pq.n, lda = pq.lda, mpad = pq.mpad, nchmax = pq.nchmax, i = p + k;
@@ -460,24 +478,24 @@ __global__ void __launch_bounds__(256) ht_finish(const HtProb<R> *pr, int64_t p,
   const int lane = tid & 63, wave = tid >> 6;
   const int64_t rho = (b0 + lbi) * HV_T + lane;     // absolute row
   const bool live = rho > i && rho < n;
-  // ---- loads that wait for nothing else: V, W of this row, the partials
-  C vq[QW], wq[QW], u = cmk<R>(0, 0);
-#pragma unroll
-  for (int j = 0; j < QW; ++j) {
-    const int qc = wave + 4 * j;
-    vq[j] = wq[j] = cmk<R>(0, 0);
-    if (qc < k && live) {
-      vq[j] = gload(P3 + rho + (int64_t)qc * n);
-      wq[j] = gload(P3 + rho + (int64_t)(HT_NB + qc) * n);
-    }
-  }
   const C tau = gload((const MMF_GLOBAL C *)pq.tau + i);
-  C v = cmk<R>(0, 0), a = cmk<R>(0, 0);
-  if (wave == 0 && live) {
-    v = gload(P3 + rho + (int64_t)k * n);
-    if (next) a = gload((const MMF_GLOBAL C *)pq.A + rho + (i + 1) * lda);
-  }
-  {
+  C vq[QW], wq[QW], u = cmk<R>(0, 0), v = cmk<R>(0, 0), a = cmk<R>(0, 0), r1 = cmk<R>(0, 0);
+  const int part2 = WIDE ? wave : wave + 4;         // 4 .. 7: the second part of this wavefront
+  if (wave < 4) {
+    // ---- V, W of this row, the partials of u
+#pragma unroll
+    for (int j = 0; j < QW; ++j) {
+      const int qc = wave + 4 * j;
+      vq[j] = wq[j] = cmk<R>(0, 0);
+      if (qc < k && live) {
+        vq[j] = gload(P3 + rho + (int64_t)qc * n);
+        wq[j] = gload(P3 + rho + (int64_t)(HT_NB + qc) * n);
+      }
+    }
+    if (wave == 0 && live) {
+      v = gload(P3 + rho + (int64_t)k * n);
+      if (next) a = gload((const MMF_GLOBAL C *)pq.A + rho + (i + 1) * lda);
+    }
     // direct partials of block columns wave, wave + 4, ... (four independent
     // accumulators), transposed partials of this block column's slots
     const MMF_GLOBAL C *pc = pdir + lbi * HV_T + lane;
@@ -500,60 +518,63 @@ __global__ void __launch_bounds__(256) ht_finish(const HtProb<R> *pr, int64_t p,
     for (int c = wave; c < nin; c += 4) u2 = cadd(u2, gload(pt + (int64_t)(c + 2) * HV_T));
     u = cadd(cadd(u0, u1), cadd(u2, u3));
   }
-  // ---- panel products, v^H A v (partials per thread, wavefront sums in sh)
-  const int gdot = (int)((n - i - 1 + dr - 1) / dr);
-  if (tid < 2 * k) {
-    const int qc = tid % k, which = tid / k;
+  if (part2 == 4) {
+    // ---- panel products x1 (lanes < k), x2 (the next k) and 2 Re(x2^H x1)
+    const int gdot = (int)((n - i - 1 + dr - 1) / dr);
     C s = cmk<R>(0, 0);
+    const bool on = lane < 2 * k;
+    const int qc = lane < k ? lane : lane - k;
+    if (on) {
+      const MMF_GLOBAL C *dp = dots + (lane < k ? 0 : HT_NB) + qc;
 #pragma unroll 4
-    for (int g = 0; g < gdot; ++g) s = cadd(s, gload(dots + (int64_t)g * 2 * HT_NB + which * HT_NB + qc));
-    if (which == 0) x1[qc] = s; else x2[qc] = s;
-  }
-  {
-    const int nbl = (int)(nb - b0);
+      for (int g = 0; g < gdot; ++g) s = cadd(s, gload(dp + (int64_t)g * 2 * HT_NB));
+      if (lane < k) x1[qc] = s; else x2[qc] = s;
+    }
+    const R ore = __shfl(s.re, (lane + k) & 63, 64), oim = __shfl(s.im, (lane + k) & 63, 64);
+    const R xx = wave_sum(lane < k ? s.re * ore + s.im * oim : R(0));
+    if (lane == 0) xxs = xx;
+  } else if (part2 == 5 || part2 == 6) {
+    // ---- v^H A v
+    const int nbl = (int)(nb - b0), t = (part2 - 5) * 64 + lane;
     const int nsl = ht_slots(n, i, ch);
     R s = 0;
-    for (int lb = tid >> 3; lb < nbl; lb += 32)
-      for (int c = tid & 7; c < nsl; c += 8) s += gload(sparts + lb * nchmax + c);
+    for (int lb = t >> 3; lb < nbl; lb += 16)
+#pragma unroll 4
+      for (int c = t & 7; c < nsl; c += 8) s += gload(sparts + lb * nchmax + c);
     s = wave_sum(s);
-    if (lane == 0) sh[wave] = s;
-  }
-  // wavefront 3: row i+1 of the partials and of V, W
-  C r1 = cmk<R>(0, 0);
-  if (wave == 3) {
+    if (lane == 0) sh[part2 - 5] = s;
+  } else if (part2 == 7) {
+    // ---- row i+1 of the partials and of V, W
     const int row = (int)(i + 1 - b0 * HV_T);
     const int nin = ht_slots(n, i, ch) - 2;
     const bool edge = nb != nfull && b0 < nb - 1;
-    for (int c = lane; c < nin; c += 64) r1 = cadd(r1, gload(ptrn + (int64_t)(c + 2) * HV_T + row));
-    if (lane == 0) r1 = cadd(r1, cadd(gload(pdir + row), gload(ptrn + row)));
-    if (lane == 1 && edge) r1 = cadd(r1, gload(ptrn + HV_T + row));
     if (lane < k) {
       cv[lane] = cconj(gload(P3 + (i + 1) + (int64_t)lane * n));
       cw[lane] = cconj(gload(P3 + (i + 1) + (int64_t)(HT_NB + lane) * n));
     }
+    for (int c = lane; c < nin; c += 64) r1 = cadd(r1, gload(ptrn + (int64_t)(c + 2) * HV_T + row));
+    if (lane == 0) r1 = cadd(r1, cadd(gload(pdir + row), gload(ptrn + row)));
+    if (lane == 1 && edge) r1 = cadd(r1, gload(ptrn + HV_T + row));
   }
   __syncthreads();
   // ---- alpha = -|tau|^2 g / 2 with g = v^H A v - 2 Re(x2^H x1)
-  R alpha = 0;
-  if (wave == 0 || wave == 3) {
-    const R xx = lane < k ? x2[lane].re * x1[lane].re + x2[lane].im * x1[lane].im : R(0);
-    const R g = ((sh[0] + sh[1]) + (sh[2] + sh[3])) - 2 * wave_sum(xx);
-    alpha = R(-0.5) * cabs2(tau) * g;
-  }
-  C as = cmk<R>(0, 0);
+  const R alpha = R(-0.5) * cabs2(tau) * ((sh[0] + sh[1]) - 2 * xxs);
+  if (wave < 4) {
+    C as = cmk<R>(0, 0);
 #pragma unroll
-  for (int j = 0; j < QW; ++j) {
-    const int qc = wave + 4 * j;
-    if (qc < k) {
-      u = csub(u, cmul(vq[j], x1[qc]));
-      u = csub(u, cmul(wq[j], x2[qc]));
-      as = cadd(as, cmul(vq[j], cw[qc]));
-      as = cadd(as, cmul(wq[j], cv[qc]));
+    for (int j = 0; j < QW; ++j) {
+      const int qc = wave + 4 * j;
+      if (qc < k) {
+        u = csub(u, cmul(vq[j], x1[qc]));
+        u = csub(u, cmul(wq[j], x2[qc]));
+        as = cadd(as, cmul(vq[j], cw[qc]));
+        as = cadd(as, cmul(wq[j], cv[qc]));
+      }
     }
+    part[wave][lane] = u;
+    apart[wave][lane] = as;
   }
-  part[wave][lane] = u;
-  apart[wave][lane] = as;
-  if (wave == 3) {                                  // w[i+1] = tau u[i+1] + alpha (v[i+1] = 1)
+  if (part2 == 7) {                                 // w[i+1] = tau u[i+1] + alpha (v[i+1] = 1)
     if (lane < k) {
       r1 = csub(r1, cmul(cconj(cv[lane]), x1[lane]));
       r1 = csub(r1, cmul(cconj(cw[lane]), x2[lane]));
@@ -591,7 +612,7 @@ __global__ void __launch_bounds__(256) ht_finish(const HtProb<R> *pr, int64_t p,
 // product u = A v and the rank-2 update A -= v w^H + w v^H over all rows
 // (32-lane units: row group, column part).  The scalars are derived by every
 // wavefront for itself; three barriers per column.  A chain of m columns:
-// latency bound, 2.0 us per column (order 66) to 3.1 (82) against 11.3 for
+// latency bound, 2.0 us per column (order 66) to 3.1 (82) against 10.0 for
 // the two launches at order 450.
 template <typename R>
 __global__ void __launch_bounds__(TAIL_THREADS) ht_tail(const HtProb<R> *pr) {
@@ -728,10 +749,11 @@ int hetrd_grouped(const HtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
   const unsigned Z = (unsigned)count;
   const int64_t ps = ht_tail_start(nmax);
   for (int64_t p = 0; p < ps; p += HT_NB) {
-    int nslot = 2;                                   // most slots of any matrix in this panel
+    int nslot = 2, strip = 1;                        // most slots and longest strip of any matrix in this panel
     for (int64_t c = 0; c < count; ++c) {
       if (p >= ht_tail_start(nh[c])) continue;
-      const int sl = ht_slots(nh[c], p, ht_strip(nh[c], p));
+      const int ch = ht_strip(nh[c], p), sl = ht_slots(nh[c], p, ch);
+      strip = ch > strip ? ch : strip;
       nslot = sl > nslot ? sl : nslot;
     }
     hipLaunchKernelGGL(ht_colnorm<R>, dim3(cdiv(cdiv(nmax, HV_T) - p / HV_T, 4), 1, Z), dim3(256), 0, st, pr, p);
@@ -744,9 +766,11 @@ int hetrd_grouped(const HtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
       const int ks = ktimer_begin(sizeof(R) == 8 ? "hemv" : "hemv_c64", st);
       const dim3 grid((unsigned)nbl, (unsigned)(nslot + dot_rows), Z);
       if ((int64_t)sizeof(cx<R>) * (nmax - p) * (nmax - p) / 2 > HV_NT_BYTES)
-        hipLaunchKernelGGL((ht_column<R, true>), grid, dim3(256), 0, st, pr, p, k, nslot);
+        hipLaunchKernelGGL((ht_column<R, true, true>), grid, dim3(256), 0, st, pr, p, k, nslot);
+      else if (strip > 1)
+        hipLaunchKernelGGL((ht_column<R, false, true>), grid, dim3(256), 0, st, pr, p, k, nslot);
       else
-        hipLaunchKernelGGL((ht_column<R, false>), grid, dim3(256), 0, st, pr, p, k, nslot);
+        hipLaunchKernelGGL((ht_column<R, false, false>), grid, dim3(256), 0, st, pr, p, k, nslot);
       MMF_LAUNCH_CHECK();
       if (ks >= 0) {
         // algorithmic bytes: the lower triangle of every trailing matrix, read
@@ -758,7 +782,10 @@ int hetrd_grouped(const HtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
         }
         ktimer_end(ks, st, bytes);
       }
-      hipLaunchKernelGGL(ht_finish<R>, dim3((unsigned)nbl, 1, Z), dim3(256), 0, st, pr, p, k);
+      if (nbl * count <= 256)
+        hipLaunchKernelGGL((ht_finish<R, true>), dim3((unsigned)nbl, 1, Z), dim3(512), 0, st, pr, p, k);
+      else
+        hipLaunchKernelGGL((ht_finish<R, false>), dim3((unsigned)nbl, 1, Z), dim3(256), 0, st, pr, p, k);
       MMF_LAUNCH_CHECK();
     }
     const unsigned t = cdiv(nmax - p - HT_NB, GT_M);

@@ -46,6 +46,24 @@ def test_batched_equals_single_calls(prec):
         assert torch.equal(Pts[k], P1), f"eigenvectors differ from the single call, n={n}"
 
 
+def test_batched_equals_single_across_kernel_forms():
+    """Orders whose single reductions take other kernel forms than the batch:
+    strips of two tiles beside single tiles, narrow against wide workgroups
+    (more than 256 of them in the batch, fewer alone)."""
+    torch, mmf = require_gpu()
+    sizes = [2200, 450, 97, 130, 700, 321, 65, 1100]
+    log(f"batched eigh forms sizes={sizes}")
+    Hs = [_hermitian(n, 800 + k) for k, n in enumerate(sizes)]
+    mats = [to_dev_cm(torch, H) for H in Hs]
+    ws, Pts, info = mmf.eigh_batched(mats)
+    torch.cuda.synchronize()
+    assert info.cpu().tolist() == [0] * len(sizes)
+    for k, H in enumerate(Hs):
+        w1, P1, _ = mmf.eigh(to_dev_cm(torch, H))
+        torch.cuda.synchronize()
+        assert torch.equal(ws[k], w1) and torch.equal(Pts[k], P1), f"n={sizes[k]}"
+
+
 def test_batched_against_oracle():
     torch, mmf = require_gpu()
     Hs = [_hermitian(n, 900 + k) for k, n in enumerate(SIZES) if n]
