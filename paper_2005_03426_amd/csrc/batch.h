@@ -32,6 +32,15 @@ struct BEnt {
   int32_t *flags;      // degenerate-pair counts [G]
 };
 
+// What a call knows of a problem, packed for the kernel arguments (32 entries a
+// launch, where whole BEnt entries went 14 at a time); the table kernels derive
+// the rest (radix, S, M, s0 and the workspace carving).
+struct BPack {
+  double omega[BMAX_F];
+  int32_t N[BMAX_F];
+  int32_t D, F;
+};
+
 int assemble_batched_launch(const BEnt *tab, int64_t count, int64_t Mmax, hipStream_t st);
 
 }  // namespace mmf

@@ -22,8 +22,7 @@
 namespace mmf {
 
 constexpr int OB_THREADS = 256;
-constexpr int OB_SUB = 32;            // columns staged per step of the contraction
-constexpr int OB_PROJ_GRID = 1024;    // workgroups per problem row of the projection (they loop over columns)
+constexpr int OB_PROJ_GRID = 1024;    // most workgroups per problem row of the projection (they loop over columns)
 constexpr int AP_GROUPS = 64;         // averaged-probability partials per problem
 constexpr double OB_CLUSTER_REL = 1e-8;
 constexpr double OB_SHARED_WEIGHT = 1e-20;
@@ -46,28 +45,50 @@ __global__ void __launch_bounds__(OB_THREADS) ob_phases(const BEnt *__restrict__
   b.B[e] = cmake(cs, sn);
 }
 
-// Column a of problem blockIdx.y: thread e = i + D q sums over the sites.
+// Columns a of problem blockIdx.y.  With D T <= 128 a workgroup takes
+// 256 / (D T) columns at a time (thread e = i + D q of a column), otherwise one
+// column with up to eight outputs per thread; the columns' rows are staged in
+// LDS in chunks of whole sites.  For 512 problems of order 34 (T = 32) a grid
+// of 1024 workgroups per problem, one column and 64 busy threads each, took
+// 289 us, mostly empty workgroups; now 34.
+__host__ __device__ inline int ob_project_cols(int D, int T) { return D * T <= OB_THREADS / 2 ? OB_THREADS / (D * T) : 1; }
+
+// KMAX: most outputs per thread over the batch (1 or 8).
+template <int KMAX>
 __global__ void __launch_bounds__(OB_THREADS) ob_project(const BEnt *__restrict__ tab) {
   __shared__ cd col[2048];
   const BEnt &b = tab[blockIdx.y];
-  const int D = b.D, T = b.T;
+  const int D = b.D, T = b.T, DT = D * T;
   const int tid = threadIdx.x;
-  for (int64_t a = blockIdx.x; a < b.M; a += gridDim.x) {
-    const cd *Pa = b.HF + a * b.ld;
+  const int CB = ob_project_cols(D, T);
+  const int lim = 2048 / CB, chunk = lim / D * D;     // rows of a column staged at a time
+  const int cb = CB > 1 ? tid / DT : 0;
+  for (int64_t a0 = (int64_t)blockIdx.x * CB; a0 < b.M; a0 += (int64_t)gridDim.x * CB) {
+    const int nc = (int)(b.M - a0 < CB ? b.M - a0 : CB);
     double sn, cs;
-    cd acc[8];
-    for (int k = 0; k < 8; ++k) acc[k] = cmake(0.0, 0.0);
-    // the column in chunks of whole sites (at most 2048 rows) staged in LDS
-    const int64_t chunk = (int64_t)(2048 / D) * D;
+    cd acc[KMAX];
+    for (int k = 0; k < KMAX; ++k) acc[k] = cmake(0.0, 0.0);
     for (int64_t r0 = 0; r0 < b.M; r0 += chunk) {
       const int nr = (int)((b.M - r0 < chunk) ? b.M - r0 : chunk);
       __syncthreads();
-      for (int r = tid; r < nr; r += OB_THREADS) col[r] = Pa[r0 + r];
+      for (int c = 0; c < nc; ++c)
+        for (int r = tid; r < nr; r += OB_THREADS) col[c * lim + r] = b.HF[(a0 + c) * b.ld + r0 + r];
       __syncthreads();
       const int64_t s_lo = r0 / D, s_hi = (r0 + nr) / D;      // r0 and nr are multiples of D (so is M)
-      for (int k = 0; k < 8; ++k) {
+      if (CB > 1) {
+        const int e = tid - cb * DT, i = e % D, q = e / D;
+        if (cb < nc) {
+          cd s = acc[0];
+          const cd *cc = col + cb * lim + i - r0;
+#pragma unroll 4
+          for (int64_t site = s_lo; site < s_hi; ++site) s = cadd(s, cmul(b.B[site * T + q], cc[D * site]));
+          acc[0] = s;
+        }
+        continue;
+      }
+      for (int k = 0; k < KMAX; ++k) {
         const int e = tid + OB_THREADS * k;
-        if (e >= D * T) break;
+        if (e >= DT) break;
         const int i = e % D, q = e / D;
         cd s = acc[k];
         for (int64_t site = s_lo; site < s_hi; ++site)
@@ -75,47 +96,91 @@ __global__ void __launch_bounds__(OB_THREADS) ob_project(const BEnt *__restrict_
         acc[k] = s;
       }
     }
-    for (int k = 0; k < 8; ++k) {
+    if (CB > 1) {
+      const int e = tid - cb * DT, i = e % D, q = e / D;
+      if (cb < nc) {
+        const int64_t a = a0 + cb;
+        sincos(-(b.w[a] * (b.t[q] - b.t0)), &sn, &cs);
+        b.Y[((int64_t)q * b.M + a) * D + i] = cmul(acc[0], cmake(cs, sn));
+      }
+      continue;
+    }
+    for (int k = 0; k < KMAX; ++k) {
       const int e = tid + OB_THREADS * k;
-      if (e >= D * T) break;
+      if (e >= DT) break;
       const int i = e % D, q = e / D;
-      sincos(-(b.w[a] * (b.t[q] - b.t0)), &sn, &cs);
-      b.Y[((int64_t)q * b.M + a) * D + i] = cmul(acc[k], cmake(cs, sn));
+      sincos(-(b.w[a0] * (b.t[q] - b.t0)), &sn, &cs);
+      b.Y[((int64_t)q * b.M + a0) * D + i] = cmul(acc[k], cmake(cs, sn));
     }
   }
 }
 
-// U[q] of problem blockIdx.y (time q = blockIdx.x).
+// U of problem blockIdx.y.  With D^2 <= 64 a workgroup takes 64 / D^2 times,
+// each with four groups of D^2 threads that share the columns (summed in group
+// order); otherwise one time, up to 16 elements per thread.  The zero-site rows
+// are staged in LDS.  512 problems of order 34 at 32 times: one time and four
+// busy threads per workgroup took 133 us, this form 7.
+constexpr int OB_PARTS = 4;
+__host__ __device__ inline int ob_contract_times(int D) { return D * D <= 64 ? OB_THREADS / (OB_PARTS * D * D) : 1; }
+
+// KMAX: most elements of U per thread over the batch (1 or 16).
+template <int KMAX>
 __global__ void __launch_bounds__(OB_THREADS) ob_contract(const BEnt *__restrict__ tab) {
-  __shared__ cd ys[OB_SUB * MAX_D];
-  __shared__ cd ps[OB_SUB * MAX_D];
+  __shared__ cd ps[2048];
+  __shared__ cd red[OB_THREADS];
   const BEnt &b = tab[blockIdx.y];
-  const int q = blockIdx.x;
-  if (q >= b.T) return;
   const int D = b.D, DD = D * D;
+  const int QB = ob_contract_times(D);
+  const int q0 = blockIdx.x * QB;
+  if (q0 >= b.T) return;
   const int tid = threadIdx.x;
-  cd acc[16];
-  for (int k = 0; k < 16; ++k) acc[k] = cmake(0.0, 0.0);
-  for (int64_t ab = 0; ab < b.M; ab += OB_SUB) {
-    const int na = (int)((b.M - ab < OB_SUB) ? b.M - ab : OB_SUB);
+  const int sub = 2048 / D;
+  const bool small = DD <= 64;
+  const int ql = small ? tid / (OB_PARTS * DD) : 0, rest = small ? tid - ql * OB_PARTS * DD : tid;
+  const int g = small ? rest / DD : 0;
+  const int q = q0 + ql;
+  cd acc[KMAX];
+  for (int k = 0; k < KMAX; ++k) acc[k] = cmake(0.0, 0.0);
+  for (int64_t ab = 0; ab < b.M; ab += sub) {
+    const int na = (int)((b.M - ab < sub) ? b.M - ab : sub);
     __syncthreads();
     for (int e = tid; e < na * D; e += OB_THREADS) {
-      const int aa = e / D, i = e % D;
-      const int64_t a = ab + aa;
-      ys[e] = b.Y[((int64_t)q * b.M + a) * D + i];
-      ps[e] = cconj(b.HF[i + (int64_t)D * b.s0 + a * b.ld]);
+      const int aa = e / D, i = e - aa * D;
+      ps[e] = cconj(b.HF[i + (int64_t)D * b.s0 + (ab + aa) * b.ld]);
     }
     __syncthreads();
-    for (int k = 0; k < 16; ++k) {
+    if (small) {
+      if (ql < QB && q < b.T) {
+        const int e = rest - g * DD, i = e % D, j = e / D;
+        const cd *y = b.Y + ((int64_t)q * b.M + ab) * D + i;
+        cd s = acc[0];
+#pragma unroll 4
+        for (int aa = g; aa < na; aa += OB_PARTS) s = cadd(s, cmul(y[(int64_t)aa * D], ps[aa * D + j]));
+        acc[0] = s;
+      }
+      continue;
+    }
+    for (int k = 0; k < KMAX; ++k) {
       const int e = tid + OB_THREADS * k;
       if (e >= DD) break;
       const int i = e % D, j = e / D;
+      const cd *y = b.Y + ((int64_t)q * b.M + ab) * D + i;
       cd s = acc[k];
-      for (int aa = 0; aa < na; ++aa) s = cadd(s, cmul(ys[aa * D + i], ps[aa * D + j]));
+      for (int aa = 0; aa < na; ++aa) s = cadd(s, cmul(y[(int64_t)aa * D], ps[aa * D + j]));
       acc[k] = s;
     }
   }
-  for (int k = 0; k < 16; ++k) {
+  if (small) {
+    red[tid] = acc[0];
+    __syncthreads();
+    if (ql < QB && q < b.T && g == 0) {
+      cd s = red[tid];
+      for (int gg = 1; gg < OB_PARTS; ++gg) s = cadd(s, red[tid + gg * DD]);
+      b.U[(int64_t)q * DD + rest] = s;
+    }
+    return;
+  }
+  for (int k = 0; k < KMAX; ++k) {
     const int e = tid + OB_THREADS * k;
     if (e >= DD) break;
     b.U[(int64_t)q * DD + e] = acc[k];
@@ -133,7 +198,7 @@ __global__ void __launch_bounds__(OB_THREADS) ob_avgprob(const BEnt *__restrict_
   if (g >= G) return;
   const int D = b.D, DD = D * D, tid = threadIdx.x;
   int P2 = 1;
-  while (D * P2 * 2 <= OB_THREADS) P2 *= 2;
+  while (D * P2 * 2 <= OB_THREADS && D * P2 < b.M) P2 *= 2;
   const int Tp = D * P2;
   const double delta = OB_CLUSTER_REL * fmax(1.0, fmax(fabs(b.w[0]), fabs(b.w[b.M - 1])));
   int32_t nflag = 0;
@@ -223,13 +288,84 @@ static int batch_params(int64_t count, const mmf_problem *p, std::vector<FloqPar
   return MMF_OK;
 }
 
-static BEnt make_ent(const FloqParams &fp) {
-  BEnt e = {};
-  e.D = fp.D; e.F = fp.F; e.K = fp.K;
-  e.M = fp.M; e.S = fp.S; e.s0 = fp.s0;
-  for (int l = 0; l < BMAX_F; ++l) { e.N[l] = fp.N[l]; e.radix[l] = fp.radix[l]; e.omega[l] = fp.omega[l]; }
-  for (int k = 0; k < BMAX_K; ++k) { e.axis[k] = fp.axis[k]; e.harm[k] = fp.harm[k]; }
+static BPack make_pack(const FloqParams &fp) {
+  BPack e = {};
+  e.D = fp.D; e.F = fp.F;
+  for (int l = 0; l < BMAX_F; ++l) { e.N[l] = fp.N[l]; e.omega[l] = fp.omega[l]; }
   return e;
+}
+
+// The problem part of a table entry.
+__device__ inline void unpack(const BPack &q, BEnt &e) {
+  e.D = q.D; e.F = q.F;
+  e.S = 1; e.s0 = 0;
+  for (int l = 0; l < BMAX_F; ++l) {
+    const bool in = l < q.F;
+    e.N[l] = in ? q.N[l] : 0;
+    e.omega[l] = in ? q.omega[l] : 0.0;
+    e.radix[l] = 2 * e.N[l] + 1;
+    e.s0 += e.N[l] * e.S;
+    e.S *= e.radix[l];
+  }
+  e.M = q.D * e.S;
+}
+
+// Entries for the assembly.
+struct BuildPack {
+  BPack q;
+  const cd *EV;
+  cd *HF;
+  int64_t ld;
+  int32_t harm[BMAX_K];
+  int8_t axis[BMAX_K];
+  int32_t K;
+};
+__global__ void ob_set_build(BEnt *dst, TableChunk<BuildPack, 3840 / sizeof(BuildPack)> c) {
+  const int i = threadIdx.x;
+  if (i >= c.count) return;
+  const BuildPack &v = c.v[i];
+  BEnt e = {};
+  unpack(v.q, e);
+  e.K = v.K;
+  for (int k = 0; k < BMAX_K; ++k) { e.axis[k] = v.axis[k]; e.harm[k] = v.harm[k]; }
+  e.EV = v.EV; e.HF = v.HF; e.ld = v.ld;
+  dst[i] = e;
+}
+
+// Entries for the observables; `base` is the problem's part of the workspace,
+// carved as in ob_prob_bytes.
+struct ObsPack {
+  BPack q;
+  cd *HF;
+  int64_t ld;
+  const double *w, *t;
+  cd *U;
+  double *P;
+  char *base;
+};
+__global__ void ob_set_obs(BEnt *dst, int32_t *status, int32_t T, double t0,
+                           TableChunk<ObsPack, 3840 / sizeof(ObsPack)> c) {
+  const int i = threadIdx.x;
+  if (i >= c.count) return;
+  const ObsPack &v = c.v[i];
+  BEnt e = {};
+  unpack(v.q, e);
+  e.T = T; e.t0 = t0;
+  e.HF = v.HF; e.ld = v.ld; e.w = v.w; e.t = v.t; e.U = v.U; e.P = v.P;
+  e.status = status + i;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    off = (off + 255) & ~(size_t)255;
+    char *r = v.base + off;
+    off += bytes;
+    return r;
+  };
+  const int64_t G = e.M < AP_GROUPS ? e.M : AP_GROUPS;
+  e.B = reinterpret_cast<cd *>(take((size_t)e.S * T * sizeof(cd)));
+  e.Y = reinterpret_cast<cd *>(take((size_t)T * e.M * e.D * sizeof(cd)));
+  e.part = reinterpret_cast<double *>(take((size_t)G * e.D * e.D * sizeof(double)));
+  e.flags = reinterpret_cast<int32_t *>(take((size_t)G * sizeof(int32_t)));
+  dst[i] = e;
 }
 
 }  // namespace mmf
@@ -271,19 +407,27 @@ extern "C" int mmf_build_floquet_batched(int64_t count, const mmf_problem *p, co
   }
   if (!work) return -6;
   if (work_bytes < (size_t)count * sizeof(BEnt)) return -7;
-  std::vector<BEnt> h((size_t)count);
-  int64_t Mmax = 0;
-  for (int64_t c = 0; c < count; ++c) {
-    h[c] = make_ent(fps[c]);
-    h[c].EV = reinterpret_cast<const cd *>(EV[c]);
-    h[c].HF = reinterpret_cast<cd *>(HF[c]);
-    h[c].ld = ldh[c];
-    Mmax = fps[c].M > Mmax ? fps[c].M : Mmax;
-  }
   hipStream_t st = (hipStream_t)stream;
   BEnt *tab = reinterpret_cast<BEnt *>(work);
-  rc = table_write<BEnt, 3840>(tab, h.data(), count, st);
-  if (rc) return rc;
+  int64_t Mmax = 0;
+  TableChunk<BuildPack, 3840 / sizeof(BuildPack)> ch;
+  constexpr int64_t CH = 3840 / sizeof(BuildPack);
+  for (int64_t c0 = 0; c0 < count; c0 += CH) {
+    ch.count = (int32_t)(count - c0 < CH ? count - c0 : CH);
+    for (int32_t i = 0; i < ch.count; ++i) {
+      const FloqParams &fp = fps[c0 + i];
+      BuildPack &v = ch.v[i];
+      v.q = make_pack(fp);
+      v.EV = reinterpret_cast<const cd *>(EV[c0 + i]);
+      v.HF = reinterpret_cast<cd *>(HF[c0 + i]);
+      v.ld = ldh[c0 + i];
+      v.K = fp.K;
+      for (int k = 0; k < BMAX_K; ++k) { v.axis[k] = (int8_t)fp.axis[k]; v.harm[k] = fp.harm[k]; }
+      Mmax = fp.M > Mmax ? fp.M : Mmax;
+    }
+    hipLaunchKernelGGL(ob_set_build, dim3(1), dim3(64), 0, st, tab + c0, ch);
+    MMF_LAUNCH_CHECK();
+  }
   return assemble_batched_launch(tab, count, Mmax, st);
 }
 
@@ -318,44 +462,53 @@ extern "C" int mmf_observables_batched(int64_t count, const mmf_problem *p, cons
   size_t need = 0;
   mmf_batched_workspace(count, p, T, &need);
   if (work_bytes < need) return -13;
-  std::vector<BEnt> h((size_t)count);
   char *cur = (char *)work + (((size_t)count * sizeof(BEnt) + 255) & ~(size_t)255);
-  int64_t Smax_T = 0;
-  for (int64_t c = 0; c < count; ++c) {
-    const FloqParams &fp = fps[c];
-    BEnt &e = h[c];
-    e = make_ent(fp);
-    e.T = T;
-    e.HF = const_cast<cd *>(reinterpret_cast<const cd *>(Phi[c]));
-    e.ld = ld[c];
-    e.w = w[c];
-    e.t = t[c];
-    e.t0 = t0;
-    e.U = reinterpret_cast<cd *>(U[c]);
-    e.P = P[c];
-    e.status = dev_status + c;
-    Carver cv(cur);
-    e.B = cv.take<cd>((size_t)fp.S * T);
-    e.Y = cv.take<cd>((size_t)T * fp.M * fp.D);
-    const int64_t G = fp.M < AP_GROUPS ? fp.M : AP_GROUPS;
-    e.part = cv.take<double>((size_t)G * fp.D * fp.D);
-    e.flags = cv.take<int32_t>((size_t)G);
-    cur += cv.used();
-    Smax_T = fp.S * T > Smax_T ? fp.S * T : Smax_T;
-  }
+  int64_t Smax_T = 0, Mmax = 0, proj = 0, qb = 1;   // largest grids of the batch
+  int32_t Dmax = 0;
   hipStream_t st = (hipStream_t)stream;
   BEnt *tab = reinterpret_cast<BEnt *>(work);
-  rc = table_write<BEnt, 3840>(tab, h.data(), count, st);
-  if (rc) return rc;
+  TableChunk<ObsPack, 3840 / sizeof(ObsPack)> ch;
+  constexpr int64_t CH = 3840 / sizeof(ObsPack);
+  for (int64_t c0 = 0; c0 < count; c0 += CH) {
+    ch.count = (int32_t)(count - c0 < CH ? count - c0 : CH);
+    for (int32_t i = 0; i < ch.count; ++i) {
+      const int64_t c = c0 + i;
+      const FloqParams &fp = fps[c];
+      ObsPack &v = ch.v[i];
+      v.q = make_pack(fp);
+      v.HF = const_cast<cd *>(reinterpret_cast<const cd *>(Phi[c]));
+      v.ld = ld[c];
+      v.w = w[c];
+      v.t = t[c];
+      v.U = reinterpret_cast<cd *>(U[c]);
+      v.P = P[c];
+      v.base = cur;
+      cur += ob_prob_bytes(fp, T);
+      Smax_T = fp.S * T > Smax_T ? fp.S * T : Smax_T;
+      Mmax = fp.M > Mmax ? fp.M : Mmax;
+      Dmax = fp.D > Dmax ? fp.D : Dmax;
+      proj = std::max(proj, (int64_t)cdiv(fp.M, ob_project_cols(fp.D, T)));
+      qb = std::max(qb, (int64_t)cdiv(T, ob_contract_times(fp.D)));
+    }
+    hipLaunchKernelGGL(ob_set_obs, dim3(1), dim3(64), 0, st, tab + c0, dev_status + c0, T, t0, ch);
+    MMF_LAUNCH_CHECK();
+  }
   for (int64_t y0 = 0; y0 < count; y0 += 65535) {
     const unsigned yc = (unsigned)(count - y0 < 65535 ? count - y0 : 65535);
     hipLaunchKernelGGL(ob_phases, dim3(cdiv(Smax_T, OB_THREADS), yc), dim3(OB_THREADS), 0, st, tab + y0);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(ob_project, dim3(OB_PROJ_GRID, yc), dim3(OB_THREADS), 0, st, tab + y0);
+    const dim3 pg((unsigned)std::min<int64_t>(proj, OB_PROJ_GRID), yc), cg((unsigned)qb, yc);
+    if ((int64_t)Dmax * T <= OB_THREADS)
+      hipLaunchKernelGGL(ob_project<1>, pg, dim3(OB_THREADS), 0, st, tab + y0);
+    else
+      hipLaunchKernelGGL(ob_project<8>, pg, dim3(OB_THREADS), 0, st, tab + y0);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(ob_contract, dim3((unsigned)T, yc), dim3(OB_THREADS), 0, st, tab + y0);
+    if (Dmax <= 16)
+      hipLaunchKernelGGL(ob_contract<1>, cg, dim3(OB_THREADS), 0, st, tab + y0);
+    else
+      hipLaunchKernelGGL(ob_contract<16>, cg, dim3(OB_THREADS), 0, st, tab + y0);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(ob_avgprob, dim3(AP_GROUPS, yc), dim3(OB_THREADS), 0, st, tab + y0);
+    hipLaunchKernelGGL(ob_avgprob, dim3((unsigned)std::min<int64_t>(Mmax, AP_GROUPS), yc), dim3(OB_THREADS), 0, st, tab + y0);
     MMF_LAUNCH_CHECK();
     hipLaunchKernelGGL(ob_avgprob_sum, dim3(yc), dim3(OB_THREADS), 0, st, tab + y0);
     MMF_LAUNCH_CHECK();

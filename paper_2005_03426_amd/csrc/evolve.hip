@@ -19,8 +19,11 @@
 
 namespace mmf {
 
-constexpr int EV_CHUNK = 2048;   // eigenvector columns per contraction workgroup
-constexpr int EV_SUB = 32;       // columns staged in LDS at a time
+constexpr int EV_LDS = 2048;     // entries of C and of the zero-site rows staged at a time
+
+// Eigenvector columns per contraction workgroup: enough workgroups to fill the
+// chip at small orders, few partials at large ones.
+inline int64_t ev_chunk(int64_t M) { return M <= 2048 ? 256 : (M <= 8192 ? 512 : 2048); }
 
 __global__ void site_phase_kernel(FloqParams fp, int32_t T, const double *__restrict__ t,
                                   mmf_z *__restrict__ B) {
@@ -41,52 +44,81 @@ __global__ void site_phase_kernel(FloqParams fp, int32_t T, const double *__rest
   stz(B + e, cmake(cs, -sn));    // Bc[q + s*T] = conj(e^{i theta t})
 }
 
-// U partial for one time index and one chunk of eigenvector columns.
+// U partial for one time index and one chunk of eigenvector columns.  The
+// products C e^{-i eps (t - t0)} and the zero-site rows of up to 256 columns are
+// staged in LDS; with D^2 <= 128 the columns are split over 256 / D^2 groups of
+// threads (element = thread within its group), summed in group order.  Bound
+// by the read of C (8 D M T words once); one group of D^2 threads and 32
+// columns per stage took 589 us at D = 8, M = 5000, T = 256, this form 87.
+// KMAX: elements of U per thread (1 up to D = 16, else 16).
+template <int KMAX>
 __global__ void __launch_bounds__(256)
-evolve_contract(int D, int64_t M, int64_t s0, int32_t T, const mmf_z *__restrict__ C,
+evolve_contract(int D, int64_t M, int64_t s0, int32_t T, int64_t chunk, const mmf_z *__restrict__ C,
                 const mmf_z *__restrict__ Phi, int64_t ld, const double *__restrict__ w,
                 double t0, const double *__restrict__ t, mmf_z *__restrict__ part) {
-  __shared__ cd cs[EV_SUB * MAX_D];
-  __shared__ cd ps[EV_SUB * MAX_D];
-  __shared__ cd ph[EV_SUB];
+  __shared__ cd cs[EV_LDS];
+  __shared__ cd ps[EV_LDS];
+  __shared__ cd ph[256];
   const int q = blockIdx.x;                  // time index
-  const int64_t a0 = (int64_t)blockIdx.y * EV_CHUNK;
-  const int64_t a1 = (a0 + EV_CHUNK < M) ? a0 + EV_CHUNK : M;
+  const int64_t a0 = (int64_t)blockIdx.y * chunk;
+  const int64_t a1 = (a0 + chunk < M) ? a0 + chunk : M;
   const int tid = threadIdx.x;
   const int DD = D * D;
+  const int G = DD <= 128 ? 256 / DD : 1;    // column groups
+  const int g = G > 1 ? tid / DD : 0;
+  const int sub = EV_LDS / D < 256 ? EV_LDS / D : 256;
   const double tau = t[q] - t0;
-  cd acc[16];
+  const mmf_z *Cq = C + (int64_t)q * D * M;
+  cd acc[KMAX];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) acc[k] = cmake(0.0, 0.0);
-  for (int64_t ab = a0; ab < a1; ab += EV_SUB) {
-    const int na = (int)((a1 - ab < EV_SUB) ? a1 - ab : EV_SUB);
-    for (int e = tid; e < na * D; e += 256) {
-      const int aa = e / D, i = e % D;
-      const int64_t a = ab + aa;
-      cs[e] = ldz(C + (i + (int64_t)D * a) + (int64_t)q * D * M);
-      ps[e] = cconj(ldz(Phi + i + (int64_t)D * s0 + a * ld));
-    }
+  for (int k = 0; k < KMAX; ++k) acc[k] = cmake(0.0, 0.0);
+  for (int64_t ab = a0; ab < a1; ab += sub) {
+    const int na = (int)((a1 - ab < sub) ? a1 - ab : sub);
+    __syncthreads();
     if (tid < na) {
       double sn, c;
       sincos(-(w[ab + tid] * tau), &sn, &c);
       ph[tid] = cmake(c, sn);
     }
     __syncthreads();
-    for (int k = 0; k < 16; ++k) {
-      const int e = tid + 256 * k;
-      if (e >= DD) break;
-      const int i = e % D, j = e / D;
-      cd s = acc[k];
-      for (int aa = 0; aa < na; ++aa) {
-        const cd x = cmul(cmul(cs[aa * D + i], ph[aa]), ps[aa * D + j]);
-        s = cadd(s, x);
-      }
-      acc[k] = s;
+    for (int e = tid; e < na * D; e += 256) {
+      const int aa = e / D, i = e - aa * D;
+      cs[e] = cmul(ldz(Cq + (int64_t)D * ab + e), ph[aa]);
+      ps[e] = cconj(ldz(Phi + i + (int64_t)D * s0 + (ab + aa) * ld));
     }
     __syncthreads();
+    if (G > 1) {
+      const int e = tid - g * DD, i = e % D, j = e / D;
+      if (g < G) {
+        cd s = acc[0];
+#pragma unroll 4
+        for (int aa = g; aa < na; aa += G) s = cadd(s, cmul(cs[aa * D + i], ps[aa * D + j]));
+        acc[0] = s;
+      }
+    } else {
+      for (int k = 0; k < KMAX; ++k) {
+        const int e = tid + 256 * k;
+        if (e >= DD) break;
+        const int i = e % D, j = e / D;
+        cd s = acc[k];
+        for (int aa = 0; aa < na; ++aa) s = cadd(s, cmul(cs[aa * D + i], ps[aa * D + j]));
+        acc[k] = s;
+      }
+    }
   }
   mmf_z *out = part + ((int64_t)blockIdx.y * T + q) * DD;
-  for (int k = 0; k < 16; ++k) {
+  if (G > 1) {
+    __syncthreads();
+    cs[tid] = acc[0];
+    __syncthreads();
+    if (tid < DD) {
+      cd s = cs[tid];
+      for (int gg = 1; gg < G; ++gg) s = cadd(s, cs[gg * DD + tid]);
+      stz(out + tid, s);
+    }
+    return;
+  }
+  for (int k = 0; k < KMAX; ++k) {
     const int e = tid + 256 * k;
     if (e >= DD) break;
     stz(out + e, acc[k]);
@@ -112,7 +144,7 @@ inline EvolveWs evolve_ws(const FloqParams &fp, int32_t T, void *base) {
   EvolveWs ws;
   ws.B = cv.take<mmf_z>((size_t)T * fp.S);
   ws.C = cv.take<mmf_z>((size_t)T * fp.D * fp.M);
-  const int G = (int)cdiv(fp.M, EV_CHUNK);
+  const int G = (int)cdiv(fp.M, ev_chunk(fp.M));
   ws.part = cv.take<mmf_z>((size_t)G * T * fp.D * fp.D);
   ws.bytes = cv.used();
   return ws;
@@ -157,9 +189,13 @@ extern "C" int mmf_evolve(const mmf_problem *p, const mmf_z *Phi, int64_t ld, co
   g.grp = fp.D;
   int r = gemm_launch<true, A_G, B_C>(g, st);
   if (r) return r;
-  const int G = (int)cdiv(fp.M, EV_CHUNK);
-  hipLaunchKernelGGL(evolve_contract, dim3(T, G), dim3(256), 0, st, fp.D, fp.M, fp.s0, T, ws.C,
-                     Phi, ld, w, t0, t, ws.part);
+  const int G = (int)cdiv(fp.M, ev_chunk(fp.M));
+  if (fp.D <= 16)
+    hipLaunchKernelGGL(evolve_contract<1>, dim3(T, G), dim3(256), 0, st, fp.D, fp.M, fp.s0, T, ev_chunk(fp.M), ws.C,
+                       Phi, ld, w, t0, t, ws.part);
+  else
+    hipLaunchKernelGGL(evolve_contract<16>, dim3(T, G), dim3(256), 0, st, fp.D, fp.M, fp.s0, T, ev_chunk(fp.M), ws.C,
+                       Phi, ld, w, t0, t, ws.part);
   MMF_LAUNCH_CHECK();
   const int DD = fp.D * fp.D;
   hipLaunchKernelGGL(evolve_reduce, dim3(cdiv((int64_t)T * DD, 256)), dim3(256), 0, st, DD, T, G,

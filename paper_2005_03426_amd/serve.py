@@ -47,7 +47,8 @@ def footprint_bytes(M: int, D: int, T: int, prec: int = MMF_C128, band: int | No
     for a mixed-precision request also what its complex128 retry needs; with
     `band`, the band-aware eigensolver's workspace)."""
     S = M // D
-    ev = T * S * 16 + T * D * M * 16 + ((M + 2047) // 2048) * T * D * D * 16
+    chunk = 256 if M <= 2048 else 512 if M <= 8192 else 2048       # columns per partial of U(t)
+    ev = T * S * 16 + T * D * M * 16 + ((M + chunk - 1) // chunk) * T * D * D * 16
     ws = eigh_band_workspace_bytes(M, band) if band is not None else eigh_workspace_bytes(M, prec)
     if prec != MMF_C128:
         ws = max(ws, eigh_workspace_bytes(M, MMF_C128))
