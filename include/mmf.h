@@ -248,8 +248,8 @@ int mmf_eigh_batched(int64_t count, const int64_t *n, mmf_z *const *A, const int
  * eigenvectors in LDS (parallel cyclic Jacobi), or 0 to send the bucket to
  * the grouped Householder / divide-and-conquer path.  Written by the
  * project's autotuner from measurements (paper_2005_03426_amd/autotune.py);
- * without one the library uses 64 threads up to order 16, 128 up to 32 and
- * 256 up to 64 (the same rule mmf_eigh applies to a single matrix of order
+ * without one the library uses 64 threads up to order 16, 256 up to 32 and
+ * 512 up to 64 (the same rule mmf_eigh applies to a single matrix of order
  * <= 64). */
 typedef struct {
   int32_t small_threads[8];

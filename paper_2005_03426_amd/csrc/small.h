@@ -15,8 +15,11 @@ struct SmallProb {
 };
 
 // Workgroup size the library uses for an order n (1 <= n <= SMALL_NMAX) when
-// the caller gives no tuning table: 64 up to 16, 128 up to 32, 256 above.
-inline int32_t small_default_threads(int64_t n) { return n <= 16 ? 64 : (n <= 32 ? 128 : 256); }
+// the caller gives no tuning table: 64 up to 16, 256 up to 32, 512 above.
+// One matrix, 64 / 128 / 256 / 512 threads: order 16 112 / 102 / 107 / 108 us,
+// 32 555 / 356 / 259 / 247, 34 812 / 468 / 359 / 290, 64 4179 / 2351 / 1405 /
+// 1083; 512 matrices of order 34 1350 / 1010 / 865 / 791 us.
+inline int32_t small_default_threads(int64_t n) { return n <= 16 ? 64 : (n <= 32 ? 256 : 512); }
 
 // Device bytes of the table region eigh_small_batched needs for `count` problems.
 size_t small_table_bytes(int64_t count);
