@@ -147,12 +147,12 @@ inline Eigh2Ws eigh2_ws(int64_t M, int64_t nc, bool window, void *base) {
 // Band reduction, bulge chase and divide and conquer: eigenvalues in w,
 // tridiagonal eigenvectors in ws.Z, stage-1 reflectors in A.
 inline int eigh2_tridiag(int64_t M, mmf_z *A, int64_t lda, double *w, const Eigh2Ws &ws, int32_t *dev_info,
-                         hipStream_t st, const EighLimits &lim = EighLimits()) {
+                         hipStream_t st, const EighLimits &lim = EighLimits(), const double *win = nullptr) {
   int rc = he2hb_run(M, A, lda, ws.tau1, ws.AB, ws.rest, ws.rest_bytes, st);
   if (rc) return rc;
   rc = hb2st_run(M, ws.AB, ws.V2, ws.tau2, w, ws.e, ws.table, st);
   if (rc) return rc;
-  return stedc_run(M, w, ws.e, ws.Z, M, ws.rest, ws.rest_bytes, dev_info, st, lim);
+  return stedc_run(M, w, ws.e, ws.Z, M, ws.rest, ws.rest_bytes, dev_info, st, lim, win);
 }
 
 size_t eigh2_full_ws_bytes(int64_t M) { return eigh2_ws(M, M, false, nullptr).bytes; }
@@ -338,7 +338,8 @@ extern "C" int mmf_eigh_band_window(int64_t M, const mmf_z *A, int64_t lda, int6
   if (rc) return rc;
   rc = hb2st_run(M, ws.AB, ws.V2, ws.tau2, ws.wall, ws.e, ws.table, st);
   if (rc) return rc;
-  rc = stedc_run(M, ws.wall, ws.e, ws.Z, M, ws.rest, ws.rest_bytes, dev_info, st);
+  const double win[2] = {vl, vu};
+  rc = stedc_run(M, ws.wall, ws.e, ws.Z, M, ws.rest, ws.rest_bytes, dev_info, st, EighLimits(), win);
   if (rc) return rc;
   hipLaunchKernelGGL(eigh_window_gather, dim3(kk > 0 ? cdiv(M, 256) : 1, kk > 0 ? (unsigned)kk : 1),
                      dim3(kk > 0 ? 256 : 1), 0, st, M, ws.wall, ws.Z, vl, vu, kk, w, ws.Zk, count);
@@ -529,7 +530,8 @@ extern "C" int mmf_eigh_window(int64_t M, mmf_z *A, int64_t lda, double vl, doub
   if (M == 0) return MMF_OK;
   if (two) {
     const Eigh2Ws ws = eigh2_ws(M, kk, true, work);
-    int rc = eigh2_tridiag(M, A, lda, ws.wall, ws, dev_info, st);
+    const double win[2] = {vl, vu};
+    int rc = eigh2_tridiag(M, A, lda, ws.wall, ws, dev_info, st, EighLimits(), win);
     if (rc) return rc;
     const int64_t g = kk > 0 ? kk : 0;
     hipLaunchKernelGGL(eigh_window_gather, dim3(g > 0 ? cdiv(M, 256) : 1, g > 0 ? (unsigned)g : 1),
@@ -544,7 +546,8 @@ extern "C" int mmf_eigh_window(int64_t M, mmf_z *A, int64_t lda, double vl, doub
   WinWs ws = win_ws(M, kk, work);
   int rc = hetrd_run(M, A, lda, ws.wall, ws.e.e, ws.e.tau, ws.e.rest, ws.e.rest_bytes, st);
   if (rc) return rc;
-  rc = stedc_run(M, ws.wall, ws.e.e, ws.e.Z, M, ws.e.rest, ws.e.rest_bytes, dev_info, st);
+  const double win[2] = {vl, vu};
+  rc = stedc_run(M, ws.wall, ws.e.e, ws.e.Z, M, ws.e.rest, ws.e.rest_bytes, dev_info, st, EighLimits(), win);
   if (rc) return rc;
   if (kk == 0) {
     hipLaunchKernelGGL(eigh_window_gather, dim3(1, 1), dim3(1), 0, st, M, ws.wall, ws.e.Z, vl, vu, (int64_t)0, w,

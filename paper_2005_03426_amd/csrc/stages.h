@@ -22,8 +22,11 @@ int hetrd_run(int64_t n, mmf_z *A, int64_t lda, double *d, double *e, mmf_z *tau
               size_t bytes, hipStream_t st);
 
 size_t stedc_ws_bytes(int64_t n);
+// win (optional): {vl, vu}; only the eigenvectors of eigenvalues in [vl, vu)
+// are formed in Z, its other columns are left undefined.
 int stedc_run(int64_t n, double *d, const double *e, double *Z, int64_t ldz, void *work,
-              size_t bytes, int32_t *info, hipStream_t st, const EighLimits &lim = EighLimits());
+              size_t bytes, int32_t *info, hipStream_t st, const EighLimits &lim = EighLimits(),
+              const double *win = nullptr);
 
 size_t unmtr_ws_bytes(int64_t n);
 // Phi may alias V (the reflectors are copied to the workspace first).

@@ -88,6 +88,8 @@ struct DcProb {
   int64_t n, ldz, L;
   int32_t h;
   int32_t sec_max, leaf_max;     // iteration caps: secular steps per root, QL steps per eigenvalue
+  int32_t window;                // eigenvectors wanted: all (0), or those of eigenvalues in [vl, vu)
+  double vl, vu;
   double *d;
   const double *e0;              // caller's off-diagonal; the kernels use e = w.es
   const double *e;
@@ -690,6 +692,14 @@ __global__ void __launch_bounds__(256) dc_lowner(const DcProb *pr, int lev) {
   }
 }
 
+// Whether root j of a merge needs its eigenvector: every root below the top
+// merge, there those of the wanted window (compared as the caller will see them).
+__device__ inline bool dc_wanted(const DcProb &P, int lev, int64_t s, int j) {
+  if (lev < P.h || !P.window) return true;
+  const double v = (P.w.dn[s + P.w.lamo[s + j]] + P.w.lamt[s + j]) * P.w.scl[1];
+  return v >= P.vl && v < P.vu;
+}
+
 // Column j of the rank-one eigenvector matrix U (T2 block, ld n).
 __global__ void __launch_bounds__(256) dc_vectors(const DcProb *pr, int lev) {
   __shared__ double sh[4];
@@ -703,7 +713,7 @@ __global__ void __launch_bounds__(256) dc_vectors(const DcProb *pr, int lev) {
   const MergeGeom q = dc_geom(n, P.L, lev, g);
   const int K = cnt[DC_CNT * g];
   const int j = blockIdx.x;
-  if (j >= K) return;
+  if (j >= K || !dc_wanted(P, lev, q.s, j)) return;
   const int64_t s = q.s;
   const double *d = dn + s;
   const double dorg = d[lamo[s + j]], tj = lamt[s + j];
@@ -778,6 +788,12 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) dc_gemm(const DcProb *pr, int
   const int K = cnt[DC_CNT * g], c1 = cnt[DC_CNT * g + 3], c12 = cnt[DC_CNT * g + 4];
   const int64_t m0 = (int64_t)blockIdx.x * GT_M, n0 = (int64_t)blockIdx.y * GT_N;
   if (m0 >= q.m || n0 >= K) return;
+  // no column of this tile wanted (a window: the top merge is three quarters of
+  // the products, 52 ms of 259 at order 12816, of which its 16 states need 16)
+  {
+    const int j = (int)n0 + (threadIdx.x & 63);
+    if (!__any(j < K && dc_wanted(P, lev, q.s, j))) return;      // the same in every wavefront
+  }
   // rows of the first child meet only kept columns [0, c12), rows of the
   // second only [c1, K); a row tile across the boundary takes all K
   int64_t k0 = 0, k1 = K;
@@ -906,8 +922,11 @@ int stedc_grouped(const DcProb *pr, const int64_t *nh, int64_t count, hipStream_
 }
 
 inline DcProb dc_prob(int64_t n, double *d, const double *e, double *Z, int64_t ldz, int32_t *info,
-                      const DcWs &w, const EighLimits &lim) {
+                      const DcWs &w, const EighLimits &lim, const double *win = nullptr) {
   DcProb q;
+  q.window = win != nullptr;
+  q.vl = win ? win[0] : 0.0;
+  q.vu = win ? win[1] : 0.0;
   q.n = n; q.ldz = ldz;
   q.sec_max = lim.secular_iters;
   q.leaf_max = lim.leaf_iters;
@@ -932,13 +951,13 @@ int stedc_batched(int64_t count, const int64_t *n, double *const *d, double *con
 }
 
 int stedc_run(int64_t n, double *d, const double *e, double *Z, int64_t ldz, void *work, size_t bytes,
-              int32_t *info, hipStream_t st, const EighLimits &lim) {
+              int32_t *info, hipStream_t st, const EighLimits &lim, const double *win) {
   if (n <= 0) return MMF_OK;
   static_assert(sizeof(DcProb) <= 512, "table entry");
   DcWs w = stedc_ws(n, (char *)work + 512);
   if (bytes < w.bytes + 512) return MMF_ERR_WORKSPACE;
   DcProb *pr = reinterpret_cast<DcProb *>(work);
-  const DcProb q = dc_prob(n, d, e, Z, ldz, info, w, lim);
+  const DcProb q = dc_prob(n, d, e, Z, ldz, info, w, lim, win);
   const int rc = table_write(pr, &q, 1, st);
   if (rc) return rc;
   return stedc_grouped(pr, &n, 1, st);
