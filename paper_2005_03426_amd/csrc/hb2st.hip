@@ -330,10 +330,26 @@ constexpr int BT2_THREADS = 512;          // eight wavefronts per workgroup, one
 constexpr int BT2_TILE = 128;             // columns per tile (16 per wavefront)
 constexpr int BT2_SLOTS = 256;            // workgroups resident at once
 
-size_t bt2_ws_bytes(int64_t n, int64_t nc) {
-  (void)n; (void)nc;
-  return 256 + sizeof(cd) * (size_t)BT2_CHUNK * BT2_NG * BT2_VR * BT2_NB;
+// Launches whose T factors are formed at once.  bt2_tgen is latency bound (a
+// launch takes 25 us for the 64 blocks of one bt2_apply, which waits for it);
+// over eight launches it takes 53 us.
+constexpr int BT2_AHEAD = 8;
+constexpr int64_t BT2_BLOCK_ELEMS = BT2_NG * BT2_VR * BT2_NB;      // V T of one block
+// most blocks of one launch at order n
+inline int64_t bt2_launch_blocks(int64_t n) {
+  const int64_t g = n > 2 ? (n - 2) / BT2_G + 1 : 1;
+  return g < BT2_CHUNK ? g : BT2_CHUNK;
 }
+
+size_t bt2_ws_bytes(int64_t n, int64_t nc) {
+  (void)nc;
+  return 256 + sizeof(cd) * (size_t)(BT2_AHEAD * bt2_launch_blocks(n) * BT2_BLOCK_ELEMS);
+}
+// The launches of one bt2_tgen: launch l takes the blocks Gb .. Gb - cnt + 1 of
+// step `step`; its factors start at l bt2_launch_blocks(n) blocks.
+struct Bt2Ahead {
+  int32_t step[BT2_AHEAD], Gb[BT2_AHEAD], cnt[BT2_AHEAD];
+};
 
 // Block B_{G,k} holds the reflectors j = 0 .. 63 of sweeps s0 + j at position
 // k; reflector j covers rows j .. j + 63 of the block (block row 0 = global row
@@ -344,17 +360,18 @@ size_t bt2_ws_bytes(int64_t n, int64_t nc) {
 // 16 g .. 16 g + 79 of the block) and T the upper triangular factor of the
 // forward recurrence T_ii = tau_i, T_{0:i,i} = -tau_i T_{0:i,0:i} V_{:,0:i}^H v_i.
 
-// T of group g of the launch's block b (one workgroup each), then V T (80 x 16)
-// at Tws + (b BT2_NG + g) 1280.
+// T of group g of block b of launch l = blockIdx.z (one workgroup each), then
+// V T (80 x 16) at Tws + ((l per_launch + b) BT2_NG + g) 1280.
 __global__ void __launch_bounds__(256) bt2_tgen(int64_t n, const cd *V2, const cd *tau2, cd *Tws, int64_t Gmax,
-                                              int64_t step, int64_t Gb) {
+                                              Bt2Ahead ahead, int64_t per_launch) {
   __shared__ cd v[BT2_NB][BW];
   __shared__ cd tau[BT2_NB];
   __shared__ cd G[BT2_NB][BT2_NB + 1];
   __shared__ cd T[BT2_NB][BT2_NB + 1];
   const int g = blockIdx.x;
   const int64_t b = blockIdx.y;
-  const int64_t Gi = Gb - b;
+  if (b >= ahead.cnt[blockIdx.z]) return;
+  const int64_t step = ahead.step[blockIdx.z], Gi = ahead.Gb[blockIdx.z] - b;
   const int64_t k = step - (Gmax - Gi);
   const int64_t s0 = Gi * BT2_G + g * BT2_NB;      // sweep of the group's column 0
   const int64_t base = hb_voff(n, k);
@@ -402,7 +419,7 @@ __global__ void __launch_bounds__(256) bt2_tgen(int64_t n, const cd *V2, const c
   __syncthreads();
   // V T (80 x 16): row rho, column c = sum_{i <= c} v_i[rho - i] T[i][c], stored
   // row-major with the columns XOR-swizzled by row as the apply kernel keeps it
-  cd *out = Tws + (b * BT2_NG + g) * (BT2_VR * BT2_NB);
+  cd *out = Tws + ((blockIdx.z * per_launch + b) * BT2_NG + g) * (BT2_VR * BT2_NB);
   for (int e = tid; e < BT2_VR * BT2_NB; e += 256) {
     const int rho = e / BT2_NB, c = e % BT2_NB;
     cd acc = cmake(0.0, 0.0);
@@ -781,16 +798,19 @@ int bt2_run(int64_t n, int64_t nc, const mmf_z *V2z, const mmf_z *tau2z, const d
   const int64_t Gmax = (n - 2) / BT2_G;
   const int64_t Kmax = (n - 2) / BW;
   const unsigned ntile = cdiv(nc, BT2_TILE);
-  for (int64_t step = 0; step <= Gmax + Kmax; ++step) {
-    // blocks G with k = step - (Gmax - G) in [0, Kmax] and BT2_G G + BW k <= n - 2
-    int64_t Glo = Gmax - step > 0 ? Gmax - step : 0;
-    int64_t Ghi = Gmax;
-    while (Ghi >= Glo && (Ghi * BT2_G + (step - (Gmax - Ghi)) * BW > n - 2)) --Ghi;
-    if (Ghi < Glo) continue;
-    for (int64_t Gb = Ghi; Gb >= Glo; Gb -= BT2_CHUNK) {
-      const int64_t cnt = (Gb - Glo + 1 < BT2_CHUNK) ? Gb - Glo + 1 : BT2_CHUNK;
-      hipLaunchKernelGGL(bt2_tgen, dim3(BT2_NG, (unsigned)cnt), dim3(256), 0, st, n, V2, tau2, Tws, Gmax, step, Gb);
-      MMF_LAUNCH_CHECK();
+  const int64_t per_launch = bt2_launch_blocks(n);
+  Bt2Ahead ahead;
+  int held = 0;                                     // launches collected
+  auto flush = [&]() -> int {
+    if (held == 0) return MMF_OK;
+    int64_t most = 0;
+    for (int l = 0; l < held; ++l) most = ahead.cnt[l] > most ? ahead.cnt[l] : most;
+    hipLaunchKernelGGL(bt2_tgen, dim3(BT2_NG, (unsigned)most, (unsigned)held), dim3(256), 0, st, n, V2, tau2, Tws, Gmax,
+                       ahead, per_launch);
+    MMF_LAUNCH_CHECK();
+    for (int l = 0; l < held; ++l) {
+      const int64_t step = ahead.step[l], Gb = ahead.Gb[l], cnt = ahead.cnt[l];
+      const cd *Tl = Tws + l * per_launch * BT2_BLOCK_ELEMS;
       const int ks = ktimer_begin("bt2", st);
       // one workgroup per CU at most (all resident at once: a workgroup that
       // had to wait for a free CU would double the launch), the launch's
@@ -798,10 +818,10 @@ int bt2_run(int64_t n, int64_t nc, const mmf_z *V2z, const mmf_z *tau2z, const d
       const int64_t pairs = cnt * (int64_t)ntile;
       const unsigned nwg = (unsigned)(pairs < BT2_SLOTS ? pairs : BT2_SLOTS);
       if (rm)
-        hipLaunchKernelGGL(bt2_apply<true>, dim3(nwg), dim3(BT2_THREADS), 0, st, n, nc, V2, Tws, Phi, ldphi, Gmax,
+        hipLaunchKernelGGL(bt2_apply<true>, dim3(nwg), dim3(BT2_THREADS), 0, st, n, nc, V2, Tl, Phi, ldphi, Gmax,
                            step, Gb, cnt, (int64_t)ntile, sink);
       else
-        hipLaunchKernelGGL(bt2_apply<false>, dim3(nwg), dim3(BT2_THREADS), 0, st, n, nc, V2, Tws, Phi, ldphi, Gmax,
+        hipLaunchKernelGGL(bt2_apply<false>, dim3(nwg), dim3(BT2_THREADS), 0, st, n, nc, V2, Tl, Phi, ldphi, Gmax,
                            step, Gb, cnt, (int64_t)ntile, sink);
       MMF_LAUNCH_CHECK();
       if (ks >= 0) {
@@ -819,6 +839,28 @@ int bt2_run(int64_t n, int64_t nc, const mmf_z *V2z, const mmf_z *tau2z, const d
         ktimer_end(ks, st, fl);
       }
     }
+    held = 0;
+    return MMF_OK;
+  };
+  for (int64_t step = 0; step <= Gmax + Kmax; ++step) {
+    // blocks G with k = step - (Gmax - G) in [0, Kmax] and BT2_G G + BW k <= n - 2
+    int64_t Glo = Gmax - step > 0 ? Gmax - step : 0;
+    int64_t Ghi = Gmax;
+    while (Ghi >= Glo && (Ghi * BT2_G + (step - (Gmax - Ghi)) * BW > n - 2)) --Ghi;
+    if (Ghi < Glo) continue;
+    for (int64_t Gb = Ghi; Gb >= Glo; Gb -= BT2_CHUNK) {
+      ahead.step[held] = (int32_t)step;
+      ahead.Gb[held] = (int32_t)Gb;
+      ahead.cnt[held] = (int32_t)((Gb - Glo + 1 < BT2_CHUNK) ? Gb - Glo + 1 : BT2_CHUNK);
+      if (++held == BT2_AHEAD) {
+        const int rc = flush();
+        if (rc) return rc;
+      }
+    }
+  }
+  {
+    const int rc = flush();
+    if (rc) return rc;
   }
   if (rm) {
     const unsigned nt = cdiv(n, 32);
