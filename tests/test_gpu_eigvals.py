@@ -92,3 +92,25 @@ def test_lattice_full_size_one_frequency():
     qo = oracle.quasienergies(p)
     assert q.shape == qo.shape == (5376,)
     assert np.abs(q - qo).max() <= 1e-10 * max(1.0, np.abs(qo).max())
+
+
+@pytest.mark.parametrize("n", [1, 2, 7, 8, 9, 10, 16, 17, 18, 25, 65])
+@pytest.mark.parametrize("scale", [1.0, 1e-100, 1e100])
+def test_eigvalsh_row_batches_and_scales(n, scale):
+    """Orders around the Sturm count's batches of eight rows, with repeated
+    eigenvalues and exact zeros, at scales whose squares are far from one
+    (n eps |A| times 10)."""
+    torch, mmf = require_gpu()
+    rng = np.random.default_rng(n)
+    A = rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))
+    Q = np.linalg.qr(A)[0]
+    w0 = np.sort(np.round(rng.normal(size=n), 0))
+    H = (Q * w0) @ Q.conj().T
+    H = scale * (H + H.conj().T) / 2
+    log(f"eigvalsh rows n={n} scale={scale}")
+    ws, info = mmf.eigvalsh_batched([to_dev_cm(torch, H)])
+    torch.cuda.synchronize()
+    assert not info.any().item()
+    w = ws[0].cpu().numpy() / scale
+    assert np.all(np.diff(w) >= 0)
+    assert np.abs(w - w0).max() <= 10 * max(n, 10) * np.finfo(float).eps * max(1.0, np.abs(w0).max())
