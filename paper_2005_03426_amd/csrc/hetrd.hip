@@ -116,10 +116,10 @@ __host__ __device__ inline int ht_strip(int64_t n, int64_t p) {
   const int64_t want = (nb * (nb - 1) / 2 + 127) / 128;
   return (int)(want < 1 ? 1 : (want > HV_CH ? HV_CH : want));
 }
-// Strip slots of the panel's widest block column.
-__host__ __device__ inline int ht_slots(int64_t n, int64_t i, int ch) {
-  const int64_t inner = n / HV_T - (i + 1) / HV_T - 1;
-  return 2 + (inner > 0 ? (int)((inner + ch - 1) / ch) : 0);
+// Strips of local block column lb of column i's trailing matrix.
+__host__ __device__ inline int ht_strips(int64_t n, int64_t i, int ch, int64_t lb) {
+  const int64_t inner = n / HV_T - (i + 1) / HV_T - lb - 1;
+  return inner > 0 ? (int)((inner + ch - 1) / ch) : 0;
 }
 // Rows per wavefront of the panel products: one round of four loads per lane
 // while the partials stay few, longer chunks for long columns.
@@ -251,12 +251,16 @@ __device__ void ht_dots_wave(const HtProb<R> &pq, int64_t i, int k, int g, int q
 // A_trail = A[i+1:, i+1:].  Tiles lie on the absolute 64 x 64 grid of A
 // (block b covers rows 64b .. 64b+63), so on a leading dimension divisible by
 // 8 every column segment a load touches starts on a 128-byte line; b0 is the
-// block holding row i+1 and local block lb = b - b0 = blockIdx.x.
-//   blockIdx.y == 0: the diagonal tile of the block column (masked: lower
-//     triangle, real diagonal); also stores v of these rows;
-//   blockIdx.y == 1: its tile in the last block row when that is partial;
-//   blockIdx.y in [2, dot_slot): interior tiles, chunk y-2 of `ch` tiles;
-//   blockIdx.y >= dot_slot: the panel products.
+// block holding row i+1 and local block lb = b - b0.  Work items:
+//   blockIdx.y < strip_rows: the strips of `ch` interior tiles, block columns
+//     x and nbl - 1 - x one after the other (the triangle folded, so that few
+//     workgroups are empty);
+//   the others, in a row: the diagonal tiles (slot 0; masked: lower triangle,
+//     real diagonal; they also store v of their rows), the tiles in the last
+//     block row when that is partial (slot 1), the panel products.
+// (One workgroup per block column and slot of the widest one, and per block
+// column and product, left three of four empty: 20 matrices of order 1900
+// took 127 ms against 120 now, 48 of order 900 48 against 43.)
 // The four wavefronts share every tile, wave w taking its columns
 // 16w .. 16w+15 (lane: rows rg + 16q, columns 16w + 4cg + j), so a lane holds
 // 16 elements per tile; the next tile is loaded while the current one is
@@ -277,7 +281,7 @@ __device__ void ht_dots_wave(const HtProb<R> &pq, int64_t i, int k, int g, int q
 // against 93.3 at 4000, 184.5 against 203.4 at 6000, 389.8 against 396.2 at
 // 8000, but 947.6 against 897.3 at 11000: NT above HV_NT_BYTES.
 template <typename R, bool NT, bool STRIP>
-__global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t p, int k, int dot_slot) {
+__global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t p, int k, int strip_rows) {
   typedef cx<R> C;
   typedef typename NtVec<R>::v nv;
   __shared__ C red[2][4][HV_T];
@@ -289,23 +293,43 @@ __global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t
   const int64_t b0 = (i + 1) / HV_T;
   const int64_t nb = (n + HV_T - 1) / HV_T;        // absolute blocks
   const int64_t nfull = n / HV_T;                   // blocks entirely inside the matrix
-  const int64_t lb = blockIdx.x;
-  const int64_t bj = b0 + lb;
-  if (bj >= nb) return;
-  const int slot = blockIdx.y;
+  const int nbl = (int)(nb - b0);
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  if (slot >= dot_slot) {                           // panel products of this column
-    const int qq = (slot - dot_slot) * 4 + wave;
-    if (lb < (n - i - 1 + dr - 1) / dr && qq < 2 * k) ht_dots_wave(q, i, k, (int)lb, qq, dr);
-    return;
+  int lb, slot;
+  int64_t first;                                    // first tile's block row
+  if ((int)blockIdx.y < strip_rows) {
+    lb = blockIdx.x;
+    if (2 * lb > nbl - 1) return;
+    int c = blockIdx.y;
+    const int c0 = ht_strips(n, i, ch, lb);
+    if (c >= c0) {
+      c -= c0;
+      const int other = nbl - 1 - lb;
+      if (other == lb || c >= ht_strips(n, i, ch, other)) return;
+      lb = other;
+    }
+    slot = 2 + c;
+    first = b0 + lb + 1 + (int64_t)c * ch;
+  } else {
+    int item = ((int)blockIdx.y - strip_rows) * (int)gridDim.x + (int)blockIdx.x;
+    const bool edge = nb != nfull;
+    if (item >= 2 * nbl) {                          // panel products of this column
+      item -= 2 * nbl;
+      const int chunks = (int)((n - i - 1 + dr - 1) / dr);
+      const int qq = item / chunks * 4 + wave;
+      if (qq < 2 * k) ht_dots_wave(q, i, k, item % chunks, qq, dr);
+      return;
+    }
+    slot = item >= nbl;
+    lb = slot ? item - nbl : item;
+    first = slot ? nb - 1 : b0 + lb;
+    if (slot && (!edge || lb == nbl - 1)) {         // its partial of v^H A v is summed all the same
+      if (tid == 0) q.sparts[lb * nchmax + 1] = R(0);
+      return;
+    }
   }
-  const int64_t first = slot == 0 ? bj : (slot == 1 ? nb - 1 : bj + 1 + (int64_t)(slot - 2) * ch);
-  const bool idle = slot == 1 ? (nb == nfull || bj >= nb - 1) : (slot >= 2 && first >= nfull);
-  if (idle) {                                       // its partial of v^H A v is summed all the same
-    if (tid == 0 && slot < ht_slots(n, i, ch)) q.sparts[lb * nchmax + slot] = R(0);
-    return;
-  }
+  const int64_t bj = b0 + lb;
   const MMF_GLOBAL C *A = (const MMF_GLOBAL C *)q.A;
   const MMF_GLOBAL C *x = (const MMF_GLOBAL C *)q.x;
   MMF_GLOBAL C *pdir = (MMF_GLOBAL C *)q.pdir, *ptrn = (MMF_GLOBAL C *)q.ptrn;
@@ -508,8 +532,7 @@ __global__ void __launch_bounds__(WIDE ? 512 : 256) ht_finish(const HtProb<R> *p
       u3 = cadd(u3, gload(pc + (lb + 12) * mpad));
     }
     for (; lb <= lbi; lb += 4) u0 = cadd(u0, gload(pc + lb * mpad));
-    const int64_t inner = nfull - (b0 + lbi) - 1;   // interior tiles below this block's diagonal
-    const int nin = inner > 0 ? (int)((inner + ch - 1) / ch) : 0;
+    const int nin = ht_strips(n, i, ch, lbi);
     const bool edge = nb != nfull && b0 + lbi < nb - 1;
     const MMF_GLOBAL C *pt = ptrn + lbi * nchmax * HV_T + lane;
     if (wave == 1) u1 = cadd(u1, gload(pt));
@@ -536,17 +559,18 @@ __global__ void __launch_bounds__(WIDE ? 512 : 256) ht_finish(const HtProb<R> *p
   } else if (part2 == 5 || part2 == 6) {
     // ---- v^H A v
     const int nbl = (int)(nb - b0), t = (part2 - 5) * 64 + lane;
-    const int nsl = ht_slots(n, i, ch);
     R s = 0;
-    for (int lb = t >> 3; lb < nbl; lb += 16)
+    for (int lb = t >> 3; lb < nbl; lb += 16) {
+      const int nsl = 2 + ht_strips(n, i, ch, lb);
 #pragma unroll 4
       for (int c = t & 7; c < nsl; c += 8) s += gload(sparts + lb * nchmax + c);
+    }
     s = wave_sum(s);
     if (lane == 0) sh[part2 - 5] = s;
   } else if (part2 == 7) {
     // ---- row i+1 of the partials and of V, W
     const int row = (int)(i + 1 - b0 * HV_T);
-    const int nin = ht_slots(n, i, ch) - 2;
+    const int nin = ht_strips(n, i, ch, 0);
     const bool edge = nb != nfull && b0 < nb - 1;
     if (lane < k) {
       cv[lane] = cconj(gload(P3 + (i + 1) + (int64_t)lane * n));
@@ -749,12 +773,12 @@ int hetrd_grouped(const HtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
   const unsigned Z = (unsigned)count;
   const int64_t ps = ht_tail_start(nmax);
   for (int64_t p = 0; p < ps; p += HT_NB) {
-    int nslot = 2, strip = 1;                        // most slots and longest strip of any matrix in this panel
+    int rows = 0, strip = 1;                         // most strip rows and longest strip of any matrix in this panel
     for (int64_t c = 0; c < count; ++c) {
       if (p >= ht_tail_start(nh[c])) continue;
-      const int ch = ht_strip(nh[c], p), sl = ht_slots(nh[c], p, ch);
+      const int ch = ht_strip(nh[c], p), sl = ht_strips(nh[c], p, ch, 0) + 1;   // two folded columns have at most these
       strip = ch > strip ? ch : strip;
-      nslot = sl > nslot ? sl : nslot;
+      rows = sl > rows ? sl : rows;
     }
     hipLaunchKernelGGL(ht_colnorm<R>, dim3(cdiv(cdiv(nmax, HV_T) - p / HV_T, 4), 1, Z), dim3(256), 0, st, pr, p);
     MMF_LAUNCH_CHECK();
@@ -762,15 +786,22 @@ int hetrd_grouped(const HtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
       const int64_t i = p + k;
       // anchored 64-blocks of the largest matrix: block columns b0 .. nb-1
       const int64_t nbl = (nmax + HV_T - 1) / HV_T - (i + 1) / HV_T;
-      const int dot_rows = (2 * k + 3) / 4;          // four panel products per workgroup
+      const int64_t gx = (nbl + 1) / 2;
+      int64_t items = 0;                             // most diagonal, edge and product workgroups of any matrix
+      for (int64_t c = 0; c < count; ++c) {
+        if (p >= ht_tail_start(nh[c])) continue;
+        const int64_t dr = ht_dot_rows(nh[c]), nb = (nh[c] + HV_T - 1) / HV_T - (i + 1) / HV_T;
+        const int64_t it = 2 * nb + (2 * k + 3) / 4 * ((nh[c] - i - 1 + dr - 1) / dr);   // four products per workgroup
+        items = it > items ? it : items;
+      }
       const int ks = ktimer_begin(sizeof(R) == 8 ? "hemv" : "hemv_c64", st);
-      const dim3 grid((unsigned)nbl, (unsigned)(nslot + dot_rows), Z);
+      const dim3 grid((unsigned)gx, (unsigned)(rows + (items + gx - 1) / gx), Z);
       if ((int64_t)sizeof(cx<R>) * (nmax - p) * (nmax - p) / 2 > HV_NT_BYTES)
-        hipLaunchKernelGGL((ht_column<R, true, true>), grid, dim3(256), 0, st, pr, p, k, nslot);
+        hipLaunchKernelGGL((ht_column<R, true, true>), grid, dim3(256), 0, st, pr, p, k, rows);
       else if (strip > 1)
-        hipLaunchKernelGGL((ht_column<R, false, true>), grid, dim3(256), 0, st, pr, p, k, nslot);
+        hipLaunchKernelGGL((ht_column<R, false, true>), grid, dim3(256), 0, st, pr, p, k, rows);
       else
-        hipLaunchKernelGGL((ht_column<R, false, false>), grid, dim3(256), 0, st, pr, p, k, nslot);
+        hipLaunchKernelGGL((ht_column<R, false, false>), grid, dim3(256), 0, st, pr, p, k, rows);
       MMF_LAUNCH_CHECK();
       if (ks >= 0) {
         // algorithmic bytes: the lower triangle of every trailing matrix, read
