@@ -10,8 +10,9 @@
 //       e_ij = (s_ij + lam_j r_ij) / (lam_j - lam_i),
 //   e_ii = r_ii / 2, and inside a cluster e_ij = r_ij / 2;  X <- X (I + E).
 //   Before the correction, every cluster is moved to its Rayleigh-Ritz
-//   basis: Q_C diagonalises the cluster block of T = S - (R S + S R)/2 (the
-//   first-order projection onto the orthonormalised cluster basis) and
+//   basis: Q_C diagonalises the cluster block of T = S + (R S + S R)/2 (the
+//   first-order projection onto the orthonormalised cluster basis X (I + R/2),
+//   in which the corrections leave the cluster) and
 //   X <- X Q, S <- Q^H S Q, G <- Q^H G Q, so that the corrections coupling a
 //   cluster to the rest use the Ritz values of its rotated vectors.
 // Clusters are runs of consecutive eigenvalues closer than
@@ -275,7 +276,7 @@ __global__ void __launch_bounds__(256) rf_build_f(int64_t n, cd *S, const cd *G,
   }
 }
 
-// Cluster blocks: T = S_CC - (R S + S R)/2 with R = I - G (first order,
+// Cluster blocks: T = S_CC + (R S + S R)/2 with R = I - G (first order,
 // sums over the chunk's members), diagonalised by one workgroup per chunk
 // with the parallel Jacobi method in LDS; Q (size x size, column-major at the
 // chunk's offset in Qbuf) and the Ritz values are stored for the rotations.
@@ -306,7 +307,7 @@ __global__ void __launch_bounds__(256) rf_cluster_rr(int64_t n, const cd *S, con
       for (int k = 0; k < sz; ++k)
         sum = cadd(sum, cadd(cmul(L.Q[a * JAC_LD + k], L.T[k * JAC_LD + b]),
                              cmul(L.T[a * JAC_LD + k], L.Q[k * JAC_LD + b])));
-      acc[q] = csub(L.T[a * JAC_LD + b], cscale(sum, 0.5));
+      acc[q] = cadd(L.T[a * JAC_LD + b], cscale(sum, 0.5));
     }
     __syncthreads();
     for (int q = 0; q < CL_MAX * CL_MAX / 256; ++q) {

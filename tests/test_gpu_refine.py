@@ -59,6 +59,21 @@ def test_refined_degenerate_level_of_40():
     assert int(out["P_status"].item()) == mmf.MMF_ERR_DEGENERATE
 
 
+@pytest.mark.parametrize("n,run,spread", [(100, 12, 1e-9), (100, 40, 4e-9), (130, 60, 1e-9), (240, 20, 4e-9)])
+def test_refined_cluster_basis(n, run, spread):
+    """Clusters of non-orthogonal complex64 vectors are rotated to the Ritz
+    basis of the orthonormalised ones: no coupling of the order of
+    eps32^2 .. eps32 |G - I| is left inside a cluster when info is 0."""
+    torch, mmf = require_gpu()
+    log(f"refined: near-degenerate run of {run}, n={n}, 8 matrices")
+    for seed in range(8):
+        H = _near_run(n, run, spread, seed=100 * seed + run)
+        w, Phi, info = _solve(H, mmf.MMF_C64_REFINED)
+        assert info == 0
+        assert np.linalg.norm(H @ Phi - Phi * w) < 1e-12 * np.linalg.norm(H), f"seed {seed}"
+        assert np.abs(Phi.conj().T @ Phi - np.eye(n)).max() < 1e-12
+
+
 @pytest.mark.parametrize("run,spread", [(40, 4e-9), (100, 1e-8)])
 def test_refined_near_degenerate_run(run, spread):
     torch, mmf = require_gpu()
