@@ -28,9 +28,9 @@
 //     workgroup) and leaves its norm partials.
 // Four launches per column (reflector, product, u, w with the next column)
 // took 18.5 us per column at order 82, 23 at 450 and 31.5 at 1715
-// (profiled); the two take 3.1 (all in the tail), 10.0 and 11.9.
+// (profiled); the two take 2.1 (all in the tail), 10.0 and 11.9.
 // The last HT_TAIL rows of every matrix (all of a smaller one) are reduced by
-// one workgroup in LDS (ht_tail).
+// one workgroup in registers (ht_tail).
 // All sums are over fixed partitions in fixed order (deterministic).
 //
 // Every kernel is a template over the scalar type R: R = double is the
@@ -55,8 +55,8 @@ constexpr int HV_T = 64;        // HEMV tile
 constexpr int HV_CH = 8;        // most interior tiles per HEMV workgroup (one block column strip)
 constexpr int64_t HV_NT_BYTES = (int64_t)512 << 20;   // lower trailing triangle from which its tiles are read non-temporally
 constexpr int DOT_MIN = 256;    // fewest rows per wavefront of the panel dot products
-constexpr int HT_TAIL = 92;     // largest order of the LDS tail: 92 x 93 complex128 + partials = 156 KB
-constexpr int TAIL_THREADS = 1024;
+constexpr int HT_TAIL = 128;    // largest order of the register tail: 32 entries a lane
+constexpr int TAIL_THREADS = 512;
 
 // First column of the tail: the panels before it are all full.
 __host__ __device__ inline int64_t ht_tail_start(int64_t n) {
@@ -631,114 +631,202 @@ __global__ void __launch_bounds__(WIDE ? 512 : 256) ht_finish(const HtProb<R> *p
   }
 }
 
+// a - v conj(wc) - w conj(vc)
+template <typename R>
+__device__ __forceinline__ cx<R> ht_rank2(cx<R> a, cx<R> v, cx<R> w, cx<R> vc, cx<R> wc) {
+  a.re = fma(-w.im, vc.im, fma(-w.re, vc.re, fma(-v.im, wc.im, fma(-v.re, wc.re, a.re))));
+  a.im = fma(w.re, vc.im, fma(-w.im, vc.re, fma(v.re, wc.im, fma(-v.im, wc.re, a.im))));
+  return a;
+}
+
+// Entry kk of the accumulators (block kk / 4, register kk % 4) for a uniform
+// kk: a tree of scalar branches (the empty asm keeps the compiler from merging
+// its leaves to one indexed read, for which the array would go to memory).
+template <int LO, int N, typename R, typename V>
+__device__ __forceinline__ cx<R> ht_pick(const V (&re)[8], const V (&im)[8], int kk) {
+  if constexpr (N == 1) {
+    cx<R> t = cmk<R>(re[LO / 4][LO % 4], im[LO / 4][LO % 4]);
+    asm("" : "+v"(t.re), "+v"(t.im));
+    return t;
+  } else {
+    return kk < LO + N / 2 ? ht_pick<LO, N / 2, R>(re, im, kk) : ht_pick<LO + N / 2, N / 2, R>(re, im, kk);
+  }
+}
+
+// Barrier that orders LDS only (__syncthreads also waits for the global stores in flight).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // The last m <= HT_TAIL rows (columns ps .. n-1) of every matrix by one
-// workgroup: the Hermitian block in LDS with both triangles, per column the
-// product u = A v and the rank-2 update A -= v w^H + w v^H over all rows
-// (32-lane units: row group, column part).  The scalars are derived by every
-// wavefront for itself; three barriers per column.  A chain of m columns:
-// latency bound, 2.0 us per column (order 66) to 3.1 (82) against 10.0 for
-// the two launches at order 450.
+// workgroup, the Hermitian block (both triangles) in registers in the layout
+// of the matrix cores' accumulators, at the end of a 128 x 128 frame:
+// wavefront w holds columns 16 w .. 16 w + 15 of all rows, lane (lrow, lk) the
+// rows MfmaT::row(r, lk) of every 16-row block of column 16 w + lrow.  Per
+// column j:
+//   x = column j, read as the conjugate of row j (its update by column j-1
+//     applied on the fly), shared; barrier;
+//   A -= v w^H + w v^H of column j-1: the complex rank-2 update is one
+//     four-deep real product each for the real and the imaginary part, one
+//     matrix instruction per 16 x 16 block; beside it the scalars and
+//     y_c = sum_r conj(a_rc) x_r, whole in the wavefront of its column; y and
+//     row j+1 (for u = scale (y - beta a_{j+1}): v = scale x but for v_{j+1} =
+//     1) shared; barrier;
+//   g = v^H u and w = tau u - (|tau|^2 g / 2) v by every wavefront for itself,
+//     v and w into its own operand copy P in LDS.
+// Blocks of finished rows and wavefronts of finished columns drop out; rows
+// above them are multiplied by zeros of v, w and x.
+// Bound: the chain of m columns, of which the code takes what it can off the
+// path between the barriers.  Order 82: 254 us with the block in LDS (three
+// barriers, at most 92 rows), 195 with rows on lanes, columns in registers and
+// operands broadcast from LDS, 167 now.  The two launches of a longer
+// matrix cost 10 us a column.
 template <typename R>
 __global__ void __launch_bounds__(TAIL_THREADS) ht_tail(const HtProb<R> *pr) {
   typedef cx<R> C;
-  extern __shared__ __attribute__((aligned(16))) char tail_smem[];
+  typedef MfmaT<R> MF;
+  typedef typename MF::v4 v4;
+  static_assert(TAIL_THREADS == 512 && HT_TAIL == 128, "one wavefront per 16 columns");
+  __shared__ C xs[HT_TAIL], us[HT_TAIL], as[HT_TAIL];
+  __shared__ R P[8][HT_TAIL][4];                    // per wavefront: Re v, Im v, Re w, Im w of a row
   const HtProb<R> &q = pr[blockIdx.z];
   const int64_t n = q.n, lda = q.lda;
   if (n <= 0) return;
   const int64_t ps = ht_tail_start(n);
-  const int m = (int)(n - ps), ld = m | 1;
-  C *red = reinterpret_cast<C *>(tail_smem);       // TAIL_THREADS
-  C *vs = red + TAIL_THREADS, *ws = vs + 96, *S = ws + 96;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int unit = tid >> 5, l = tid & 31;
+  const int o = HT_TAIL - (int)(n - ps);            // frame row of the first one
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lrow = lane & 15, lk = lane >> 4, col = 16 * wave + lrow;
   MMF_GLOBAL C *A = (MMF_GLOBAL C *)q.A + ps + ps * lda;
-  for (int c = unit; c < m; c += TAIL_THREADS / 32)
-    for (int r = c + l; r < m; r += 32) {
-      C t = gload(A + r + c * lda);
-      if (r == c) t.im = R(0);
-      S[c * ld + r] = t;
-      S[r * ld + c] = cconj(t);
+  MMF_GLOBAL double *d = (MMF_GLOBAL double *)q.d + ps, *e = (MMF_GLOBAL double *)q.e + ps;
+  MMF_GLOBAL C *tq = (MMF_GLOBAL C *)q.tau + ps;
+  // register and lane group of row j
+  constexpr bool PACKED = sizeof(R) == 4;           // MfmaT::row(r, lk) = 4 lk + r, else 4 r + lk
+  const auto reg_of = [](int j) { return (j & ~15) / 4 + (PACKED ? j & 3 : (j >> 2) & 3); };
+  const auto grp_of = [](int j) { return PACKED ? (j >> 2) & 3 : j & 3; };
+  v4 are[8], aim[8];
+#pragma unroll
+  for (int b = 0; b < 8; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * b + MF::row(r, lk);
+      const bool ok = row >= o && col >= o;
+      const C t = gload(A + (ok ? (row >= col ? (row - o) + (col - o) * lda : (col - o) + (row - o) * lda) : 0));
+      are[b][r] = t.re;
+      aim[b][r] = t.im;
     }
-  __syncthreads();
-  for (int j = 0; j < m - 1; ++j) {
-    const int cnt = m - 1 - j;                      // rows j+1 .. m-1
-    const int G = (cnt + 31) >> 5;                  // row groups of 32 (1 .. 3)
-    const int part = G == 1 ? unit : (G == 2 ? unit >> 1 : unit / 3);
-    const int rgp = unit - part * G;
-    const int parts = G == 1 ? 32 : (G == 2 ? 16 : 10);
-    const int rr = rgp * 32 + l;                    // row relative to j+1
-    const bool act = rr < cnt && part < parts;
-    const C *xc = S + j * ld + j + 1;               // column j from row j+1
-    C *T = S + (j + 1) * ld + j + 1;                // trailing block
-    R xn = 0;
-    if (lane >= 1 && lane < cnt) xn = cabs2(xc[lane]);
-    if (lane + 64 < cnt) xn += cabs2(xc[lane + 64]);
-    const C alpha = xc[0];
-    R beta;
-    C tau, scale;
-    ht_scalars<R>(alpha, wave_sum(xn), beta, tau, scale);
-    // u = scale (A x'), x' = (alpha - beta, x): v = scale x'
-    C y = cmk<R>(0, 0);
-    if (act) {
-      for (int c = part; c < cnt; c += parts) {
-        C xv = xc[c];
-        if (c == 0) xv.re -= beta;
-        y = cadd(y, cmul(T[c * ld + rr], xv));
+  {                                                 // masks afresh: those of the addresses would not fit the scalar registers
+    int c2 = col >= o ? col : -1;
+    asm("" : "+v"(c2));
+#pragma unroll
+    for (int b = 0; b < 8; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * b + MF::row(r, lk);
+        const bool ok = row >= o && c2 >= 0;
+        are[b][r] = ok ? are[b][r] : R(0);
+        aim[b][r] = !ok || row == c2 ? R(0) : row > c2 ? aim[b][r] : -aim[b][r];
       }
-    }
-    red[part * 32 * G + rr] = y;                    // unused units write past the summed parts
-    __syncthreads();
-    if (wave == 0) {
-      C u0 = cmk<R>(0, 0), u1 = u0, v0 = u0, v1 = u0;
-      if (lane < cnt) {
-        for (int g = 0; g < parts; ++g) u0 = cadd(u0, red[g * 32 * G + lane]);
-        u0 = cmul(scale, u0);
-        v0 = lane == 0 ? cmk<R>(1, 0) : cmul(scale, xc[lane]);
-      }
-      if (lane + 64 < cnt) {
-        for (int g = 0; g < parts; ++g) u1 = cadd(u1, red[g * 32 * G + lane + 64]);
-        u1 = cmul(scale, u1);
-        v1 = cmul(scale, xc[lane + 64]);
-      }
-      const R g = wave_sum(cmulc(v0, u0).re + cmulc(v1, u1).re);
-      const R h = R(-0.5) * cabs2(tau) * g;
-      if (lane < cnt) {
-        vs[lane] = v0;
-        ws[lane] = cadd(cmul(tau, u0), cscale(v0, h));
-        S[j * ld + j + 1 + lane] = v0;
-      }
-      if (lane + 64 < cnt) {
-        vs[lane + 64] = v1;
-        ws[lane + 64] = cadd(cmul(tau, u1), cscale(v1, h));
-        S[j * ld + j + 1 + lane + 64] = v1;
-      }
-      if (lane == 0) {
-        q.d[ps + j] = (double)S[j * ld + j].re;
-        q.e[ps + j] = (double)beta;
-        q.tau[ps + j] = tau;
-      }
-    }
-    __syncthreads();
-    if (act) {
-      const C vr = vs[rr], wr = ws[rr];
-      for (int c = part; c < cnt; c += parts) {
-        C t = T[c * ld + rr];
-        t = csub(t, cmul(vr, cconj(ws[c])));
-        t = csub(t, cmul(wr, cconj(vs[c])));
-        if (c == rr) t.im = R(0);
-        T[c * ld + rr] = t;
-      }
-    }
-    __syncthreads();
   }
-  if (tid == 0) q.d[n - 1] = (double)S[(m - 1) * ld + m - 1].re;
-  for (int c = unit; c < m - 1; c += TAIL_THREADS / 32)
-    for (int r = c + 1 + l; r < m; r += 32) A[r + c * lda] = S[c * ld + r];
+#pragma unroll
+  for (int t = 0; t < HT_TAIL * 4 / 64; ++t) P[wave][0][lane + 64 * t] = R(0);
+  if (tid < HT_TAIL && tid < o) xs[tid] = cmk<R>(0, 0);
+  C nx = ht_pick<0, 32, R>(are, aim, reg_of(o));    // row j of A (in lane group grp_of(j)) without the last update
+  C vc = cmk<R>(0, 0), wc = vc, wj = vc;            // v, w of this lane's column, w of row j (v is 1 there)
+  R vj = 0;
+  C xa, xb, xc, tau, scale;                         // x of rows lane, 64 + lane and this lane's column
+  R beta, yr, yi;
+  for (int j = o;; ++j) {
+    if (16 * wave + 15 >= j) {
+      const C a = ht_rank2<R>(nx, cmk<R>(vj, 0), wj, vc, wc);
+      if (lk == grp_of(j)) {
+        xs[col] = cmk<R>(col > j ? a.re : R(0), col > j ? -a.im : R(0));
+        if (col == j) d[j - o] = (double)a.re;
+      }
+    }
+    if (j == HT_TAIL - 1) break;
+    lds_barrier();
+    const bool live = 16 * wave + 15 > j;
+    if (live) {
+      const R bre = -P[wave][col][lk ^ 2], bi = P[wave][col][lk ^ 3], bim = (lk & 1) ? -bi : bi;
+      R pa[8];
+#pragma unroll
+      for (int b = 0; b < 8; ++b) pa[b] = P[wave][16 * b + lrow][lk];
+      const C alpha = xs[j + 1];
+      xa = xs[lane];
+      xb = xs[64 + lane];
+      xc = xs[col];
+#pragma unroll
+      for (int h = 0; h < 4; ++h)
+        if (32 * h + 31 > j) {
+#pragma unroll
+          for (int b = 2 * h; b < 2 * h + 2; ++b) {
+            are[b] = MF::run(pa[b], bre, are[b]);
+            aim[b] = MF::run(pa[b], bim, aim[b]);
+          }
+        }
+      const R xn = (lane == j + 1 ? R(0) : cabs2(xa)) + (64 + lane == j + 1 ? R(0) : cabs2(xb));
+      ht_scalars<R>(alpha, wave_sum(xn), beta, tau, scale);
+      R sr[4], si[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sr[r] = si[r] = R(0);
+#pragma unroll
+      for (int h = 0; h < 4; ++h)
+        if (32 * h + 31 > j) {
+#pragma unroll
+          for (int b = 2 * h; b < 2 * h + 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const C x = xs[16 * b + MF::row(r, lk)];
+              sr[r] = fma(aim[b][r], x.im, fma(are[b][r], x.re, sr[r]));
+              si[r] = fma(-aim[b][r], x.re, fma(are[b][r], x.im, si[r]));
+            }
+        }
+      yr = rows_sum((sr[0] + sr[1]) + (sr[2] + sr[3]));
+      yi = rows_sum((si[0] + si[1]) + (si[2] + si[3]));
+      nx = ht_pick<0, 32, R>(are, aim, reg_of(j + 1));
+      if (lk == grp_of(j + 1)) {
+        us[col] = cmk<R>(yr, yi);
+        as[col] = cconj(nx);
+      }
+    }
+    lds_barrier();
+    if (live) {
+      const auto u_of = [&](C y, C a, bool on) {
+        const C u = cmul(scale, cmk<R>(fma(-beta, a.re, y.re), fma(-beta, a.im, y.im)));
+        return cmk<R>(on ? u.re : R(0), on ? u.im : R(0));
+      };
+      const bool ina = lane > j, inb = 64 + lane > j;
+      const C ua = u_of(us[lane], as[lane], ina), ub = u_of(us[64 + lane], as[64 + lane], inb);
+      const C uj = u_of(us[j + 1], as[j + 1], true), uc = u_of(cmk<R>(yr, yi), cconj(nx), col > j);
+      C va = cmul(scale, xa), vb = cmul(scale, xb);
+      if (lane == j + 1) va = cmk<R>(1, 0);
+      if (64 + lane == j + 1) vb = cmk<R>(1, 0);
+      vc = cmul(scale, xc);
+      if (col == j + 1) vc = cmk<R>(1, 0);
+      const R g = wave_sum(cmulc(va, ua).re + cmulc(vb, ub).re);
+      const R hh = R(-0.5) * cabs2(tau) * g;
+      wc = cadd(cmul(tau, uc), cscale(vc, hh));
+      wj = cmul(tau, uj);
+      wj.re += hh;
+      vj = 1;
+      const C wa = cadd(cmul(tau, ua), cscale(va, hh)), wb = cadd(cmul(tau, ub), cscale(vb, hh));
+      R *p = P[wave][lane];
+      p[0] = va.re; p[1] = va.im; p[2] = wa.re; p[3] = wa.im;
+      p = P[wave][64 + lane];
+      p[0] = vb.re; p[1] = vb.im; p[2] = wb.re; p[3] = wb.im;
+      if (wave == 7) {                              // live to the end
+        if (ina) A[lane - o + (j - o) * lda] = va;
+        if (inb) A[64 + lane - o + (j - o) * lda] = vb;
+        if (lane == 0) {
+          e[j - o] = (double)beta;
+          tq[j - o] = tau;
+        }
+      }
+    }
+  }
 }
-
-// LDS bytes of the tail of order m
-template <typename R>
-inline size_t ht_tail_lds(int64_t m) { return sizeof(cx<R>) * (size_t)(TAIL_THREADS + 2 * 96 + m * (m | 1)); }
 
 // Trailing update A[q0:, q0:] -= [V W] [W V]^H (lower tiles) after the panel
 // starting at column p, for every matrix of the table.
@@ -763,12 +851,8 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) ht_her2k(const HtProb<R> *pr,
 // (orders nh[0..count) on the host).
 template <typename R>
 int hetrd_grouped(const HtProb<R> *pr, const int64_t *nh, int64_t count, hipStream_t st) {
-  int64_t nmax = 0, tail = 0;
-  for (int64_t c = 0; c < count; ++c) {
-    nmax = nh[c] > nmax ? nh[c] : nmax;
-    const int64_t m = nh[c] - ht_tail_start(nh[c]);
-    tail = m > tail ? m : tail;
-  }
+  int64_t nmax = 0;
+  for (int64_t c = 0; c < count; ++c) nmax = nh[c] > nmax ? nh[c] : nmax;
   if (nmax <= 0 || count <= 0) return MMF_OK;
   const unsigned Z = (unsigned)count;
   const int64_t ps = ht_tail_start(nmax);
@@ -823,12 +907,7 @@ int hetrd_grouped(const HtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
     hipLaunchKernelGGL(ht_her2k<R>, dim3(t, t, Z), dim3(GEMM_THREADS), 0, st, pr, p);
     MMF_LAUNCH_CHECK();
   }
-  // dynamic LDS above the default limit must be allowed per kernel (once)
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&ht_tail<R>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     (int)ht_tail_lds<R>(HT_TAIL));
-  if (attr != hipSuccess) return MMF_ERR_HIP;
-  hipLaunchKernelGGL(ht_tail<R>, dim3(1, 1, Z), dim3(TAIL_THREADS), ht_tail_lds<R>(tail), st, pr);
+  hipLaunchKernelGGL(ht_tail<R>, dim3(1, 1, Z), dim3(TAIL_THREADS), 0, st, pr);
   MMF_LAUNCH_CHECK();
   return MMF_OK;
 }

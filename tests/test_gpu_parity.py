@@ -513,3 +513,22 @@ def test_refined_ladder_medium_against_oracle():
     ep = np.abs(out["P"].cpu().numpy() - oracle.avg_prob(p, Phio)).max()
     log(f"refined ladder M=3528: eps {ew:.2e} U {eu:.2e} P {ep:.2e}")
     assert ew <= 1e-9 and eu <= 1e-9
+
+
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 33, 65, 80, 81, 96, 97, 112, 127, 128, 129, 160, 161])
+def test_reduction_tail_orders(n):
+    """Orders around the 16-, 32- and 64-row edges of the one-workgroup tail of
+    the reduction and around its largest order: both precisions against the
+    definition (complex64: the reduction's backward error bound n eps32)."""
+    torch, mmf = require_gpu()
+    H = gue(np.random.default_rng(4000 + n), n, 1.0)
+    nrm = np.linalg.norm(H)
+    wo = np.linalg.eigvalsh(H)
+    for prec, tol in ((mmf.MMF_C128, 1e-12), (mmf.MMF_C64_RAW, 1.2e-7 * max(n, 32))):
+        w, Pt, info = mmf.eigh(to_dev_cm(torch, H), prec)
+        torch.cuda.synchronize()
+        assert int(info.item()) == 0
+        w, Phi = w.cpu().numpy(), from_dev_cm(Pt)
+        assert np.abs(w - wo).max() <= tol * nrm
+        assert np.linalg.norm(H @ Phi - Phi * w) <= tol * nrm
+        assert np.abs(Phi.conj().T @ Phi - np.eye(n)).max() <= tol
