@@ -210,7 +210,7 @@ int mmf_eigh_ex(int64_t M, mmf_z *A, int64_t lda, double *w, int prec, const mmf
                 void *work, size_t work_bytes, int32_t *dev_info, void *stream);
 
 /* Order from which mmf_eigh and mmf_eigh_window take the two-stage reduction
- * (default 5888, the measured crossover; the environment variable
+ * (default 6400, the measured crossover; the environment variable
  * MMF_EIGH_TWO_STAGE_MIN, read at every call, overrides it and also the
  * eigenvalue-only thresholds of mmf_eigvalsh_batched).  Query the workspace
  * size and call the solver under the same setting.  Host-only, never fails. */
@@ -336,8 +336,8 @@ int mmf_eigvalsh_batched_workspace(int64_t count, const int64_t *n, int prec, si
  * the grouped Householder reduction (complex128, or complex64 for
  * MMF_C64_RAW, from a complex64 copy; A[c] then stays intact; complex128
  * problems take the grouped two-stage reduction, dense -> band ->
- * tridiagonal, from order 4608 up, or from 1280 up when the call holds at
- * least 8 problems of order >= 1280), and all
+ * tridiagonal, from order 5248 up, or from 1920 up when the call holds at
+ * least 8 problems of order >= 1920), and all
  * eigenvalues are found by bisection on Sturm counts in FP64; w[c] receives
  * them in ascending order.  Arguments, ownership and errors as for
  * mmf_eigh_batched (-6: prec not MMF_C128 / MMF_C64_RAW); dev_info[c] is set

@@ -14,13 +14,15 @@ constexpr int BT2_G = 64;         // sweeps per block of the second back-transfo
 // one-stage reduction streams the whole trailing matrix from HBM once per
 // column, the two-stage one runs almost all of its reduction flops on the
 // matrix cores but adds 2 n sequential chase steps and (with eigenvectors) a
-// second back-transformation.  Measured crossovers on MI355X: full
-// eigensolve ~5.9k; eigenvalues only ~4.6k for one matrix, ~1.2k for a batch
-// of 8 (the chase steps of all problems share each launch).  The environment
-// variable MMF_EIGH_TWO_STAGE_MIN overrides every default.
-constexpr int64_t TWO_STAGE_MIN_DEFAULT = 5888;
-constexpr int64_t EV_TWO_STAGE_MIN_ONE = 4608;     // eigenvalues only, few problems
-constexpr int64_t EV_TWO_STAGE_MIN_BATCH = 1280;   // eigenvalues only, >= EV_TWO_STAGE_BATCH such problems
+// second back-transformation.  Measured on MI355X, one-stage against two-stage
+// in ms: full eigensolve 224 / 235 at order 6144, 339 / 310 at 7168;
+// eigenvalues of one matrix 138 / 142 at 5120, 203 / 177 at 6144, of 8
+// matrices (the chase steps of all share each launch) 37.0 / 42.5 at 1536,
+// 63.7 / 60.9 at 2048.  The environment variable MMF_EIGH_TWO_STAGE_MIN
+// overrides every default.
+constexpr int64_t TWO_STAGE_MIN_DEFAULT = 6400;
+constexpr int64_t EV_TWO_STAGE_MIN_ONE = 5248;     // eigenvalues only, few problems
+constexpr int64_t EV_TWO_STAGE_MIN_BATCH = 1920;   // eigenvalues only, >= EV_TWO_STAGE_BATCH such problems
 constexpr int64_t EV_TWO_STAGE_BATCH = 8;
 inline int64_t two_stage_env() {
   const char *s = getenv("MMF_EIGH_TWO_STAGE_MIN");
