@@ -199,6 +199,28 @@ def test_stedc_leaf_and_chunk_edges(n, scale):
     assert np.abs(Z.T @ Z - np.eye(n)).max() <= 20 * n * np.finfo(float).eps
 
 
+@pytest.mark.parametrize("kind", ["random", "graded", "clustered"])
+def test_secular_steps_bounded(kind):
+    """Every root of the secular equation within 24 steps (the mean is 3; a
+    root approached from one side needs no halvings of its bracket)."""
+    torch, mmf = require_gpu()
+    n = 300
+    rng = np.random.default_rng(77)
+    Q, _ = np.linalg.qr(rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n)))
+    lam = {"random": rng.normal(size=n), "graded": 10.0 ** rng.uniform(-10, 1, n),
+           "clustered": np.round(rng.normal(size=n)) + 1e-7 * rng.normal(size=n)}[kind]
+    H = (Q * lam) @ Q.conj().T
+    H = (H + H.conj().T) / 2
+    w, Pt, info = mmf.eigh(to_dev_cm(torch, H), limits={"secular_max_iters": 24})
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    w, Phi = w.cpu().numpy(), from_dev_cm(Pt)
+    nrm = np.linalg.norm(H)
+    assert np.abs(w - np.linalg.eigvalsh(H)).max() <= 1e-12 * nrm
+    assert np.linalg.norm(H @ Phi - Phi * w) <= 1e-12 * nrm
+    assert np.abs(Phi.conj().T @ Phi - np.eye(n)).max() <= 1e-12
+
+
 @pytest.mark.parametrize("kind", ["glued", "constant", "wilkinson", "zero_offdiag", "floquet", "glued_2000",
                                   "mixed_2000"])
 def test_stedc_structured(kind):
