@@ -559,13 +559,14 @@ __global__ void __launch_bounds__(256) dc_gather(const DcProb *pr, int lev, int6
 // ------------------------------------------------------------------ merge: secular equation
 // One wavefront per root k of f(x) = 1 + rho sum_i z_i^2/(d_i - x): rational
 // interpolation with the poles beside the root exact, from the root of the
-// two poles and of the rest of f at the middle of the interval.  A step that
-// comes from one side leaves the bracket wide, so the bracket is halved only
-// when in three steps neither it shrank to half nor f to a tenth.
+// two poles and of the rest of f at the middle of the interval.  Where three
+// steps did not bring f to a tenth (clustered poles on one side: the model's
+// steps only halve the distance) the next one divides the bracket, by orders of
+// magnitude: the geometric mean, or a thousandth while one end is the pole.
 // Bound: the longest chain of steps of any root.  Starting in the middle and
-// halving whenever the bracket had not halved, single roots took 20 to 30 steps
-// (half of them back from the halvings) where the mean is 5, now at most
-// about 10 with a mean of 3: 10 us a merge at order 82, 14 at 450, 24 at 1715,
+// halving whenever the bracket had not halved (which it does not where the steps
+// come from one side), single roots took 20 to 30 steps where the mean is 5, now
+// 7 to 11, at most about 20, with a mean of 3 to 4: 10 us a merge at order 82, 14 at 450, 24 at 1715,
 // against 24, 36 and 56.
 __global__ void __launch_bounds__(256) dc_secular(const DcProb *pr, int lev) {
   const DcProb &P = pr[blockIdx.z];
@@ -629,7 +630,7 @@ __global__ void __launch_bounds__(256) dc_secular(const DcProb *pr, int lev) {
     return x2 > lo && x2 < hi ? x2 : 0.5 * (lo + hi);
   };
   double tau = k < K - 1 ? rational(c0, rh * z[k] * z[k], rh * z[k + 1] * z[k + 1]) : 0.5 * (lo + hi);
-  double lastw = hi - lo, lastf = INFINITY;
+  double lastf = INFINITY;
   bool conv = false;
   for (int it = 0; it < P.sec_max; ++it) {
     double ps = 0.0, ph = 0.0, dps = 0.0, dph = 0.0;
@@ -660,10 +661,12 @@ __global__ void __launch_bounds__(256) dc_secular(const DcProb *pr, int lev) {
       xn = (c != 0.0) ? pk + b1 / c : 0.5 * (lo + hi);
       if (!(xn > lo && xn < hi)) xn = 0.5 * (lo + hi);
     }
-    const double wdt = hi - lo;
     if (it % 3 == 2) {
-      if (wdt > 0.5 * lastw && fabs(f) > 0.1 * lastf) xn = 0.5 * (lo + hi);
-      lastw = wdt;
+      if (fabs(f) > 0.1 * lastf) {
+        const double near = fmin(fabs(lo), fabs(hi)), far = fmax(fabs(lo), fabs(hi));   // from the pole d[o]
+        const double g = near == 0.0 ? 1e-3 * far : (far > 4.0 * near ? sqrt(near * far) : 0.5 * (near + far));
+        xn = hi > 0.0 ? g : -g;
+      }
       lastf = fabs(f);
     }
     tau = xn;
