@@ -271,15 +271,13 @@ __global__ void __launch_bounds__(64) dc_leaf(const DcProb *pr) {
 }
 
 // ------------------------------------------------------------------ merge: prepare
-__global__ void dc_prep(const DcProb *pr, int lev) {
-  const DcProb &P = pr[blockIdx.z];
-  if (lev > P.h || (int64_t)blockIdx.y >= (P.L >> lev)) return;
+__device__ void dc_sort(const DcProb &P, int lev, int64_t bx) {
   const int64_t n = P.n, L = P.L, ldz = P.ldz;
   const double *e = P.e, *lam = P.w.lam, *Z = P.Z;
   double *ds = P.w.ds, *zs = P.w.zs, *rho = P.w.rho;
   int32_t *src = P.w.src;
   const MergeGeom q = dc_geom(n, L, lev, blockIdx.y);
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t j = bx * blockDim.x + threadIdx.x;
   if (j >= q.m) return;
   const double ek = e[q.mid - 1];
   const double sg = ek >= 0.0 ? 1.0 : -1.0;
@@ -310,22 +308,31 @@ __global__ void dc_prep(const DcProb *pr, int lev) {
   if (j == 0) rho[q.s] = 2.0 * fabs(ek);
 }
 
-// Off-diagonal blocks of the merged block start as exact zeros.
-// grid: x = row block, y = chunk of 64 columns, z = merge + Gmax * problem
-__global__ void dc_zero_off(const DcProb *pr, int lev, int64_t Gmax) {
-  const DcProb &P = pr[blockIdx.z / Gmax];
-  const int64_t g = blockIdx.z % Gmax;
-  if (lev > P.h || g >= (P.L >> lev)) return;
-  const MergeGeom q = dc_geom(P.n, P.L, lev, g);
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Off-diagonal blocks of the merged block start as exact zeros: row block rb,
+// chunk ch of 64 columns.
+__device__ void dc_zero_off(const DcProb &P, int lev, int64_t rb, int64_t ch) {
+  const MergeGeom q = dc_geom(P.n, P.L, lev, blockIdx.y);
+  const int64_t r = rb * blockDim.x + threadIdx.x;
   if (r >= q.m) return;
   const bool rl = r < q.n1;
-  const int64_t c0 = (int64_t)blockIdx.y * 64;
+  const int64_t c0 = ch * 64;
   const int64_t c1 = (c0 + 64 < q.m) ? c0 + 64 : q.m;
   for (int64_t c = c0; c < c1; ++c) {
     const bool cl = c < q.n1;
     if (rl != cl) P.Z[(q.s + r) + (q.s + c) * P.ldz] = 0.0;
   }
+}
+
+// The two together: nrow blocks of the sorted union, then the zero blocks.
+// (Steps of a merge that do not need one another share a launch: seven launches
+// a level instead of eleven, each as long as its longer step: whole solves
+// 0.675 -> 0.619 ms at order 82, 5.04 -> 4.88 at 450, 21.9 -> 21.6 at 1715.)
+__global__ void __launch_bounds__(256) dc_prep(const DcProb *pr, int lev, int nrow) {
+  const DcProb &P = pr[blockIdx.z];
+  if (lev > P.h || (int64_t)blockIdx.y >= (P.L >> lev)) return;
+  const int64_t x = (int64_t)blockIdx.x - nrow;
+  if (x < 0) dc_sort(P, lev, blockIdx.x);
+  else dc_zero_off(P, lev, x % nrow, x / nrow);
 }
 
 // ------------------------------------------------------------------ merge: deflation scan
@@ -528,16 +535,14 @@ __global__ void dc_rotate(const DcProb *pr, int lev) {
 // row.  Chunks of 256 columns with the look-up in the copy loop took 131 us a
 // level at order 450 (403 at 12816), this form 19 (154).
 constexpr int DC_GCOLS = 64;
-__global__ void __launch_bounds__(256) dc_gather(const DcProb *pr, int lev, int64_t nch) {
+__device__ void dc_gather(const DcProb &P, int lev, int64_t rb, int64_t ch) {
   __shared__ int32_t cfrom[DC_GCOLS], cto[DC_GCOLS];
-  const DcProb &P = pr[blockIdx.z];
-  const int64_t g = blockIdx.y / nch, ch = blockIdx.y % nch;
-  if (lev > P.h || g >= (P.L >> lev)) return;
+  const int64_t g = blockIdx.y;
   const int64_t n = P.n, ldz = P.ldz;
   const int32_t *src = P.w.src, *ndidx = P.w.ndidx, *dfidx = P.w.dfidx, *perm = P.w.perm;
   const int32_t *cnt = P.w.cnt;
   const MergeGeom q = dc_geom(n, P.L, lev, g);
-  const int64_t r0 = (int64_t)blockIdx.x * blockDim.x, o0 = ch * DC_GCOLS;
+  const int64_t r0 = rb * blockDim.x, o0 = ch * DC_GCOLS;
   if (r0 >= q.m || o0 >= q.m) return;
   const int64_t s = q.s;
   const int32_t K = cnt[DC_CNT * g];
@@ -568,10 +573,8 @@ __global__ void __launch_bounds__(256) dc_gather(const DcProb *pr, int lev, int6
 // come from one side), single roots took 20 to 30 steps where the mean is 5, now
 // 7 to 11, at most about 20, with a mean of 3 to 4: 10 us a merge at order 82, 14 at 450, 24 at 1715,
 // against 24, 36 and 56.
-__global__ void __launch_bounds__(256) dc_secular(const DcProb *pr, int lev) {
-  const DcProb &P = pr[blockIdx.z];
+__device__ void dc_roots(const DcProb &P, int lev) {
   const int64_t g = blockIdx.y;
-  if (lev > P.h || g >= (P.L >> lev)) return;
   const double *dn = P.w.dn, *zn = P.w.zn, *rho = P.w.rho;
   const int32_t *cnt = P.w.cnt;
   int32_t *lamo = P.w.lamo, *info = P.info;
@@ -678,12 +681,19 @@ __global__ void __launch_bounds__(256) dc_secular(const DcProb *pr, int lev) {
   }
 }
 
+// nroot workgroups of roots, then the gathered columns (nrow row blocks of each chunk).
+__global__ void __launch_bounds__(256) dc_secular(const DcProb *pr, int lev, int nroot, int nrow) {
+  const DcProb &P = pr[blockIdx.z];
+  if (lev > P.h || (int64_t)blockIdx.y >= (P.L >> lev)) return;
+  const int64_t x = (int64_t)blockIdx.x - nroot;
+  if (x < 0) dc_roots(P, lev);
+  else dc_gather(P, lev, x % nrow, x / nrow);
+}
+
 // zhat_i^2 = (x_{K-1} - d_i)/rho * prod_{j<i} (x_j - d_i)/(d_j - d_i)
 //                                 * prod_{i<=j<K-1} (x_j - d_i)/(d_{j+1} - d_i)
-__global__ void __launch_bounds__(256) dc_lowner(const DcProb *pr, int lev) {
-  const DcProb &P = pr[blockIdx.z];
+__device__ void dc_zhat(const DcProb &P, int lev) {
   const int64_t g = blockIdx.y;
-  if (lev > P.h || g >= (P.L >> lev)) return;
   const double *dn = P.w.dn, *zn = P.w.zn, *rho = P.w.rho, *lamt = P.w.lamt;
   const int32_t *cnt = P.w.cnt, *lamo = P.w.lamo;
   double *zhat = P.w.zhat;
@@ -753,18 +763,16 @@ __global__ void __launch_bounds__(256) dc_vectors(const DcProb *pr, int lev) {
 // Final ascending position of every eigenvalue of the merge (roots first in
 // the tie order, then deflated values by index), eigenvalue output and the
 // destination column of every T1 column.
-__global__ void __launch_bounds__(256) dc_final_pos(const DcProb *pr, int lev) {
+__device__ void dc_final_pos(const DcProb &P, int lev, int64_t bx) {
   __shared__ double vals[256];
-  const DcProb &P = pr[blockIdx.z];
   const int64_t g = blockIdx.y;
-  if (lev > P.h || g >= (P.L >> lev)) return;
   const double *dn = P.w.dn, *lamt = P.w.lamt, *ddef = P.w.ddef;
   const int32_t *cnt = P.w.cnt, *lamo = P.w.lamo;
   double *lam = P.w.lam;
   int32_t *colmap = P.w.colmap;
   const MergeGeom q = dc_geom(P.n, P.L, lev, g);
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if ((int64_t)blockIdx.x * blockDim.x >= q.m) return;
+  const int64_t e = bx * blockDim.x + threadIdx.x;
+  if (bx * blockDim.x >= q.m) return;
   const int64_t s = q.s;
   const int K = cnt[DC_CNT * g];
   auto val = [&](int64_t x) -> double {
@@ -793,18 +801,50 @@ __global__ void __launch_bounds__(256) dc_final_pos(const DcProb *pr, int lev) {
   colmap[s + e] = (int32_t)(s + pos);
 }
 
-__global__ void __launch_bounds__(GEMM_THREADS, 2) dc_gemm(const DcProb *pr, int lev, int64_t Gmax) {
+// nroot workgroups of weights, then the positions.
+__global__ void __launch_bounds__(256) dc_lowner(const DcProb *pr, int lev, int nroot) {
+  const DcProb &P = pr[blockIdx.z];
+  if (lev > P.h || (int64_t)blockIdx.y >= (P.L >> lev)) return;
+  const int64_t x = (int64_t)blockIdx.x - nroot;
+  if (x < 0) dc_zhat(P, lev);
+  else dc_final_pos(P, lev, x);
+}
+
+// Deflated columns K + 64 ch .. to their final positions, thread = row.
+__device__ void dc_copy_def(const DcProb &P, int lev, int64_t rb, int64_t ch) {
+  const int64_t g = blockIdx.y;
+  const int64_t n = P.n, ldz = P.ldz;
+  const int32_t *cnt = P.w.cnt, *colmap = P.w.colmap;
+  const double *T1 = P.w.T1;
+  double *Z = P.Z;
+  const MergeGeom q = dc_geom(n, P.L, lev, g);
+  const int64_t r = rb * blockDim.x + threadIdx.x;
+  const int64_t k0 = cnt[DC_CNT * g] + ch * DC_GCOLS;
+  if (r >= q.m) return;
+  const int64_t k1 = k0 + DC_GCOLS < q.m ? k0 + DC_GCOLS : q.m;
+#pragma unroll 8
+  for (int64_t k = k0; k < k1; ++k)
+    Z[(q.s + r) + (int64_t)colmap[q.s + k] * ldz] = T1[(q.s + r) + (q.s + k) * n];
+}
+
+__global__ void __launch_bounds__(GEMM_THREADS, 2) dc_gemm(const DcProb *pr, int lev, int tx, int tiles, int nrow) {
   __shared__ double lds[GEMM_LDS_DOUBLES];
-  const DcProb &P = pr[blockIdx.z / Gmax];
-  const int64_t g = blockIdx.z % Gmax;
+  static_assert(GEMM_THREADS == 256, "shared with the row copies");
+  const DcProb &P = pr[blockIdx.z];
+  const int64_t g = blockIdx.y;
   if (lev > P.h || g >= (P.L >> lev)) return;
+  const int64_t x = (int64_t)blockIdx.x - tiles;
+  if (x >= 0) {
+    dc_copy_def(P, lev, x % nrow, x / nrow);
+    return;
+  }
   const int64_t n = P.n, ldz = P.ldz;
   const int32_t *cnt = P.w.cnt, *colmap = P.w.colmap;
   const double *T1 = P.w.T1, *T2 = P.w.T2;
   double *Z = P.Z;
   const MergeGeom q = dc_geom(n, P.L, lev, g);
   const int K = cnt[DC_CNT * g], c1 = cnt[DC_CNT * g + 3], c12 = cnt[DC_CNT * g + 4];
-  const int64_t m0 = (int64_t)blockIdx.x * GT_M, n0 = (int64_t)blockIdx.y * GT_N;
+  const int64_t m0 = (int64_t)(blockIdx.x % tx) * GT_M, n0 = (int64_t)(blockIdx.x / tx) * GT_N;
   if (m0 >= q.m || n0 >= K) return;
   // no column of this tile wanted (a window: the top merge is three quarters of
   // the products, 52 ms of 259 at order 12816, of which its 16 states need 16)
@@ -821,26 +861,6 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) dc_gemm(const DcProb *pr, int
                          1.0, 0.0, 0.0, 0.0);
   a.colmap = colmap + q.s;
   gemm_tile<false, A_N, B_N>(a, m0, n0, lds);
-}
-
-// Deflated columns K + 64 ch .. of merge g (y = g * nch + ch) to their final
-// positions, thread = row.
-__global__ void __launch_bounds__(256) dc_copy_def(const DcProb *pr, int lev, int64_t nch) {
-  const DcProb &P = pr[blockIdx.z];
-  const int64_t g = blockIdx.y / nch, ch = blockIdx.y % nch;
-  if (lev > P.h || g >= (P.L >> lev)) return;
-  const int64_t n = P.n, ldz = P.ldz;
-  const int32_t *cnt = P.w.cnt, *colmap = P.w.colmap;
-  const double *T1 = P.w.T1;
-  double *Z = P.Z;
-  const MergeGeom q = dc_geom(n, P.L, lev, g);
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t k0 = cnt[DC_CNT * g] + ch * DC_GCOLS;
-  if (r >= q.m) return;
-  const int64_t k1 = k0 + DC_GCOLS < q.m ? k0 + DC_GCOLS : q.m;
-#pragma unroll 8
-  for (int64_t k = k0; k < k1; ++k)
-    Z[(q.s + r) + (int64_t)colmap[q.s + k] * ldz] = T1[(q.s + r) + (q.s + k) * n];
 }
 
 __global__ void dc_copy_out(const DcProb *pr) {
@@ -906,32 +926,22 @@ int stedc_grouped(const DcProb *pr, const int64_t *nh, int64_t count, hipStream_
       }
     }
     if (Gmax == 0) continue;
-    const dim3 rows(cdiv(maxm, 256), (unsigned)Gmax, Z);
-    hipLaunchKernelGGL(dc_prep, rows, dim3(256), 0, st, pr, lev);
-    MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(dc_zero_off, dim3(cdiv(maxm, 256), cdiv(maxm, 64), (unsigned)(Gmax * count)), dim3(256),
-                       0, st, pr, lev, Gmax);
+    const unsigned nrow = cdiv(maxm, 256), nch = cdiv(maxm, DC_GCOLS), nroot = cdiv(maxm, 4);
+    const unsigned tx = cdiv(maxm, GT_M), tiles = tx * cdiv(maxm, GT_N), G = (unsigned)Gmax;
+    hipLaunchKernelGGL(dc_prep, dim3(nrow + nrow * cdiv(maxm, 64), G, Z), dim3(256), 0, st, pr, lev, (int)nrow);
     MMF_LAUNCH_CHECK();
     hipLaunchKernelGGL(dc_deflate, dim3((unsigned)(Gmax * count)), dim3(64), 0, st, pr, lev, Gmax);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(dc_rotate, rows, dim3(256), 0, st, pr, lev);
+    hipLaunchKernelGGL(dc_rotate, dim3(nrow, G, Z), dim3(256), 0, st, pr, lev);
     MMF_LAUNCH_CHECK();
-    const int64_t nch = cdiv(maxm, DC_GCOLS);
-    hipLaunchKernelGGL(dc_gather, dim3(cdiv(maxm, 256), (unsigned)(Gmax * nch), Z), dim3(256), 0, st, pr, lev, nch);
+    hipLaunchKernelGGL(dc_secular, dim3(nroot + nrow * nch, G, Z), dim3(256), 0, st, pr, lev, (int)nroot, (int)nrow);
     MMF_LAUNCH_CHECK();
-    const dim3 roots(cdiv(maxm, 4), (unsigned)Gmax, Z);
-    hipLaunchKernelGGL(dc_secular, roots, dim3(256), 0, st, pr, lev);
+    hipLaunchKernelGGL(dc_lowner, dim3(nroot + nrow, G, Z), dim3(256), 0, st, pr, lev, (int)nroot);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(dc_lowner, roots, dim3(256), 0, st, pr, lev);
+    hipLaunchKernelGGL(dc_vectors, dim3((unsigned)maxm, G, Z), dim3(256), 0, st, pr, lev);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(dc_vectors, dim3((unsigned)maxm, (unsigned)Gmax, Z), dim3(256), 0, st, pr, lev);
-    MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(dc_final_pos, rows, dim3(256), 0, st, pr, lev);
-    MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(dc_gemm, dim3(cdiv(maxm, GT_M), cdiv(maxm, GT_N), (unsigned)(Gmax * count)),
-                       dim3(GEMM_THREADS), 0, st, pr, lev, Gmax);
-    MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(dc_copy_def, dim3(cdiv(maxm, 256), (unsigned)(Gmax * nch), Z), dim3(256), 0, st, pr, lev, nch);
+    hipLaunchKernelGGL(dc_gemm, dim3(tiles + nrow * nch, G, Z), dim3(GEMM_THREADS), 0, st, pr, lev, (int)tx,
+                       (int)tiles, (int)nrow);
     MMF_LAUNCH_CHECK();
   }
   hipLaunchKernelGGL(dc_copy_out, dim3(cdiv(nmax, 256), 1, Z), dim3(256), 0, st, pr);
