@@ -162,6 +162,9 @@ __device__ __forceinline__ double lane_get(double v, int u) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), u),
                           __builtin_amdgcn_readlane(__double2loint(v), u));
 }
+__device__ __forceinline__ float lane_get(float v, int u) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), u));
+}
 __device__ __forceinline__ cd lane_get(cd v, int u) { return cmake(lane_get(v.re, u), lane_get(v.im, u)); }
 
 // Folds of two values: the lower (fold32: lanes < 32, fold16: even rows of 16)
@@ -177,9 +180,17 @@ __device__ __forceinline__ double lanes_fold16(double a, double b) {
   const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
   return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
 }
+__device__ __forceinline__ float lanes_fold32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float lanes_fold16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 #else
-__device__ inline double lanes_fold32(double a, double b) { return a + b; }
-__device__ inline double lanes_fold16(double a, double b) { return a + b; }
+template <typename R> __device__ inline R lanes_fold32(R a, R b) { return a + b; }
+template <typename R> __device__ inline R lanes_fold16(R a, R b) { return a + b; }
 #endif
 
 // Wavefront-wide sum (all 64 lanes active), the same value in every lane.

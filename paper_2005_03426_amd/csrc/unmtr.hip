@@ -18,6 +18,7 @@
 // and reduced in fixed order; the rank-NB update is a plain MFMA GEMM
 // with the left factor V T formed per block (a 128-wide GEMM).  8 n^3 real
 // flops in total, plus 8 n^2 128 for the V T products.
+// Small orders take no blocks (bt_direct).
 // Templated over the scalar type (complex128, or complex64 with FP32
 // accumulation for the precision layer; Z is read in FP64 and rounded).
 // Grouped: every kernel reads its problem from a device table (BtProb) at
@@ -39,6 +40,15 @@ namespace mmf {
 __host__ __device__ inline int64_t bt_kchunk(int64_t n) {
   return n <= 1024 ? 128 : (n <= 2048 ? 256 : (n <= 4096 ? 512 : (n <= 8192 ? 1024 : 2048)));
 }
+
+// Orders up to BT_DIRECT apply their reflectors two by two to columns in
+// registers (bt_direct), larger ones in blocks.  Whole eigensolves, blocked and
+// direct, in ms: one matrix 0.54 / 0.40 at order 82, 0.77 / 0.63 at 128, 1.49 /
+// 1.33 at 192, 2.19 / 2.02 at 256; 64 matrices of order 200 3.69 / 3.55, but 100
+// of order 256 6.35 / 6.48 and 48 of order 450 12.7 / 14.9.
+constexpr int64_t BT_DIRECT = 224;
+template <int NB>
+__host__ __device__ inline bool bt_is_direct(int64_t n) { return NB == 128 && n <= BT_DIRECT; }
 
 template <typename R>
 struct BtWs {
@@ -87,7 +97,7 @@ size_t unmtr_ws_bytes_c64(int64_t n) { return unmtr_ws<float, BT_NB>(n, nullptr)
 // One problem of a grouped back-transformation.
 template <typename R>
 struct BtProb {
-  int64_t n, nc, ldv, ldz, ldphi, nblk, nsplit;     // nc: columns of Z / Phi (n for a full back-transform)
+  int64_t n, nc, ldv, ldz, ldphi, nblk, nsplit;     // nc: columns of Z / Phi (n for a full back-transform); nblk 0: direct
   const cx<R> *V, *tau;
   const double *Z;
   cx<R> *Phi;
@@ -305,12 +315,107 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) bt_update(const BtProb<R> *pr
   gemm_tile_t<R, true, A_N, B_N>(u, m0, n0, lds);
 }
 
+// Clean copy of the reflectors of a direct problem (Phi may alias V): column j
+// (zero to row j, one at row j + 1, zeros to the next multiple of 64 rows) at
+// Vp + (j + 1) ld after a column of zeros; the columns run on into VpT (64
+// ceil(n / 64) n entries of the blocked form's 256 (n - 1) and more).  The
+// reflectors are paired from the last one down, (j - 1, j) for pair
+// blockIdx.x = (n - 2 - j) / 2, and Tm[pair] = v_{j-1}^H v_j.
+__host__ __device__ inline int bt_dld(int64_t n) { return (int)((n + 63) & ~(int64_t)63); }
+template <typename R, int NB>
+__global__ void __launch_bounds__(64) bt_dpack(const BtProb<R> *pr) {
+  const BtProb<R> &P = pr[blockIdx.z];
+  const int64_t n = P.n;
+  if (P.nblk > 0) return;
+  const int64_t j2 = n - 2 - 2 * (int64_t)blockIdx.x, j1 = j2 - 1;
+  if (j2 < -1) return;
+  const int ld = bt_dld(n);
+  cx<R> g = cmk<R>(0, 0);
+  for (int r = threadIdx.x; r < ld; r += 64) {
+    cx<R> v1 = cmk<R>(j1 >= 0 && r == j1 + 1, 0), v2 = cmk<R>(j2 >= 0 && r == j2 + 1, 0);
+    if (j2 >= 0 && r > j2 + 1 && r < n) v2 = P.V[r + j2 * P.ldv];
+    if (j1 >= 0 && r > j1 + 1 && r < n) v1 = P.V[r + j1 * P.ldv];
+    P.Vp[r + (j2 + 1) * ld] = v2;
+    if (j1 >= -1) P.Vp[r + (j1 + 1) * ld] = v1;
+    g = cadd(g, cmulc(v1, v2));
+  }
+  const R re = wave_sum(g.re), im = wave_sum(g.im);
+  if (threadIdx.x == 0) P.Tm[blockIdx.x] = cmk<R>(re, im);
+}
+
+// Phi = H_0 H_1 ... H_{n-2} Z of a direct problem, one wavefront per column:
+// lane l holds rows l, l + 64, ..., two reflectors a pass from the last ones, (I - t1 v1 v1^H)(I - t2 v2 v2^H) z with v1^H of the second's
+// result from v1^H z, v2^H z and v1^H v2: one reduction across the lanes per
+// pass, the four sums together.  The next pair is loaded meanwhile.
+// Bound: the chain of (n - 1) / 2 passes, 27 us at order 82 where the blocked
+// form spends 165 in ten launches (40 of them on the T factor).  (Two and four
+// columns per wavefront, to read the reflectors less often: 1 and 4 % slower
+// single solves, batches the same.)
+template <typename R, int NB, int RPL>
+__global__ void __launch_bounds__(64) bt_direct(const BtProb<R> *pr) {
+  typedef cx<R> C;
+  const BtProb<R> &P = pr[blockIdx.z];
+  const int n = (int)P.n;
+  const int64_t col = blockIdx.x;
+  if (P.nblk > 0 || col >= P.nc) return;
+  const int lane = threadIdx.x, ld = bt_dld(n), chunks = ld / 64;
+  const MMF_GLOBAL C *V = (const MMF_GLOBAL C *)P.Vp + lane, *G = (const MMF_GLOBAL C *)P.Tm;
+  const MMF_GLOBAL C *tau = (const MMF_GLOBAL C *)P.tau;
+  C z[RPL], v[2][2][RPL];
+#pragma unroll
+  for (int k = 0; k < RPL; ++k) {
+    const int r = lane + 64 * k;
+    z[k] = cmk<R>(0, 0);
+    if (r < n) z[k].re = (R)P.Z[r + col * P.ldz];
+  }
+  // reflectors j - 1 and j (column 0 of the copy is zero: j = 0 has no partner)
+  auto load = [&](C (&w)[2][RPL], int j) {
+    const MMF_GLOBAL C *a = V + (int64_t)(j > 0 ? j : 0) * ld;
+    const int64_t next = j >= 0 ? ld : 0;
+#pragma unroll
+    for (int k = 0; k < RPL; ++k)
+      if (k < chunks) {                             // rows beyond a smaller problem of the launch stay zero
+        w[0][k] = gload(a + 64 * k);
+        w[1][k] = gload(a + next + 64 * k);
+      }
+  };
+  auto pass = [&](const C (&w)[2][RPL], C (&nx)[2][RPL], int j) {
+    const C t2 = gload(tau + j), t1 = gload(tau + (j > 0 ? j - 1 : 0)), g = gload(G + (n - 2 - j) / 2);
+    load(nx, j - 2);
+    C a1 = cmk<R>(0, 0), a2 = a1;
+#pragma unroll
+    for (int k = 0; k < RPL; ++k) {
+      a1 = cadd(a1, cmulc(w[0][k], z[k]));
+      a2 = cadd(a2, cmulc(w[1][k], z[k]));
+    }
+    const R s = row16_sum(lanes_fold16(lanes_fold32(a1.re, a1.im), lanes_fold32(a2.re, a2.im)));
+    a1 = cmk<R>(lane_get(s, 0), lane_get(s, 32));
+    a2 = cmk<R>(lane_get(s, 16), lane_get(s, 48));
+    const C s2 = cmul(t2, a2), s1 = cmul(t1, csub(a1, cmul(s2, g)));
+#pragma unroll
+    for (int k = 0; k < RPL; ++k) z[k] = csub(csub(z[k], cmul(s2, w[1][k])), cmul(s1, w[0][k]));
+  };
+#pragma unroll
+  for (int k = 0; k < RPL; ++k)
+    if (k >= chunks) v[0][0][k] = v[0][1][k] = v[1][0][k] = v[1][1][k] = cmk<R>(0, 0);
+  load(v[0], n - 2);
+  for (int j = n - 2; j >= 0; j -= 4) {
+    pass(v[0], v[1], j);
+    if (j >= 2) pass(v[1], v[0], j - 2);
+  }
+#pragma unroll
+  for (int k = 0; k < RPL; ++k) {
+    const int r = lane + 64 * k;
+    if (r < n) P.Phi[r + col * P.ldphi] = z[k];
+  }
+}
+
 // Phi = Z (complex); grid y walks 64-column chunks.  Without Z, Phi already
 // holds the matrix to transform.
 template <typename R, int NB>
 __global__ void bt_init_phi(const BtProb<R> *pr) {
   const BtProb<R> &P = pr[blockIdx.z];
-  if (!P.Z) return;
+  if (!P.Z || bt_is_direct<NB>(P.n)) return;
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n = P.n;
   if (r >= n) return;
@@ -334,12 +439,27 @@ int unmtr_grouped(const BtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
     }
     return MMF_OK;
   }
-  int64_t nmax = 0;
-  for (int64_t c = 0; c < count; ++c) nmax = nh[c] > nmax ? nh[c] : nmax;
+  int64_t nmax = 0, dmax = 0;                         // largest blocked and direct orders
+  for (int64_t c = 0; c < count; ++c) {
+    int64_t &m = bt_is_direct<NB>(nh[c]) ? dmax : nmax;
+    m = nh[c] > m ? nh[c] : m;
+  }
+  if (ncmax == 0) return MMF_OK;
+  const unsigned Z = (unsigned)count;
+  if constexpr (NB == BT_NB) {
+    if (dmax > 0) {
+      if (dmax > 1) {
+        hipLaunchKernelGGL((bt_dpack<R, NB>), dim3((unsigned)((dmax + 1) / 2), 1, Z), dim3(64), 0, st, pr);
+        MMF_LAUNCH_CHECK();
+      }
+      const dim3 grid((unsigned)(ncmax >= 0 ? ncmax : dmax), 1, Z);
+      if (dmax <= 128) hipLaunchKernelGGL((bt_direct<R, NB, 2>), grid, dim3(64), 0, st, pr);
+      else hipLaunchKernelGGL((bt_direct<R, NB, 4>), grid, dim3(64), 0, st, pr);
+      MMF_LAUNCH_CHECK();
+    }
+  }
   if (nmax <= 0) return MMF_OK;
   const int64_t ncols = ncmax >= 0 ? ncmax : nmax;
-  if (ncols <= 0) return MMF_OK;
-  const unsigned Z = (unsigned)count;
   const int64_t nblk = nmax > 1 ? (nmax - 1 + NB - 1) / NB : 0;
   int64_t nsplit = 1;                                 // most slices of any problem
   for (int64_t c = 0; c < count; ++c) {
@@ -399,7 +519,8 @@ inline BtProb<R> bt_prob(int64_t n, const cx<R> *V, int64_t ldv, const cx<R> *ta
                          int64_t ldz, cx<R> *Phi, int64_t ldphi, void *ws, int64_t nc = -1) {
   const BtWs<R> w = unmtr_ws<R, NB>(n, ws, nc);
   BtProb<R> q;
-  q.n = n; q.nc = nc >= 0 ? nc : n; q.ldv = ldv; q.ldz = ldz; q.ldphi = ldphi; q.nblk = w.nblk; q.nsplit = w.nsplit;
+  q.n = n; q.nc = nc >= 0 ? nc : n; q.ldv = ldv; q.ldz = ldz; q.ldphi = ldphi; q.nsplit = w.nsplit;
+  q.nblk = bt_is_direct<NB>(n) ? 0 : w.nblk;
   q.V = V; q.tau = tau; q.Z = Z; q.Phi = Phi;
   q.Vp = w.Vp; q.VpT = w.VpT; q.Tm = w.Tm; q.Wpart = w.Wpart; q.W2 = w.W2; q.VT = w.VT; q.Gpart = w.Gpart;
   return q;

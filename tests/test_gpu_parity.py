@@ -554,3 +554,24 @@ def test_reduction_tail_orders(n):
         assert np.abs(w - wo).max() <= tol * nrm
         assert np.linalg.norm(H @ Phi - Phi * w) <= tol * nrm
         assert np.abs(Phi.conj().T @ Phi - np.eye(n)).max() <= tol
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 64, 65, 127, 128, 129, 192, 193, 223, 224, 225])
+def test_unmtr_direct_orders(n):
+    """Back-transformation around the 64-row edges of the direct form and its
+    largest order, odd and even reflector counts, Phi over the matrix that
+    held the reflectors, against the product of the reflectors in FP64."""
+    torch, mmf = require_gpu()
+    H = gue(np.random.default_rng(9100 + n), n, 1.0)
+    At = to_dev_cm(torch, H)
+    d, e, tau = mmf.hetrd(At)
+    torch.cuda.synchronize()
+    V, t = from_dev_cm(At), tau.cpu().numpy()
+    Z = np.linalg.qr(np.random.default_rng(n).normal(size=(n, n)))[0]
+    want = Z.astype(complex)
+    for j in range(n - 2, -1, -1):
+        v = np.concatenate([np.zeros(j + 1), [1.0], V[j + 2:, j]])
+        want -= t[j] * np.outer(v, v.conj() @ want)
+    got = from_dev_cm(mmf.unmtr(At, tau, to_dev_cm(torch, Z), out=At))
+    torch.cuda.synchronize()
+    assert np.abs(got - want).max() <= 20 * n * np.finfo(float).eps
