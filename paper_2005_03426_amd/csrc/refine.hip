@@ -174,36 +174,69 @@ __global__ void __launch_bounds__(256) rf_lambda(int64_t n, const cd *S, const c
   }
 }
 
-// Cluster scan (one thread): cid[i] = first index of i's run (consecutive
-// eigenvalues closer than delta); clist holds (start, size, offset of its Q
-// block) of every chunk of size >= 2 for the Rayleigh-Ritz rotation (runs cut
-// at start + off + k CL_MAX); ncl its count; *longrun = 1 when some run is
-// longer than a chunk (then pairs of one run are not all rotated together).
-// A non-finite residual, orthogonality or eigenvalue sets *bad and stops the
-// iteration.
-__global__ void rf_clusters(int64_t n, const double *lam, const double *colmax, int32_t *cid,
-                            int32_t *clist, int32_t *ncl, double *delta_out, double *msml,
-                            const int32_t *skip, int32_t *stop_next, int32_t *bad, int32_t *longrun, int off) {
-  if (threadIdx.x != 0 || blockIdx.x != 0 || *skip) return;
+// Inclusive scan of v over the RC_THREADS threads of the workgroup (sh: RC_THREADS / 64 entries).
+constexpr int RC_THREADS = 1024;
+template <typename T, typename Op>
+__device__ inline T rc_scan(T v, T *sh, Op op) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const T u = __shfl_up(v, o, 64);
+    if (lane >= o) v = op(u, v);
+  }
+  __syncthreads();
+  if (lane == 63) sh[wave] = v;
+  __syncthreads();
+  for (int w = wave - 1; w >= 0; --w) v = op(sh[w], v);
+  return v;
+}
+
+// Cluster scan (one workgroup): cid[i] = first index of i's run (consecutive
+// eigenvalues closer than delta), cend[i] the index behind it; clist holds
+// (start, size, offset of its Q block) of every chunk of size >= 2 for the
+// Rayleigh-Ritz rotation (runs cut at start + off + k CL_MAX), in order; ncl
+// its count; *longrun = 1 when some run is longer than a chunk (then pairs of
+// one run are not all rotated together).  A non-finite residual, orthogonality
+// or eigenvalue sets *bad and stops the iteration.
+// Scans over 1024 entries at a time; one thread walking the entries took 147
+// us at order 1352, twelve times a solve (20.8 ms, now 19.1), this form 17.
+__global__ void __launch_bounds__(RC_THREADS)
+rf_clusters(int64_t n, const double *lam, const double *colmax, int32_t *cid, int32_t *cend, int32_t *clist,
+            int32_t *ncl, double *delta_out, double *msml, const int32_t *skip, int32_t *stop_next, int32_t *bad,
+            int32_t *longrun, int off) {
+  __shared__ double sd[3][RC_THREADS / 64];
+  __shared__ int32_t si[RC_THREADS / 64];
+  __shared__ int32_t carry, carry2;
+  if (*skip) return;
+  const int tid = threadIdx.x;
   double ms = 0.0, ml = 1.0, mr = 0.0;
   bool finite = true;
-  for (int64_t j = 0; j < n; ++j) {
+  for (int64_t j = tid; j < n; j += RC_THREADS) {
     finite = finite && isfinite(colmax[j]) && isfinite(colmax[n + j]) && isfinite(lam[j]);
     ms = fmax(ms, colmax[j]);
     mr = fmax(mr, colmax[n + j]);
     ml = fmax(ml, fabs(lam[j]));
   }
-  *longrun = 0;
+  finite = __syncthreads_and(finite);
   if (!finite) {
-    *bad = 1;
-    *stop_next = 1;
-    *ncl = 0;
+    if (tid == 0) {
+      *longrun = 0;
+      *bad = 1;
+      *stop_next = 1;
+      *ncl = 0;
+    }
     return;
   }
-  if (ms <= CONV_TOL * ml && mr <= CONV_TOL_R) *stop_next = 1;     // this iteration's update is the last one
-  msml[0] = ms;
-  msml[1] = ml;
-  msml[2] = mr;
+  ms = wave_max(ms);
+  ml = wave_max(ml);
+  mr = wave_max(mr);
+  if ((tid & 63) == 0) { sd[0][tid >> 6] = ms; sd[1][tid >> 6] = ml; sd[2][tid >> 6] = mr; }
+  __syncthreads();
+  for (int w = 0; w < RC_THREADS / 64; ++w) {
+    ms = fmax(ms, sd[0][w]);
+    ml = fmax(ml, sd[1][w]);
+    mr = fmax(mr, sd[2][w]);
+  }
   // A first-order correction e_ij = (s_ij - lam_j g_ij) / (lam_j - lam_i)
   // carries the rounding error of s_ij, eta ~ eps max|lam| sqrt(n), divided
   // by the gap, and X (I + E) leaves |e|^2 in the orthogonality: pairs
@@ -211,33 +244,75 @@ __global__ void rf_clusters(int64_t n, const double *lam, const double *colmax, 
   // (Rayleigh-Ritz rotation) so that this term stays below the tolerance.
   const double eta = DBL_EPSILON * ml * sqrt((double)n);
   const double delta = fmax(CL_FACTOR * ms, eta * sqrt(REF_SAFETY / CONV_TOL_R));
-  *delta_out = delta;
-  int32_t nc = 0, qoff = 0, lr = 0;
-  int64_t start = 0;
-  for (int64_t i = 1; i <= n; ++i) {
-    if (i < n && fabs(lam[i] - lam[i - 1]) <= delta) continue;
-    // run [start, i): cid for the r_ij / 2 rule, chunks for the rotation
-    for (int64_t q = start; q < i; ++q) cid[q] = (int32_t)start;
-    if (i - start > CL_MAX) lr = 1;
-    int64_t c0 = start;
-    int64_t cut = (i - start > CL_MAX && off > 0) ? start + off : start + CL_MAX;
-    while (c0 < i) {
-      const int64_t c1 = cut < i ? cut : i;
-      const int32_t sz = (int32_t)(c1 - c0);
-      if (sz >= 2) {
-        clist[3 * nc] = (int32_t)c0;
-        clist[3 * nc + 1] = sz;
-        clist[3 * nc + 2] = qoff;
-        qoff += sz * sz;
-        ++nc;
-      }
-      c0 = c1;
-      cut = c1 + CL_MAX;
-    }
-    start = i;
+  if (tid == 0) {
+    if (ms <= CONV_TOL * ml && mr <= CONV_TOL_R) *stop_next = 1;   // this iteration's update is the last one
+    msml[0] = ms;
+    msml[1] = ml;
+    msml[2] = mr;
+    *delta_out = delta;
+    carry = 0;
   }
-  *ncl = nc;
-  *longrun = lr;
+  __syncthreads();
+  const auto starts = [&](int64_t i) { return i == 0 || i >= n || !(fabs(lam[i] - lam[i - 1]) <= delta); };
+  // first index of every run, ascending
+  const int64_t tiles = (n + RC_THREADS - 1) / RC_THREADS;
+  for (int64_t t = 0; t < tiles; ++t) {
+    const int64_t i = t * RC_THREADS + tid;
+    int32_t v = i < n && starts(i) ? (int32_t)i : 0;
+    v = rc_scan(v, si, [](int32_t a, int32_t b) { return a > b ? a : b; });
+    v = v > carry ? v : carry;
+    if (i < n) cid[i] = v;
+    __syncthreads();
+    if (tid == RC_THREADS - 1) carry = v;
+  }
+  // the index behind it, descending
+  __syncthreads();
+  if (tid == 0) carry = (int32_t)n;
+  __syncthreads();
+  for (int64_t t = tiles - 1; t >= 0; --t) {
+    const int64_t i = t * RC_THREADS + (RC_THREADS - 1 - tid);
+    int32_t v = i < n && starts(i + 1) ? (int32_t)(i + 1) : (int32_t)n;
+    v = rc_scan(v, si, [](int32_t a, int32_t b) { return a < b ? a : b; });
+    v = v < carry ? v : carry;
+    if (i < n) cend[i] = v;
+    __syncthreads();
+    if (tid == RC_THREADS - 1) carry = v;
+  }
+  __syncthreads();
+  if (tid == 0) carry = carry2 = 0;
+  __syncthreads();
+  // chunks in ascending order
+  bool lr = false;
+  for (int64_t t = 0; t < tiles; ++t) {
+    const int64_t i = t * RC_THREADS + tid;
+    int32_t sz = 0;
+    if (i < n) {
+      const int64_t st = cid[i], en = cend[i];
+      const bool cut = en - st > CL_MAX;
+      const int64_t first = st + (cut && off > 0 ? off : CL_MAX);  // end of the run's first chunk
+      lr = lr || cut;
+      if (i == st || (i >= first && (i - first) % CL_MAX == 0)) {
+        const int64_t c1 = i == st ? first : i + CL_MAX;
+        sz = (int32_t)((c1 < en ? c1 : en) - i);
+      }
+    }
+    const auto plus = [](int32_t a, int32_t b) { return a + b; };
+    const int32_t use = sz >= 2, area = use ? sz * sz : 0;
+    const int32_t nc = rc_scan(use, si, plus) + carry, qo = rc_scan(area, si, plus) + carry2;
+    if (use) {
+      clist[3 * (nc - 1)] = (int32_t)i;
+      clist[3 * (nc - 1) + 1] = sz;
+      clist[3 * (nc - 1) + 2] = qo - area;
+    }
+    __syncthreads();
+    if (tid == RC_THREADS - 1) { carry = nc; carry2 = qo; }
+    __syncthreads();
+  }
+  lr = __syncthreads_or(lr);
+  if (tid == 0) {
+    *ncl = carry;
+    *longrun = lr;
+  }
 }
 
 // F = I + E, written over S; emax_bits collects max |e_ij| outside clusters
@@ -572,7 +647,7 @@ static int c64_finish(int64_t n, cd *A, int64_t lda, double *w, bool refine, con
     MMF_LAUNCH_CHECK();
     hipLaunchKernelGGL(rf_lambda, dim3((unsigned)n), dim3(256), 0, st, n, S, G, ws.lam, ws.colmax, ws.skip);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rf_clusters, dim3(1), dim3(64), 0, st, n, ws.lam, ws.colmax, ws.cid, ws.clist,
+    hipLaunchKernelGGL(rf_clusters, dim3(1), dim3(RC_THREADS), 0, st, n, ws.lam, ws.colmax, ws.cid, ws.dest, ws.clist,
                        ws.ncl, ws.delta, ws.msml, ws.skip, ws.stop, ws.bad, ws.longrun,
                        (it & 1) ? CL_MAX / 2 : 0);
     MMF_LAUNCH_CHECK();
