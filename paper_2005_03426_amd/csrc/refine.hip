@@ -101,8 +101,16 @@ __global__ void rf_band(int64_t n, const cd *A, int64_t lda, int32_t *band) {
 }
 
 __global__ void rf_zero_int(int32_t *p) { if (threadIdx.x == 0) *p = 0; }
-// skip <- stop_next at the start of an iteration (both flags live on the device)
-__global__ void rf_latch(int32_t *skip, const int32_t *stop_next) { if (threadIdx.x == 0) *skip = *stop_next; }
+// S = X^H (A X) and G = X^H X (grid z), both on their lower triangle: one after
+// the other each leaves a CU at most one tile at order 1352, 316 us each; together 573.
+__global__ void __launch_bounds__(GEMM_THREADS, 2) rf_gram(GemmArgs s, GemmArgs g) {
+  __shared__ double lds[GEMM_LDS_DOUBLES];
+  if (*s.skip) return;
+  const GemmArgs &a = blockIdx.z == 0 ? s : g;
+  const int64_t m0 = (int64_t)blockIdx.x * GT_M, n0 = (int64_t)blockIdx.y * GT_N;
+  if (m0 + GT_M <= n0) return;
+  gemm_tile<true, A_C, B_N>(a, m0, n0, lds);
+}
 
 // S and G are computed on their lower triangle only (Hermitian products);
 // the upper triangle is filled with the conjugates and the diagonal made real.
@@ -119,8 +127,6 @@ __global__ void rf_mirror(int64_t n, cd *S, cd *G, const int32_t *skip) {
     G[r + c * n] = cconj(G[c + r * n]);
   }
 }
-
-__global__ void rf_zero_u64(unsigned long long *p) { if (threadIdx.x == 0) *p = 0ull; }
 
 // stop_next <- 1 when the next iteration is predicted converged (msml: this
 // iteration's max |s_ij - lam_j g_ij|, max(1, max |lam|), max |g_ij - delta_ij|).
@@ -197,17 +203,21 @@ __device__ inline T rc_scan(T v, T *sh, Op op) {
 // Rayleigh-Ritz rotation (runs cut at start + off + k CL_MAX), in order; ncl
 // its count; *longrun = 1 when some run is longer than a chunk (then pairs of
 // one run are not all rotated together).  A non-finite residual, orthogonality
-// or eigenvalue sets *bad and stops the iteration.
+// or eigenvalue sets *bad and stops the iteration.  *stop_next, the next
+// iteration's skip flag, is set in any case; *emax_bits is cleared for rf_build_f.
 // Scans over 1024 entries at a time; one thread walking the entries took 147
 // us at order 1352, twelve times a solve (20.8 ms, now 19.1), this form 17.
 __global__ void __launch_bounds__(RC_THREADS)
 rf_clusters(int64_t n, const double *lam, const double *colmax, int32_t *cid, int32_t *cend, int32_t *clist,
-            int32_t *ncl, double *delta_out, double *msml, const int32_t *skip, int32_t *stop_next, int32_t *bad,
-            int32_t *longrun, int off) {
+            int32_t *ncl, double *delta_out, double *msml, unsigned long long *emax_bits, const int32_t *skip,
+            int32_t *stop_next, int32_t *bad, int32_t *longrun, int off) {
   __shared__ double sd[3][RC_THREADS / 64];
   __shared__ int32_t si[RC_THREADS / 64];
   __shared__ int32_t carry, carry2;
-  if (*skip) return;
+  if (*skip) {
+    if (threadIdx.x == 0) *stop_next = 1;
+    return;
+  }
   const int tid = threadIdx.x;
   double ms = 0.0, ml = 1.0, mr = 0.0;
   bool finite = true;
@@ -245,7 +255,8 @@ rf_clusters(int64_t n, const double *lam, const double *colmax, int32_t *cid, in
   const double eta = DBL_EPSILON * ml * sqrt((double)n);
   const double delta = fmax(CL_FACTOR * ms, eta * sqrt(REF_SAFETY / CONV_TOL_R));
   if (tid == 0) {
-    if (ms <= CONV_TOL * ml && mr <= CONV_TOL_R) *stop_next = 1;   // this iteration's update is the last one
+    *stop_next = ms <= CONV_TOL * ml && mr <= CONV_TOL_R;          // this iteration's update is the last one
+    *emax_bits = 0ull;
     msml[0] = ms;
     msml[1] = ml;
     msml[2] = mr;
@@ -347,7 +358,10 @@ __global__ void __launch_bounds__(256) rf_build_f(int64_t n, cd *S, const cd *G,
   __syncthreads();
   if (threadIdx.x == 0) {
     e = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
-    atomicMax(emax_bits, (unsigned long long)__double_as_longlong(e));
+    // most workgroups are below the maximum so far (8112 atomics on one word: 97
+    // us at order 1352, now 39)
+    const unsigned long long b = (unsigned long long)__double_as_longlong(e);
+    if (b > *(volatile unsigned long long *)emax_bits) atomicMax(emax_bits, b);
   }
 }
 
@@ -413,13 +427,14 @@ __global__ void __launch_bounds__(256) rf_cluster_rr(int64_t n, const cd *S, con
   }
 }
 
-// F[:, C] <- F[:, C] Q_C for every chunk C: work items (64-row tile, chunk),
-// the tile and Q_C staged in LDS.
-__global__ void __launch_bounds__(256) rf_cluster_rotate(int64_t n, cd *F, const int32_t *clist,
+// F[:, C] <- F[:, C] Q_C for every chunk C of F = X, S, G (grid y): work items
+// (64-row tile, chunk), the tile and Q_C staged in LDS.
+__global__ void __launch_bounds__(256) rf_cluster_rotate(int64_t n, cd *X, cd *S, cd *G, const int32_t *clist,
                                                         const int32_t *ncl, const cd *Qbuf, const int32_t *skip) {
   __shared__ cd Ft[64][CL_MAX + 1];
   __shared__ cd Qs[CL_MAX][CL_MAX + 1];
   if (*skip) return;
+  cd *F = blockIdx.y == 0 ? X : (blockIdx.y == 1 ? S : G);
   const int tid = threadIdx.x;
   const int64_t ntile = (n + 63) / 64;
   const int64_t items = (int64_t)(*ncl) * ntile;
@@ -443,13 +458,14 @@ __global__ void __launch_bounds__(256) rf_cluster_rotate(int64_t n, cd *F, const
   }
 }
 
-// S[C, :] <- Q_C^H S[C, :] for every chunk C: work items (64-column tile, chunk).
-__global__ void __launch_bounds__(256) rf_cluster_rotate_rows(int64_t n, cd *S, const int32_t *clist,
+// F[C, :] <- Q_C^H F[C, :] for every chunk C of F = S, G (grid y): work items (64-column tile, chunk).
+__global__ void __launch_bounds__(256) rf_cluster_rotate_rows(int64_t n, cd *S, cd *G, const int32_t *clist,
                                                              const int32_t *ncl, const cd *Qbuf,
                                                              const int32_t *skip) {
   __shared__ cd St[CL_MAX][64 + 1];
   __shared__ cd Qs[CL_MAX][CL_MAX + 1];
   if (*skip) return;
+  cd *F = blockIdx.y == 0 ? S : G;
   const int tid = threadIdx.x;
   const int64_t ntile = (n + 63) / 64;
   const int64_t items = (int64_t)(*ncl) * ntile;
@@ -460,7 +476,7 @@ __global__ void __launch_bounds__(256) rf_cluster_rotate_rows(int64_t n, cd *S, 
     __syncthreads();
     for (int e = tid; e < 64 * sz; e += 256) {
       const int a = e % sz, k = e / sz;
-      St[a][k] = (c0 + k < n) ? S[(st + a) + (c0 + k) * n] : cmake(0.0, 0.0);
+      St[a][k] = (c0 + k < n) ? F[(st + a) + (c0 + k) * n] : cmake(0.0, 0.0);
     }
     for (int e = tid; e < sz * sz; e += 256) Qs[e % sz][e / sz] = Qbuf[qoff + e];
     __syncthreads();
@@ -468,7 +484,7 @@ __global__ void __launch_bounds__(256) rf_cluster_rotate_rows(int64_t n, cd *S, 
     for (int b = tid / 64; b < sz; b += 4) {
       cd s = cmake(0.0, 0.0);
       for (int a = 0; a < sz; ++a) s = cadd(s, cmulc(Qs[a][b], St[a][k]));     // (Q^H)_{ba} = conj(Q_ab)
-      if (c0 + k < n) S[(st + b) + (c0 + k) * n] = s;
+      if (c0 + k < n) F[(st + b) + (c0 + k) * n] = s;
     }
   }
 }
@@ -507,17 +523,25 @@ __global__ void __launch_bounds__(256) rf_rayleigh(int64_t n, const cd *X, const
     lam[j] = ((sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3])) / ((sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]));
 }
 
-// Ascending order of the refined eigenvalues (rank by counting, ties by index).
-__global__ void rf_rank(int64_t n, const double *lam, int32_t *dest) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double v = lam[i];
+// Ascending order of the refined eigenvalues (rank by counting, ties by index;
+// 256 values at a time staged in LDS: 98 us at order 1352 without, 39 with).
+__global__ void __launch_bounds__(256) rf_rank(int64_t n, const double *lam, int32_t *dest) {
+  __shared__ double vals[256];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const double v = i < n ? lam[i] : 0.0;
   int64_t pos = 0;
-  for (int64_t k = 0; k < n; ++k) {
-    const double u = lam[k];
-    pos += (u < v) || (u == v && k < i);
+  for (int64_t k0 = 0; k0 < n; k0 += 256) {
+    __syncthreads();
+    if (k0 + threadIdx.x < n) vals[threadIdx.x] = lam[k0 + threadIdx.x];
+    __syncthreads();
+    const int nk = (int)(n - k0 < 256 ? n - k0 : 256);
+    const int me = (int)(i - k0 < 0 ? 0 : (i - k0 > 256 ? 256 : i - k0));   // k < i <=> k - k0 < me
+    int c = 0;
+#pragma unroll 8
+    for (int k = 0; k < nk; ++k) c += (vals[k] < v) || (vals[k] == v && k < me);
+    pos += c;
   }
-  dest[i] = (int32_t)pos;
+  if (i < n) dest[i] = (int32_t)pos;
 }
 
 __global__ void rf_scatter(int64_t n, const cd *X, const double *lam, const int32_t *dest, cd *A,
@@ -540,7 +564,7 @@ struct RefWs {
   size_t stage_bytes;
   cd *X, *B1, *B2;
   double *lam, *colmax, *delta;
-  int32_t *cid, *clist, *ncl, *band, *dest, *skip, *stop, *bad, *longrun;
+  int32_t *cid, *clist, *ncl, *band, *dest, *stop, *stop2, *bad, *longrun;
   unsigned long long *emax;
   double *msml;
   int32_t *noskip;        // a flag that stays zero (final products run unconditionally)
@@ -560,6 +584,7 @@ inline RefWs ref_ws(int64_t M, bool refine, void *base) {
   const size_t s2 = stedc_ws_bytes(M), s3 = unmtr_ws_bytes_c64(M);
   if (s2 > st) st = s2;
   if (s3 > st) st = s3;
+  if (refine && n * n * sizeof(cd) > st) st = n * n * sizeof(cd);   // G of the refinement (the divide and conquer needs more)
   w.stage = cv.take<char>(st);
   w.stage_bytes = st;
   if (refine) {
@@ -577,8 +602,8 @@ inline RefWs ref_ws(int64_t M, bool refine, void *base) {
   w.ncl = cv.take<int32_t>(1);
   w.band = cv.take<int32_t>(1);
   w.dest = cv.take<int32_t>(n);
-  w.skip = cv.take<int32_t>(1);
   w.stop = cv.take<int32_t>(1);
+  w.stop2 = cv.take<int32_t>(1);
   w.bad = cv.take<int32_t>(1);
   w.longrun = cv.take<int32_t>(1);
   w.emax = cv.take<unsigned long long>(1);
@@ -621,71 +646,62 @@ static int c64_finish(int64_t n, cd *A, int64_t lda, double *w, bool refine, con
   (void)B3;
   for (int it = 0; it < iters; ++it) {
     cd *X = bufs[it % 2], *Xo = bufs[(it + 1) % 2];
-    hipLaunchKernelGGL(rf_latch, dim3(1), dim3(64), 0, st, ws.skip, ws.stop);
-    MMF_LAUNCH_CHECK();
+    // the flag that this iteration obeys, and the one that it sets for the next
+    const int32_t *skip = it & 1 ? ws.stop2 : ws.stop;
+    int32_t *next = it & 1 ? ws.stop : ws.stop2;
     // Xo = A X (A Hermitian from its lower triangle, banded); Xo is free here
-    hipLaunchKernelGGL(rf_hermitize, g2, dim3(256), 0, st, n, A, lda, B2, ws.skip);
+    hipLaunchKernelGGL(rf_hermitize, g2, dim3(256), 0, st, n, A, lda, B2, skip);
     MMF_LAUNCH_CHECK();
     GemmArgs ga = gemm_args(n, n, n, B2, n, X, n, Xo, n, 1.0, 0.0, 0.0, 0.0);
     ga.band_ptr = ws.band;
-    ga.skip = ws.skip;
+    ga.skip = skip;
     rc = gemm_launch<true, A_N, B_N>(ga, st);
     if (rc) return rc;
-    // B2 = S = X^H (A X);  Xo = G = X^H X  (Hermitian: lower triangles, then mirrored)
-    GemmArgs gs = gemm_args(n, n, n, X, n, Xo, n, B2, n, 1.0, 0.0, 0.0, 0.0);
-    gs.skip = ws.skip;
+    // B2 = S = X^H (A X);  G = X^H X  (Hermitian: lower triangles, then mirrored)
+    cd *S = B2, *G = reinterpret_cast<cd *>(ws.stage);
+    GemmArgs gs = gemm_args(n, n, n, X, n, Xo, n, S, n, 1.0, 0.0, 0.0, 0.0);
+    gs.skip = skip;
     gs.lower = 1;
-    rc = gemm_launch<true, A_C, B_N>(gs, st);
-    if (rc) return rc;
-    GemmArgs gg = gemm_args(n, n, n, X, n, X, n, Xo, n, 1.0, 0.0, 0.0, 0.0);
-    gg.skip = ws.skip;
+    GemmArgs gg = gemm_args(n, n, n, X, n, X, n, G, n, 1.0, 0.0, 0.0, 0.0);
+    gg.skip = skip;
     gg.lower = 1;
-    rc = gemm_launch<true, A_C, B_N>(gg, st);
-    if (rc) return rc;
-    cd *S = B2, *G = Xo;
-    hipLaunchKernelGGL(rf_mirror, g2, dim3(256), 0, st, n, S, G, ws.skip);
+    hipLaunchKernelGGL(rf_gram, dim3(cdiv(n, GT_M), cdiv(n, GT_N), 2), dim3(GEMM_THREADS), 0, st, gs, gg);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rf_lambda, dim3((unsigned)n), dim3(256), 0, st, n, S, G, ws.lam, ws.colmax, ws.skip);
+    hipLaunchKernelGGL(rf_mirror, g2, dim3(256), 0, st, n, S, G, skip);
+    MMF_LAUNCH_CHECK();
+    hipLaunchKernelGGL(rf_lambda, dim3((unsigned)n), dim3(256), 0, st, n, S, G, ws.lam, ws.colmax, skip);
     MMF_LAUNCH_CHECK();
     hipLaunchKernelGGL(rf_clusters, dim3(1), dim3(RC_THREADS), 0, st, n, ws.lam, ws.colmax, ws.cid, ws.dest, ws.clist,
-                       ws.ncl, ws.delta, ws.msml, ws.skip, ws.stop, ws.bad, ws.longrun,
+                       ws.ncl, ws.delta, ws.msml, ws.emax, skip, next, ws.bad, ws.longrun,
                        (it & 1) ? CL_MAX / 2 : 0);
     MMF_LAUNCH_CHECK();
     hipLaunchKernelGGL(rf_cluster_rr, dim3(CL_GRID), dim3(256), 0, st, n, S, G, ws.clist, ws.ncl, ws.Qbuf,
-                       ws.lam, ws.skip);
+                       ws.lam, skip);
     MMF_LAUNCH_CHECK();
     // move X, S and G into the Rayleigh-Ritz basis of every cluster:
     // X <- X Q, S <- Q^H S Q, G <- Q^H G Q (Q block diagonal, identity outside clusters)
-    hipLaunchKernelGGL(rf_cluster_rotate, dim3(CL_GRID), dim3(256), 0, st, n, X, ws.clist, ws.ncl, ws.Qbuf, ws.skip);
+    hipLaunchKernelGGL(rf_cluster_rotate, dim3(CL_GRID, 3), dim3(256), 0, st, n, X, S, G, ws.clist, ws.ncl, ws.Qbuf,
+                       skip);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rf_cluster_rotate, dim3(CL_GRID), dim3(256), 0, st, n, S, ws.clist, ws.ncl, ws.Qbuf, ws.skip);
+    hipLaunchKernelGGL(rf_cluster_rotate_rows, dim3(CL_GRID, 2), dim3(256), 0, st, n, S, G, ws.clist, ws.ncl, ws.Qbuf,
+                       skip);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rf_cluster_rotate_rows, dim3(CL_GRID), dim3(256), 0, st, n, S, ws.clist, ws.ncl, ws.Qbuf,
-                       ws.skip);
+    hipLaunchKernelGGL(rf_lambda, dim3((unsigned)n), dim3(256), 0, st, n, S, G, ws.lam, ws.colmax, skip);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rf_cluster_rotate, dim3(CL_GRID), dim3(256), 0, st, n, G, ws.clist, ws.ncl, ws.Qbuf, ws.skip);
+    hipLaunchKernelGGL(rf_build_f, g2, dim3(256), 0, st, n, S, G, ws.lam, ws.cid, ws.emax, skip);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rf_cluster_rotate_rows, dim3(CL_GRID), dim3(256), 0, st, n, G, ws.clist, ws.ncl, ws.Qbuf,
-                       ws.skip);
+    hipLaunchKernelGGL(rf_predict, dim3(1), dim3(64), 0, st, ws.emax, ws.msml, next, skip, ws.longrun);
     MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rf_lambda, dim3((unsigned)n), dim3(256), 0, st, n, S, G, ws.lam, ws.colmax, ws.skip);
-    MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rf_zero_u64, dim3(1), dim3(64), 0, st, ws.emax);
-    MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rf_build_f, g2, dim3(256), 0, st, n, S, G, ws.lam, ws.cid, ws.emax, ws.skip);
-    MMF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rf_predict, dim3(1), dim3(64), 0, st, ws.emax, ws.msml, ws.stop, ws.skip, ws.longrun);
-    MMF_LAUNCH_CHECK();
-    // Xo = X F  (G in Xo is no longer needed); a skipped iteration copies X into Xo
+    // Xo = X F; a skipped iteration copies X into Xo
     GemmArgs gf = gemm_args(n, n, n, X, n, S, n, Xo, n, 1.0, 0.0, 0.0, 0.0);
-    gf.skip = ws.skip;
+    gf.skip = skip;
     rc = gemm_launch<true, A_N, B_N>(gf, st);
     if (rc) return rc;
-    hipLaunchKernelGGL(rf_carry, g2, dim3(256), 0, st, n, X, Xo, ws.skip);
+    hipLaunchKernelGGL(rf_carry, g2, dim3(256), 0, st, n, X, Xo, skip);
     MMF_LAUNCH_CHECK();
   }
   // the iteration cap was reached without the convergence test passing
-  hipLaunchKernelGGL(rf_flag_unconverged, dim3(1), dim3(64), 0, st, ws.stop, ws.bad, info);
+  hipLaunchKernelGGL(rf_flag_unconverged, dim3(1), dim3(64), 0, st, iters & 1 ? ws.stop2 : ws.stop, ws.bad, info);
   MMF_LAUNCH_CHECK();
   cd *X = bufs[iters % 2], *Y = bufs[(iters + 1) % 2];
   // eigenvalues as Rayleigh quotients of the final vectors: Y = A X (banded), then per column
