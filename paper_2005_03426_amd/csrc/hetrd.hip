@@ -466,6 +466,28 @@ __global__ void __launch_bounds__(256, 2) ht_column(const HtProb<R> *pr, int64_t
   if (tid == 0) q.sparts[lb * nchmax + slot] = (shs[0] + shs[1]) + (shs[2] + shs[3]);
 }
 
+// get(0) + ... + get(min(last, N - 1)), all N entries read before the first is
+// added: a loop's remainder waits for memory once per entry (order 1715 21.56
+// -> 21.21 ms, refined 1352 18.46 -> 18.15; eight at once: 450 1 % slower).
+constexpr int HF_LOADS = 4;
+template <int N, typename Get>
+__device__ __forceinline__ auto ht_sum_ahead(Get get, int last) {
+  if (last <= 0) return get(0);
+  decltype(get(0)) t[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) t[j] = get(j);
+#pragma unroll
+  for (int j = 1; j < N; ++j) {
+    t[j].re = j <= last ? t[j].re : 0;
+    t[j].im = j <= last ? t[j].im : 0;
+  }
+#pragma unroll
+  for (int w = N / 2; w > 0; w /= 2)
+#pragma unroll
+    for (int j = 0; j < w; ++j) t[j] = cadd(t[j], t[j + w]);
+  return t[0];
+}
+
 // Column i = p + k after ht_column: w = tau u - (|tau|^2 g / 2) v, and inside
 // the panel column i+1 updated by the k+1 reflectors so far.  One workgroup
 // per 64-row block.  Parts 0 .. 3 (a wavefront each) split the partial sums
@@ -520,26 +542,24 @@ __global__ void __launch_bounds__(WIDE ? 512 : 256) ht_finish(const HtProb<R> *p
       v = gload(P3 + rho + (int64_t)k * n);
       if (next) a = gload((const MMF_GLOBAL C *)pq.A + rho + (i + 1) * lda);
     }
-    // direct partials of block columns wave, wave + 4, ... (four independent
-    // accumulators), transposed partials of this block column's slots
+    // direct partials of block columns wave, wave + 4, ..., transposed partials
+    // of this block column's slots (beyond the last one it is read again for nothing)
     const MMF_GLOBAL C *pc = pdir + lbi * HV_T + lane;
-    C u0 = cmk<R>(0, 0), u1 = u0, u2 = u0, u3 = u0;
-    int64_t lb = wave;
-    for (; lb + 12 <= lbi; lb += 16) {
-      u0 = cadd(u0, gload(pc + lb * mpad));
-      u1 = cadd(u1, gload(pc + (lb + 4) * mpad));
-      u2 = cadd(u2, gload(pc + (lb + 8) * mpad));
-      u3 = cadd(u3, gload(pc + (lb + 12) * mpad));
-    }
-    for (; lb <= lbi; lb += 4) u0 = cadd(u0, gload(pc + lb * mpad));
+    for (int64_t l0 = wave; l0 <= lbi; l0 += 4 * HF_LOADS)
+      u = cadd(u, ht_sum_ahead<HF_LOADS>([&](int j) {
+        const int64_t lb = l0 + 4 * j;
+        return gload(pc + (lb < lbi ? lb : lbi) * mpad);
+      }, (int)((lbi - l0) >> 2)));
     const int nin = ht_strips(n, i, ch, lbi);
     const bool edge = nb != nfull && b0 + lbi < nb - 1;
     const MMF_GLOBAL C *pt = ptrn + lbi * nchmax * HV_T + lane;
-    if (wave == 1) u1 = cadd(u1, gload(pt));
-    if (wave == 2 && edge) u1 = cadd(u1, gload(pt + HV_T));
-#pragma unroll 4
-    for (int c = wave; c < nin; c += 4) u2 = cadd(u2, gload(pt + (int64_t)(c + 2) * HV_T));
-    u = cadd(cadd(u0, u1), cadd(u2, u3));
+    for (int c0 = wave; c0 < nin; c0 += 4 * HF_LOADS)
+      u = cadd(u, ht_sum_ahead<HF_LOADS>([&](int j) {
+        const int c = c0 + 4 * j;
+        return gload(pt + (int64_t)((c < nin ? c : nin - 1) + 2) * HV_T);
+      }, (nin - 1 - c0) >> 2));
+    if (wave == 1) u = cadd(u, gload(pt));
+    if (wave == 2 && edge) u = cadd(u, gload(pt + HV_T));
   }
   if (part2 == 4) {
     // ---- panel products x1 (lanes < k), x2 (the next k) and 2 Re(x2^H x1)
@@ -549,8 +569,10 @@ __global__ void __launch_bounds__(WIDE ? 512 : 256) ht_finish(const HtProb<R> *p
     const int qc = lane < k ? lane : lane - k;
     if (on) {
       const MMF_GLOBAL C *dp = dots + (lane < k ? 0 : HT_NB) + qc;
-#pragma unroll 4
-      for (int g = 0; g < gdot; ++g) s = cadd(s, gload(dp + (int64_t)g * 2 * HT_NB));
+      for (int g0 = 0; g0 < gdot; g0 += HF_LOADS)
+        s = cadd(s, ht_sum_ahead<HF_LOADS>([&](int j) {
+          return gload(dp + (int64_t)(g0 + j < gdot ? g0 + j : gdot - 1) * 2 * HT_NB);
+        }, gdot - 1 - g0));
       if (lane < k) x1[qc] = s; else x2[qc] = s;
     }
     const R ore = __shfl(s.re, (lane + k) & 63, 64), oim = __shfl(s.im, (lane + k) & 63, 64);
