@@ -225,24 +225,38 @@ template <> struct NtVec<float> { typedef float v __attribute__((ext_vector_type
 // Panel products of column i for row chunk g (dr rows):
 // dots[g*2NB + q] = sum conj(W[:,q]) v and dots[g*2NB + NB + q] =
 // sum conj(V[:,q]) v (q < k) over its rows of [i+1, n).  One wavefront per
-// product qq (lane l sums rows l, l + 64, ...).
+// product qq (lane l sums rows l, l + 64, ...), from x: v = scale x below row
+// i + 1, so that the reads need not wait for the column's scalars (order 450 4.90
+// -> 4.83 ms, 5000 140.9 -> 137.2, 48 uneven ones 110.1 -> 108.9).
 template <typename R>
 __device__ void ht_dots_wave(const HtProb<R> &pq, int64_t i, int k, int g, int qq, int dr) {
   const int64_t n = pq.n;
   const int q = qq % k, which = qq / k;
   const MMF_GLOBAL cx<R> *X = (const MMF_GLOBAL cx<R> *)pq.P3 + (int64_t)(which == 0 ? HT_NB + q : q) * n;
   const MMF_GLOBAL cx<R> *x = (const MMF_GLOBAL cx<R> *)pq.x;
+  const int lane = threadIdx.x & 63;
+  const int64_t r0 = i + 1 + (int64_t)g * dr;
+  cx<R> s = cmk<R>(0, 0), first = s;
+  for (int j0 = 0; j0 < dr && r0 + j0 < n; j0 += 256) {
+    cx<R> a[4], b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t r = r0 + j0 + 64 * u + lane, rc = r < n ? r : n - 1;
+      a[u] = gload(X + rc);
+      b[u] = gload(x + rc);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t r = r0 + j0 + 64 * u + lane;
+      const bool on = r < n && r > i + 1;
+      s = cadd(s, cmulc(a[u], cmk<R>(on ? b[u].re : R(0), on ? b[u].im : R(0))));
+      if (r == i + 1) first = cconj(a[u]);          // v is one there
+    }
+  }
   R beta;
   cx<R> tau, scale;
   ht_column_scalars<R>(pq, i, beta, tau, scale);
-  const int lane = threadIdx.x & 63;
-  const int64_t r0 = i + 1 + (int64_t)g * dr;
-  cx<R> s = cmk<R>(0, 0);
-#pragma unroll 4
-  for (int j = lane; j < dr; j += 64) {
-    const int64_t r = r0 + j;
-    if (r < n) s = cadd(s, cmulc(gload(X + r), ht_v<R>(gload(x + r), r, i, n, scale)));
-  }
+  s = cadd(cmul(scale, s), first);
   const R re = wave_sum(s.re), im = wave_sum(s.im);
   if (lane == 0) ((MMF_GLOBAL cx<R> *)pq.dots)[(int64_t)g * 2 * HT_NB + which * HT_NB + q] = cmk<R>(re, im);
 }
