@@ -141,8 +141,9 @@ __host__ __device__ inline int64_t hb_qr_wgs(int64_t m) {
 // before the sums are known, and reduces over its rows with lane folds.  Staging every product in 70 KB
 // of LDS instead (256 rows per workgroup, three barriers per 16 columns) took
 // 15.0 us a launch at order 12168 and 19.4 at 8 x 5376 beside the update of
-// the previous panel; this form takes 12.3 and 18.4 (7.8 and 9.8 alone; fewer
-// workgroups of the update at a time, 256 to 448, left it at 12.2).
+// the previous panel; this form took 12.3 and 18.4 (7.8 and 9.8 alone; fewer
+// workgroups of the update at a time, 256 to 448, left it at 12.2), and 11.6 and
+// 17.6 with the published row read before the barrier and eight partials at once.
 __global__ void __launch_bounds__(64 * QR_SETS, 4) hb_qr_step(const HbProb *pr, int64_t c0, int j) {
   __shared__ cd psum[QR_SETS][BW];
   __shared__ cd xps[QR_REP][QR_ROWS], xjs[QR_REP][QR_ROWS];
@@ -178,6 +179,14 @@ __global__ void __launch_bounds__(64 * QR_SETS, 4) hb_qr_step(const HbProb *pr, 
     }
   };
   load(rb);
+  // and the previous column's row: alpha, and the entry of column c1 (below)
+  const int cmine = (lane & 15) == 15 ? j : j + cs + 8 * (lane & 15);
+  const int c1 = cmine < BW ? cmine : BW - 1;
+  cd alpha = cmake(0.0, 0.0), pc = alpha;
+  if (j >= 1) {
+    alpha = gload(prd + jp);
+    pc = gload(prd + c1);
+  }
   if (cs == 0) {
     for (int u = 0; u < rep; ++u) {
       const int64_t r = rb + (int64_t)QR_ROWS * u;
@@ -189,10 +198,21 @@ __global__ void __launch_bounds__(64 * QR_SETS, 4) hb_qr_step(const HbProb *pr, 
   if (j >= 1) {
     // partials of the previous launch: thread = column, every eighth workgroup
     cd sum = cmake(0.0, 0.0);
-    if (lane >= jp) {
-#pragma unroll 4
-      for (int64_t w = cs; w < nwg; w += QR_SETS) sum = cadd(sum, gload(gr + w * BW + lane));
-    }
+    if (lane >= jp)
+      for (int64_t w0 = cs; w0 < nwg; w0 += 8 * QR_SETS) {
+        cd t[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {               // beyond the last workgroup it is read again for nothing
+          const int64_t w = w0 + q * QR_SETS;
+          t[q] = gload(gr + (w < nwg ? w : nwg - 1) * BW + lane);
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const bool on = w0 + q * QR_SETS < nwg;
+          sum.re += on ? t[q].re : 0.0;
+          sum.im += on ? t[q].im : 0.0;
+        }
+      }
     psum[cs][lane] = sum;
   } else if (nr < BW) {
     // a panel with fewer than BW reflectors (m <= BW rows): its other V columns vanish
@@ -208,7 +228,6 @@ __global__ void __launch_bounds__(64 * QR_SETS, 4) hb_qr_step(const HbProb *pr, 
     // ---- reflector jp from the sums
     const int u = lane & 7;
     const double xn2 = wave_sum(lane < 8 ? psum[u][jp].re : 0.0);
-    const cd alpha = gload(prd + jp);
     double beta = alpha.re;
     if (xn2 > 0.0 || alpha.im != 0.0) {
       const double nrm = sqrt(alpha.re * alpha.re + alpha.im * alpha.im + xn2);
@@ -224,10 +243,7 @@ __global__ void __launch_bounds__(64 * QR_SETS, 4) hb_qr_step(const HbProb *pr, 
     }
     // d[c] = conj(tau) (P[rjp, c] + conj(s) g[c]): lane cc < 8 (of each row of
     // 16) the cc-th column of this set, lane 15 column j, two partials per row
-    const int cmine = (lane & 15) == 15 ? j : j + cs + 8 * (lane & 15);
-    const int c1 = cmine < BW ? cmine : BW - 1;
     const int g2 = 2 * (lane >> 4);
-    const cd pc = gload(prd + c1);
     const cd a = cadd(psum[g2][c1], psum[g2 + 1][c1]);
     dl = cmulc(tj, cadd(pc, cmulc(sc, cmake(rows_sum(a.re), rows_sum(a.im)))));
   }
