@@ -101,15 +101,25 @@ __global__ void rf_band(int64_t n, const cd *A, int64_t lda, int32_t *band) {
 }
 
 __global__ void rf_zero_int(int32_t *p) { if (threadIdx.x == 0) *p = 0; }
-// S = X^H (A X) and G = X^H X (grid z), both on their lower triangle: one after
-// the other each leaves a CU at most one tile at order 1352, 316 us each; together 573.
-__global__ void __launch_bounds__(GEMM_THREADS, 2) rf_gram(GemmArgs s, GemmArgs g) {
+// S = X^H (A X) and then G = X^H X, the tiles of both lower triangles in one
+// row of workgroups: one after the other each left a CU at most one tile at
+// order 1352 (316 us each); as two halves of a square grid the tiles fell on the
+// XCDs unevenly, 506 of them in places for 512, and the last ones ran alone (573
+// us), in a row they do not: 340.
+__global__ void __launch_bounds__(GEMM_THREADS, 2) rf_gram(GemmArgs a, const cd *X, cd *G, int tri) {
   __shared__ double lds[GEMM_LDS_DOUBLES];
-  if (*s.skip) return;
-  const GemmArgs &a = blockIdx.z == 0 ? s : g;
-  const int64_t m0 = (int64_t)blockIdx.x * GT_M, n0 = (int64_t)blockIdx.y * GT_N;
-  if (m0 + GT_M <= n0) return;
-  gemm_tile<true, A_C, B_N>(a, m0, n0, lds);
+  if (*a.skip) return;
+  int t = blockIdx.x;
+  if (t >= tri) {
+    t -= tri;
+    a.B = X;
+    a.C = G;
+  }
+  int row = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);           // t = row (row + 1) / 2 + column
+  while ((int64_t)row * (row + 1) / 2 > t) --row;
+  while ((int64_t)(row + 1) * (row + 2) / 2 <= t) ++row;
+  const int col = t - (int)((int64_t)row * (row + 1) / 2);
+  gemm_tile<true, A_C, B_N>(a, (int64_t)row * GT_M, (int64_t)col * GT_N, lds);
 }
 
 // S and G are computed on their lower triangle only (Hermitian products);
@@ -662,10 +672,8 @@ static int c64_finish(int64_t n, cd *A, int64_t lda, double *w, bool refine, con
     GemmArgs gs = gemm_args(n, n, n, X, n, Xo, n, S, n, 1.0, 0.0, 0.0, 0.0);
     gs.skip = skip;
     gs.lower = 1;
-    GemmArgs gg = gemm_args(n, n, n, X, n, X, n, G, n, 1.0, 0.0, 0.0, 0.0);
-    gg.skip = skip;
-    gg.lower = 1;
-    hipLaunchKernelGGL(rf_gram, dim3(cdiv(n, GT_M), cdiv(n, GT_N), 2), dim3(GEMM_THREADS), 0, st, gs, gg);
+    const int tri = (int)(cdiv(n, GT_M) * (cdiv(n, GT_M) + 1) / 2);
+    hipLaunchKernelGGL(rf_gram, dim3(2 * tri), dim3(GEMM_THREADS), 0, st, gs, X, G, tri);
     MMF_LAUNCH_CHECK();
     hipLaunchKernelGGL(rf_mirror, g2, dim3(256), 0, st, n, S, G, skip);
     MMF_LAUNCH_CHECK();
