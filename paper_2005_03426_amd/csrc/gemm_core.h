@@ -362,6 +362,17 @@ __device__ void gemm_tile_t(const GemmArgs &g, int64_t m0, int64_t n0, R *lds) {
   }
 }
 
+// Tile t of a lower triangle enumerated by rows, t = row (row + 1) / 2 + col, and
+// the tiles of one of nt rows.  In one row of workgroups no upper tile takes a
+// dispatch, and the XCDs, which take workgroups in turn, get equal shares.
+inline unsigned tri_tiles(int64_t nt) { return (unsigned)(nt * (nt + 1) / 2); }
+__device__ inline void tri_tile(int64_t t, int64_t &row, int64_t &col) {
+  row = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
+  while (row * (row + 1) / 2 > t) --row;
+  while ((row + 1) * (row + 2) / 2 <= t) ++row;
+  col = t - row * (row + 1) / 2;
+}
+
 // FP64 entry used by the existing call sites
 template <bool CPLX, int OA, int OB>
 __device__ inline void gemm_tile(const GemmArgs &g, int64_t m0, int64_t n0, double *lds) {

@@ -115,11 +115,9 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) rf_gram(GemmArgs a, const cd 
     a.B = X;
     a.C = G;
   }
-  int row = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);           // t = row (row + 1) / 2 + column
-  while ((int64_t)row * (row + 1) / 2 > t) --row;
-  while ((int64_t)(row + 1) * (row + 2) / 2 <= t) ++row;
-  const int col = t - (int)((int64_t)row * (row + 1) / 2);
-  gemm_tile<true, A_C, B_N>(a, (int64_t)row * GT_M, (int64_t)col * GT_N, lds);
+  int64_t row, col;
+  tri_tile(t, row, col);
+  gemm_tile<true, A_C, B_N>(a, row * GT_M, col * GT_N, lds);
 }
 
 // S and G are computed on their lower triangle only (Hermitian products);
@@ -672,7 +670,7 @@ static int c64_finish(int64_t n, cd *A, int64_t lda, double *w, bool refine, con
     GemmArgs gs = gemm_args(n, n, n, X, n, Xo, n, S, n, 1.0, 0.0, 0.0, 0.0);
     gs.skip = skip;
     gs.lower = 1;
-    const int tri = (int)(cdiv(n, GT_M) * (cdiv(n, GT_M) + 1) / 2);
+    const int tri = (int)tri_tiles(cdiv(n, GT_M));
     hipLaunchKernelGGL(rf_gram, dim3(2 * tri), dim3(GEMM_THREADS), 0, st, gs, X, G, tri);
     MMF_LAUNCH_CHECK();
     hipLaunchKernelGGL(rf_mirror, g2, dim3(256), 0, st, n, S, G, skip);
