@@ -510,9 +510,11 @@ __device__ __forceinline__ auto ht_sum_ahead(Get get, int last) {
 // partials of v^H A v, 7 forms w[i+1].
 // Latency bound (table, partials, stores, two barriers), so with WIDE the sums
 // that feed the scalars run beside the row sums, in eight wavefronts: 4.9 us
-// at order 1715 against 6.3 in four wavefronts that each take two parts.  Once
-// there are more workgroups than CUs the narrow form is the faster one (48
-// matrices together: 7.4 us against 9.0); both give the same bits.
+// at order 1715 against 6.3 in four wavefronts that each take two parts.  Above
+// two workgroups per CU the narrow form is the faster one; both give the same
+// bits.  Eigenvalues with the line at 256, 512, 1024 workgroups: 20 x 1900 117.6,
+// 116.9, 117.1 ms; 48 x 900 41.8, 41.3, 41.7; 48 x 450 12.2, 11.9, 12.0; 200 x 300
+// 11.8, 11.6, 11.9.
 template <typename R, bool WIDE>
 __global__ void __launch_bounds__(WIDE ? 512 : 256) ht_finish(const HtProb<R> *pr, int64_t p, int k) {
   typedef cx<R> C;
@@ -933,7 +935,7 @@ int hetrd_grouped(const HtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
         }
         ktimer_end(ks, st, bytes);
       }
-      if (nbl * count <= 256)
+      if (nbl * count <= 512)
         hipLaunchKernelGGL((ht_finish<R, true>), dim3((unsigned)nbl, 1, Z), dim3(512), 0, st, pr, p, k);
       else
         hipLaunchKernelGGL((ht_finish<R, false>), dim3((unsigned)nbl, 1, Z), dim3(256), 0, st, pr, p, k);
