@@ -12,6 +12,12 @@ namespace mmf {
 
 constexpr int JAC_NMAX = 64;            // largest order (T and Q: 2 x 64 x 65 complex = 130 KiB of LDS)
 constexpr int JAC_LD = JAC_NMAX + 1;    // row stride of T and Q for the largest order
+// |tpq|^2 below which the entry is scaled to about one before it is squared: a
+// subnormal square keeps only a few bits, the phase tpq / |tpq| formed from it
+// is not of modulus one and the rotation not unitary.  The fill-in of a weakly
+// driven ladder (couplings V far from the diagonal as V^k) comes through that
+// range: at V = 1e-5, order 50, Q^H Q was off by 0.25.
+constexpr double JAC_SCALE = 1e-280;
 
 // LDS of one solve: T and Q (n x n, row r at r * ld, ld >= n + 1 against bank
 // conflicts), the rotations of one step and a reduction scratch.
@@ -109,13 +115,20 @@ __device__ bool jacobi_herm_lds(const JacView &L, int n, int max_sweeps) {
         if (p > q) { const int t = p; p = q; q = t; }
         double cs = 1.0, sn = 0.0, phr = 1.0, phi = 0.0;
         if (q < n) {
-          const cd tpq = L.T[p * ld + q];
-          const double r2 = cabs2(tpq);
+          cd tpq = L.T[p * ld + q];
+          double gap = L.T[q * ld + q].re - L.T[p * ld + p].re, r2 = cabs2(tpq);
+          if (r2 < JAC_SCALE) {             // the angles depend on gap / |tpq| and tpq / |tpq| alone
+            int ex;
+            (void)frexp(fmax(fabs(tpq.re), fabs(tpq.im)), &ex);
+            tpq = cmake(ldexp(tpq.re, -ex), ldexp(tpq.im, -ex));
+            gap = ldexp(gap, -ex);
+            r2 = cabs2(tpq);
+          }
           if (r2 > 0.0) {
             const double ri = rsqrt(r2);
             phr = tpq.re * ri;
             phi = tpq.im * ri;
-            const double theta = 0.5 * (L.T[q * ld + q].re - L.T[p * ld + p].re) * ri;
+            const double theta = 0.5 * gap * ri;
             const double t = copysign(1.0 / (fabs(theta) + sqrt(fma(theta, theta, 1.0))), theta);
             cs = rsqrt(fma(t, t, 1.0));
             sn = t * cs;

@@ -17,7 +17,7 @@ import numpy as np
 import pytest
 
 import oracle
-from workloads import gue, cfg3_uniform_sweep, random_problem
+from workloads import gue, cfg3_uniform_sweep, random_problem, tls_problem
 from gpu_util import require_gpu, to_dev_cm, from_dev_cm, log
 
 pytestmark = pytest.mark.gpu
@@ -194,3 +194,18 @@ def test_batched_assembly_bitwise_and_observables_against_single_calls():
         mmf.build_floquet_dev(dp, Hb)
         torch.cuda.synchronize()
         assert torch.equal(Hb, mmf.build_floquet(dp))
+
+
+@pytest.mark.parametrize("V", [1e-4, 1e-5, 1e-6, 1e-7, 1e-8, 1e-10, 1e-12])
+def test_small_weakly_driven_ladders(V):
+    """Two-level ladders whose fill-in far from the diagonal goes like V^k, so
+    that entries of about 1e-162 to 1e-154 (subnormal squares) are rotated:
+    eigenpairs to n eps as for any other matrix (the file's common bounds)."""
+    torch, mmf = require_gpu()
+    for N in (8, 11, 12, 15):
+        H = oracle.build_floquet(tls_problem(1.0, 4.0 * V, 0.873, N))
+        w, Pt, info = mmf.eigh(to_dev_cm(torch, H))
+        torch.cuda.synchronize()
+        log(f"weakly driven ladder V={V} n={H.shape[0]}")
+        assert int(info.item()) == 0
+        _check_pairs(H, w.cpu().numpy(), from_dev_cm(Pt))
