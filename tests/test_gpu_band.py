@@ -18,7 +18,7 @@ import numpy as np
 import pytest
 
 import oracle
-from workloads import one_drive_band, random_problem, tls_problem
+from workloads import Problem, one_drive_band, random_problem, tls_problem
 from gpu_util import require_gpu, to_dev_cm, from_dev_cm, log
 
 pytestmark = pytest.mark.gpu
@@ -318,3 +318,22 @@ def test_band_padded_leading_dimensions():
     torch.cuda.synchronize()
     _check_window(H, -1.0, 1.0, kmax, wv, Zb[:, :n], cnt, inf)
     assert float(Zb[:, n:].abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("D,N,V", [(2, 60, 1e-5), (2, 100, 1e-3), (2, 100, 1e-8), (3, 20, 1e-8), (3, 50, 1e-6),
+                                   (4, 40, 1e-9)])
+def test_band_weakly_driven_ladders(D, N, V):
+    """One-drive ladders whose bulge decays to columns with subnormal squares:
+    every reflector is unitary and the eigenpairs are as accurate as those of
+    any other band (the file's common bounds)."""
+    torch, mmf = require_gpu()
+    if D == 2:
+        p = tls_problem(1.0, 4.0 * V, 0.873, N)
+    else:
+        rng = np.random.default_rng(0)
+        E = np.diag(np.sort(rng.uniform(0.0, 1.25 * D, D)))
+        A = rng.normal(size=(D, D)) + 1j * rng.normal(size=(D, D))
+        p = Problem(E=E, omega=[0.873], N=[N], axis=[0], harm=[1], V=[V * (A + A.conj().T) / 2])
+    H = oracle.build_floquet(p)
+    log(f"weakly driven band D={D} n={H.shape[0]} V={V}")
+    _check(H, mmf.floquet_half_bandwidth(p))
