@@ -41,7 +41,7 @@ constexpr double DC_EPS = DBL_EPSILON;
 
 struct DcWs {
   double *dw, *lam, *T1, *T2;
-  double *es, *scl;           // scaled off-diagonal; the power of two and its reciprocal
+  double *es, *scl;           // scaled off-diagonal; the power of two, its reciprocal, nonzero once an eigenvalue is NaN
   double *ds, *zs, *dn, *zn, *ddef, *rc, *rs, *lamt, *zhat, *rho;
   int32_t *src, *ndidx, *dfidx, *rp, *rj, *lamo, *colmap, *cnt;   // cnt: [DC_CNT * n] per merge
   int32_t *ctype, *perm;      // child type of each column (1 top, 2 bottom, 3 both); T1/T2 slot of each kept column
@@ -55,7 +55,7 @@ inline DcWs stedc_ws(int64_t n, void *base) {
   w.dw = cv.take<double>(N);
   w.lam = cv.take<double>(N);
   w.es = cv.take<double>(N);
-  w.scl = cv.take<double>(2);
+  w.scl = cv.take<double>(3);
   w.T1 = cv.take<double>(N * N);
   w.T2 = cv.take<double>(N * N);
   w.ds = cv.take<double>(N);
@@ -151,7 +151,17 @@ __global__ void __launch_bounds__(1024) dc_scale(const DcProb *pr) {
   ex = ex > 1000 ? 1000 : (ex < -1000 ? -1000 : ex);
   q.w.scl[0] = ldexp(1.0, -ex);
   q.w.scl[1] = ldexp(1.0, ex);
+  q.w.scl[2] = 0.0;
   *q.info = 0;
+}
+
+// Eigenvalues are ranked by comparisons, and the ranks become positions in
+// arrays and columns of Z: a NaN (which a NaN or infinite entry of the matrix
+// spreads) would leave positions unset that are then used as indices.  It counts
+// as zero in every ranking; the call reports no convergence and returns NaN.
+__device__ inline void dc_not_a_number(const DcProb &P) {
+  P.w.scl[2] = 1.0;
+  *P.info = MMF_ERR_NO_CONVERGENCE;
 }
 
 // es = e and dw = d scaled, with |e_{k-1}| taken from d_{k-1} and d_k at every
@@ -196,7 +206,6 @@ __global__ void __launch_bounds__(64) dc_leaf(const DcProb *pr) {
   double dd = r < m ? dw[s + r] : 0.0;
   double ee = r < m - 1 ? e[s + r] : 0.0;
   for (int c = 0; c < m; ++c) Zl[c * 64 + r] = (c == r) ? 1.0 : 0.0;
-  if (r < DC_LEAF) perm[r] = r;
   __syncthreads();
   bool fail = false;
   for (int l = 0; l < m; ++l) {
@@ -255,6 +264,10 @@ __global__ void __launch_bounds__(64) dc_leaf(const DcProb *pr) {
     if (fail) break;
   }
   if (fail && r == 0) *q.info = MMF_ERR_NO_CONVERGENCE;
+  if (dd != dd) {
+    dc_not_a_number(q);
+    dd = 0.0;
+  }
   // ascending order (selection by rank; ties by index)
   int rank = 0;
   for (int j = 0; j < m; ++j) {
@@ -262,8 +275,8 @@ __global__ void __launch_bounds__(64) dc_leaf(const DcProb *pr) {
     rank += (u < dd) || (u == dd && j < r);
   }
   if (r < m) {
-    perm[rank < m ? rank : m - 1] = r;
-    lam[s + (rank < m ? rank : m - 1)] = dd;
+    perm[rank] = r;
+    lam[s + rank] = dd;
   }
   __syncthreads();
   if (r < m)
@@ -776,7 +789,10 @@ __device__ void dc_final_pos(const DcProb &P, int lev, int64_t bx) {
   const int64_t s = q.s;
   const int K = cnt[DC_CNT * g];
   auto val = [&](int64_t x) -> double {
-    return x < K ? dn[s + lamo[s + x]] + lamt[s + x] : ddef[s + (x - K)];
+    const double u = x < K ? dn[s + lamo[s + x]] + lamt[s + x] : ddef[s + (x - K)];
+    if (u == u) return u;
+    dc_not_a_number(P);
+    return 0.0;
   };
   // ranks by counting, 256 values at a time staged in LDS (each thread looking
   // every value up for itself: 691 us a level at order 12816, this form 99)
@@ -866,7 +882,7 @@ __global__ void __launch_bounds__(GEMM_THREADS, 2) dc_gemm(const DcProb *pr, int
 __global__ void dc_copy_out(const DcProb *pr) {
   const DcProb &P = pr[blockIdx.z];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < P.n) P.d[i] = P.w.lam[i] * P.w.scl[1];
+  if (i < P.n) P.d[i] = P.w.scl[2] == 0.0 ? P.w.lam[i] * P.w.scl[1] : NAN;
 }
 
 // ------------------------------------------------------------------ host

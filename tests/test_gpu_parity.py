@@ -575,3 +575,34 @@ def test_unmtr_direct_orders(n):
     got = from_dev_cm(mmf.unmtr(At, tau, to_dev_cm(torch, Z), out=At))
     torch.cuda.synchronize()
     assert np.abs(got - want).max() <= 20 * n * np.finfo(float).eps
+
+
+@pytest.mark.parametrize("n,two_stage", [(65, False), (140, False), (140, True)])
+@pytest.mark.parametrize("everywhere", [False, True])
+def test_eigh_reports_nan_entries(monkeypatch, n, two_stage, everywhere):
+    """A matrix that holds NaN has no eigenpairs: the call says so (no
+    convergence, every eigenvalue NaN), whatever the divide and conquer's
+    rankings make of it."""
+    torch, mmf = require_gpu()
+    if two_stage:
+        monkeypatch.setenv("MMF_EIGH_TWO_STAGE_MIN", "66")
+    H = gue(np.random.default_rng(n), n, 1.0)
+    H[n // 2, n // 3] = np.nan
+    if everywhere:
+        H[:] = np.nan
+    log(f"eigh with NaN n={n} two_stage={two_stage} everywhere={everywhere}")
+    w, Pt, info = mmf.eigh(to_dev_cm(torch, H))
+    torch.cuda.synchronize()
+    assert int(info.item()) == mmf.MMF_ERR_NO_CONVERGENCE
+    assert torch.isnan(w).all()
+
+
+@pytest.mark.parametrize("n", [16, 17, 300])
+def test_stedc_reports_nan_entries(n):
+    torch, mmf = require_gpu()
+    d = torch.full((n,), float("nan"), dtype=torch.float64, device="cuda")
+    log(f"stedc with NaN n={n}")
+    w, Zt, info = mmf.stedc(d, d[:n - 1].clone())
+    torch.cuda.synchronize()
+    assert int(info.item()) == mmf.MMF_ERR_NO_CONVERGENCE
+    assert torch.isnan(w).all()
