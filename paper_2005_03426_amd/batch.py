@@ -23,6 +23,8 @@ clears its flags and counters with its own kernels).
 from __future__ import annotations
 
 import ctypes as C
+import threading
+
 import numpy as np
 
 from . import (DeviceProblem, eigh_batched, eigh_batched_workspace_bytes, call, MMF_C128, _workspace, _stream,
@@ -63,6 +65,11 @@ def size_classes(sizes, small_max: int = 64, group_max: int = 64, lanes: int = 4
     return [lane for lane in plan if lane]
 
 
+# The event behind the recorded pass enqueued last in this process (its plan's `done`).
+_replay_lock = threading.Lock()
+_replay_last = None
+
+
 class BatchPlan:
     """All device state of one batch of Floquet solves, and its recorded graph.
 
@@ -71,7 +78,14 @@ class BatchPlan:
     the whole batch or one per problem (equal lengths); tiles: the batched
     eigensolver's tile table (None: the library's rule); graph: record and
     replay a graph (else each run() launches eagerly); group_max: largest
-    number of problems per grouped eigensolver call."""
+    number of problems per grouped eigensolver call.
+
+    Recorded passes of different plans take turns: a process in which two of
+    them were in flight at once ended in a corrupted heap, for a reason that is
+    not known, so run() first waits (on the host) for the pass of another plan
+    that was enqueued last.  Passes of one plan follow one another on its
+    stream.  Dropping a plan waits for its stream, since its buffers and graph
+    are in use on that stream and those of its lanes until the pass ends."""
 
     def __init__(self, problems, times, t0: float = 0.0, prec: int = MMF_C128, tiles=None, graph: bool = True,
                  device: str = "cuda", group_max: int = 64):
@@ -115,6 +129,7 @@ class BatchPlan:
         self.stream = torch.cuda.Stream(device=device)
         self.lane_streams = [torch.cuda.Stream(device=device) for _ in self.lanes]
         self.graph = None
+        self.done = torch.cuda.Event()             # behind the recorded pass enqueued last
         # one eager pass first: it also performs the library's one-time set-up
         # (code loading, kernel attributes), which a recording must not contain
         self.stream.wait_stream(torch.cuda.current_stream())
@@ -150,11 +165,26 @@ class BatchPlan:
     def run(self):
         """One pass over the batch on the plan's stream (graph replay or eager
         launches); returns when it is enqueued.  Results: results()."""
-        with self.torch.cuda.stream(self.stream):
-            if self.graph is not None:
-                self.graph.replay()
-            else:
+        global _replay_last
+        if self.graph is None:
+            with self.torch.cuda.stream(self.stream):
                 self._enqueue()
+            return
+        with _replay_lock:
+            if _replay_last is not None and _replay_last is not self.done:
+                _replay_last.synchronize()
+            with self.torch.cuda.stream(self.stream):
+                self.graph.replay()
+                self.done.record(self.stream)
+            _replay_last = self.done
+
+    def __del__(self):
+        stream = getattr(self, "stream", None)     # absent when the constructor ended early
+        if stream is not None:
+            try:
+                stream.synchronize()
+            except Exception:                      # the interpreter or the device is going down
+                pass
 
     def synchronize(self):
         self.stream.synchronize()

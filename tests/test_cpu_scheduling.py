@@ -74,3 +74,93 @@ def test_tune_table_entries_are_valid():
     tab = autotune.load_table()
     assert tab is not None and len(tab) == 8
     assert all(int(x) in (0, 64, 128, 256, 512) for x in tab)
+
+
+class _FakePlans:
+    """BatchPlans over a stand-in for the device that writes down what is done."""
+
+    def __init__(self):
+        import contextlib
+        import threading
+        from types import SimpleNamespace
+        self.log = []                      # (what, plan)
+        self.lock = threading.Lock()
+        self.torch = SimpleNamespace(cuda=SimpleNamespace(stream=lambda s: contextlib.nullcontext()))
+
+    def plan(self, name, graph=True):
+        from paper_2005_03426_amd.batch import BatchPlan
+        log, lock = self.log, self.lock
+
+        class Thing:
+            def _say(self, what):
+                with lock:
+                    log.append((what, name))
+
+        class Graph(Thing):
+            def replay(self):
+                self._say("replay")
+
+            def __del__(self):
+                self._say("graph freed")
+
+        class Event(Thing):
+            def record(self, stream):
+                self._say("record")
+
+            def synchronize(self):
+                self._say("wait")
+
+        class Stream(Thing):
+            def synchronize(self):
+                self._say("stream wait")
+
+        p = object.__new__(BatchPlan)
+        p.torch, p.stream, p.done, p.graph = self.torch, Stream(), Event(), Graph() if graph else None
+        p._enqueue = lambda: log.append(("eager", name))
+        return p
+
+
+def test_recorded_passes_of_two_plans_take_turns(monkeypatch):
+    from paper_2005_03426_amd import batch
+    monkeypatch.setattr(batch, "_replay_last", None)
+    f = _FakePlans()
+    a, b, e = f.plan("a"), f.plan("b"), f.plan("e", graph=False)
+    for p in (a, a, b, e, a, b, b):
+        p.run()
+    enqueued = [("replay", "a"), ("record", "a")], [("replay", "b"), ("record", "b")]
+    A, B = enqueued
+    assert f.log == A + A + [("wait", "a")] + B + [("eager", "e")] + [("wait", "b")] + A + [("wait", "a")] + B + B
+
+
+def test_recorded_passes_of_two_threads_take_turns(monkeypatch):
+    import threading
+    from paper_2005_03426_amd import batch
+    monkeypatch.setattr(batch, "_replay_last", None)
+    f = _FakePlans()
+    plans = [f.plan(k) for k in range(3)]
+    threads = [threading.Thread(target=lambda p=p: [p.run() for _ in range(200)]) for p in plans]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    flying = None                          # the plan whose pass nothing has waited for
+    for what, k in f.log:
+        if what == "wait":
+            assert k == flying
+            flying = None
+        elif what == "replay":
+            assert flying is None or flying == k
+            flying = k
+    assert sum(w == "replay" for w, _ in f.log) == 600
+
+
+def test_dropping_a_plan_waits_before_its_graph_and_buffers_go(monkeypatch):
+    from paper_2005_03426_amd import batch
+    monkeypatch.setattr(batch, "_replay_last", None)
+    f = _FakePlans()
+    p = f.plan("a")
+    p.run()
+    del p
+    assert f.log == [("replay", "a"), ("record", "a"), ("stream wait", "a"), ("graph freed", "a")]
+    from paper_2005_03426_amd.batch import BatchPlan
+    object.__new__(BatchPlan)              # a constructor that ended early: nothing to wait for
