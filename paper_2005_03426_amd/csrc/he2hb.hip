@@ -254,9 +254,11 @@ __global__ void __launch_bounds__(64 * QR_SETS, 4) hb_qr_step(const HbProb *pr, 
     const int64_t r = rb + (int64_t)QR_ROWS * u;
     if (u > 0) load(r);
     cd v = cmake(0.0, 0.0), xr = xjs[u][lane];
-    if (j >= 1 && r < n) {
+    // (rows past the matrix end take part with zeros: d is read from lanes that a
+    // branch on the row would leave idle in a short last block)
+    if (j >= 1) {
       v = r > rjp ? cmul(xps[u][lane], sc) : cmake(r == rjp ? 1.0 : 0.0, 0.0);
-      if (cs == 0) {
+      if (cs == 0 && r < n) {
         if (r > rjp) A[r + jp * lda] = v;
         p3[r + (int64_t)jp * n] = v;
         p3[r + (int64_t)(2 * BW + jp) * n] = v;
@@ -271,7 +273,7 @@ __global__ void __launch_bounds__(64 * QR_SETS, 4) hb_qr_step(const HbProb *pr, 
         if (8 * cc < ncol) {
           const cd d = lane_get(dl, cc);
           xv[cc] = cfnma(xv[cc], v, d);
-          if (r >= rjp) A[r + (j + cs + 8 * cc) * lda] = xv[cc];
+          if (r >= rjp && r < n) A[r + (j + cs + 8 * cc) * lda] = xv[cc];
         }
     }
     if (last) continue;                          // uniform
