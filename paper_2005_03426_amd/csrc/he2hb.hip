@@ -340,7 +340,7 @@ __global__ void __launch_bounds__(256) hb_sum_sp(const HbProb *pr, int64_t c0) {
 // betas go to the band block R, reflectors of length one get tau = 0.
 __global__ void __launch_bounds__(WY_THREADS) hb_tmat(const HbProb *pr, int64_t c0) {
   static_assert(BW == WY_N, "one factor per panel");
-  __shared__ cd G[BW][WY_LD], T[BW][WY_LD];
+  __shared__ cd W[BW][WY_LD];
   __shared__ cd tau[BW];
   const HbProb &P = pr[blockIdx.z];
   HbPanel pp;
@@ -349,11 +349,11 @@ __global__ void __launch_bounds__(WY_THREADS) hb_tmat(const HbProb *pr, int64_t 
   const HbWs &ws = P.ws;
   const int tid = threadIdx.x;
 #pragma unroll 8
-  for (int e = tid; e < BW * BW; e += WY_THREADS) G[e & 63][e >> 6] = ws.Sp[e];
+  for (int e = tid; e < BW * BW; e += WY_THREADS) W[e & 63][e >> 6] = ws.Sp[e];
   if (tid < BW) tau[tid] = tid < nr ? P.tau[c0 + tid] : cmake(0.0, 0.0);
   __syncthreads();
-  wy_tfactor<double>(G, T, tau);
-  for (int e = tid; e < BW * BW; e += WY_THREADS) ws.T[e] = T[e & 63][e >> 6];
+  wy_tfactor<double>(W, tau);
+  for (int e = tid; e < BW * BW; e += WY_THREADS) ws.T[e] = wy_t<double>(W, e & 63, e >> 6);
   if (tid < nr) P.A[(c0 + BW + tid) + (c0 + tid) * P.lda] = cmake(ws.beta[tid], 0.0);
   if (tid >= nr && tid < pp.bw) P.tau[c0 + tid] = cmake(0.0, 0.0);
 }

@@ -203,8 +203,7 @@ __global__ void bt_gram_sum(const BtProb<R> *pr) {
 template <typename R, int NB>
 __global__ void __launch_bounds__(WY_THREADS) bt_tmat(const BtProb<R> *pr) {
   constexpr int H = WY_N, Q = NB / H;
-  __shared__ cx<R> G[H][WY_LD];
-  __shared__ cx<R> T[H][WY_LD];
+  __shared__ cx<R> W[H][WY_LD];
   __shared__ cx<R> tau[H];
   const BtProb<R> &P = pr[blockIdx.z];
   const int64_t b = blockIdx.x / Q;
@@ -219,15 +218,15 @@ __global__ void __launch_bounds__(WY_THREADS) bt_tmat(const BtProb<R> *pr) {
 #pragma unroll 8
   for (int e = tid; e < H * H; e += WY_THREADS) {
     const int r = e & 63, c = e >> 6;
-    G[r][c] = Gs[(h * H + r) + (int64_t)(h * H + c) * NB];
+    W[r][c] = Gs[(h * H + r) + (int64_t)(h * H + c) * NB];
   }
   if (tid < H) tau[tid] = tid < kh ? P.tau[p + h * H + tid] : cmk<R>(0, 0);
   __syncthreads();
-  wy_tfactor<R>(G, T, tau);
+  wy_tfactor<R>(W, tau);
   cx<R> *Tb = P.Tm + b * NB * NB;
   for (int e = tid; e < H * H; e += WY_THREADS) {
     const int r = e & 63, c = e >> 6;
-    Tb[(h * H + r) + (int64_t)(h * H + c) * NB] = T[r][c];
+    Tb[(h * H + r) + (int64_t)(h * H + c) * NB] = wy_t<R>(W, r, c);
   }
   for (int e = tid; e < H * H * h; e += WY_THREADS)
     Tb[(h * H + (e & 63)) + (int64_t)(e >> 6) * NB] = cmk<R>(0, 0);
