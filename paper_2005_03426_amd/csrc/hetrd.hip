@@ -515,6 +515,7 @@ __device__ __forceinline__ auto ht_sum_ahead(Get get, int last) {
 // bits.  Eigenvalues with the line at 256, 512, 1024 workgroups: 20 x 1900 117.6,
 // 116.9, 117.1 ms; 48 x 900 41.8, 41.3, 41.7; 48 x 450 12.2, 11.9, 12.0; 200 x 300
 // 11.8, 11.6, 11.9.
+constexpr int64_t HF_WIDE_MAX = 512;              // most workgroups of a launch in the wide form
 template <typename R, bool WIDE>
 __global__ void __launch_bounds__(WIDE ? 512 : 256) ht_finish(const HtProb<R> *pr, int64_t p, int k) {
   typedef cx<R> C;
@@ -935,7 +936,7 @@ int hetrd_grouped(const HtProb<R> *pr, const int64_t *nh, int64_t count, hipStre
         }
         ktimer_end(ks, st, bytes);
       }
-      if (nbl * count <= 512)
+      if (nbl * count <= HF_WIDE_MAX)
         hipLaunchKernelGGL((ht_finish<R, true>), dim3((unsigned)nbl, 1, Z), dim3(512), 0, st, pr, p, k);
       else
         hipLaunchKernelGGL((ht_finish<R, false>), dim3((unsigned)nbl, 1, Z), dim3(256), 0, st, pr, p, k);

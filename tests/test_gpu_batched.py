@@ -8,6 +8,9 @@ also checked against the FP64 oracle (eigenvalues within 1e-10 relative,
 residual and orthogonality within 1e-12).  Batched Floquet solves are
 compared with the oracle's U(t,t0) and averaged probabilities (1e-10).
 """
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -147,3 +150,25 @@ def test_batched_routes_large_orders_to_the_two_stage_path(monkeypatch):
         assert np.linalg.norm(H @ Phi - Phi * w.cpu().numpy()) <= 1e-12 * max(1.0, np.linalg.norm(H)) * n
         assert np.abs(Phi.conj().T @ Phi - np.eye(n)).max() < 1e-12 * max(1, n)
     log("batched: orders >= 100 through the two-stage path, bitwise equal to single calls")
+
+
+def test_batched_equals_single_with_narrow_finish():
+    """A batch of more 64-row blocks than the line below which a reduction's
+    columns are finished by eight wavefronts (ht_finish), each problem alone
+    below it: the same bits from the narrow form as from the wide one."""
+    torch, mmf = require_gpu()
+    src = open(os.path.join(os.path.dirname(mmf.LIB_PATH), "csrc", "hetrd.hip")).read()
+    line = int(re.search(r"constexpr int64_t HF_WIDE_MAX = (\d+);", src).group(1))
+    sizes = [2200, 1100, 700, 450, 321, 130, 97, 65]
+    blocks = -(-max(sizes) // 64)
+    sizes += [300 + 9 * k for k in range(line // (blocks - 5) + 1 - len(sizes))]   # five blocks of columns on the narrow side
+    assert blocks <= line < (blocks - 5) * len(sizes)
+    log(f"batched eigh, narrow finish: sizes={sizes}")
+    Hs = [_hermitian(n, 1800 + k) for k, n in enumerate(sizes)]
+    ws, Pts, info = mmf.eigh_batched([to_dev_cm(torch, H) for H in Hs])
+    torch.cuda.synchronize()
+    assert info.cpu().tolist() == [0] * len(sizes)
+    for k, H in enumerate(Hs):
+        w1, P1, _ = mmf.eigh(to_dev_cm(torch, H))
+        torch.cuda.synchronize()
+        assert torch.equal(ws[k], w1) and torch.equal(Pts[k], P1), f"n={sizes[k]}"

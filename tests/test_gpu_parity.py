@@ -606,3 +606,26 @@ def test_stedc_reports_nan_entries(n):
     torch.cuda.synchronize()
     assert int(info.item()) == mmf.MMF_ERR_NO_CONVERGENCE
     assert torch.isnan(w).all()
+
+
+@pytest.mark.parametrize("n", [1087, 1088, 1089])
+def test_hetrd_strip_edges(n):
+    """The last order whose interior strips are single tiles and the first ones
+    with two: the reflectors' defining identity A = Q T Q^H and Q unitary."""
+    torch, mmf = require_gpu()
+    rng = np.random.default_rng(n)
+    A = rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))
+    A = A + A.conj().T
+    log(f"hetrd strip edges n={n}")
+    At = to_dev_cm(torch, np.tril(A))
+    d, e, tau = mmf.hetrd(At)
+    torch.cuda.synchronize()
+    refl, t = np.tril(from_dev_cm(At), -1), tau.cpu().numpy()
+    d, e = d.cpu().numpy(), e.cpu().numpy()[:n - 1]
+    Q = np.eye(n, dtype=np.complex128)
+    for i in range(n - 2, -1, -1):               # Q = H_0 (H_1 (... H_{n-2}))
+        v = refl[i + 1:, i]
+        Q[i + 1:, i + 1:] -= t[i] * np.outer(v, v.conj() @ Q[i + 1:, i + 1:])
+    T = np.diag(d) + np.diag(e, 1) + np.diag(e, -1)
+    assert np.abs(Q.conj().T @ Q - np.eye(n)).max() < 1e-13 * max(1, n / 10)
+    assert np.abs(Q @ T @ Q.conj().T - A).max() < 1e-13 * np.abs(A).max() * max(1, n / 10)
