@@ -43,8 +43,8 @@ HBM_PEAK_GBS = 8000.0
 TRAFFIC = {
     ("bt2", "ladder20808"): {
         "bytes_per_launch": 1.9207e9 + 1.8857e9,
-        "sources": {"paper_2005_03426_amd/csrc/hb2st.hip": "4111e49b2e1f7b1d",
-                    "paper_2005_03426_amd/csrc/twostage.h": "0a2ef008d04ef564"},
+        "sources": {"paper_2005_03426_amd/csrc/hb2st.hip": "713b54a8c1735bc5",
+                    "paper_2005_03426_amd/csrc/twostage.h": "1d157dc56f2ecf42"},
         "profile": "profiles/hbm_bytes_ladder20808_counters.md",
     },
 }

@@ -175,7 +175,8 @@ int mmf_eigh_workspace(int64_t M, int prec, size_t *bytes);
  *      of w[a] (the paper's U_F array).
  * w:   dev [M], eigenvalues in ascending order.
  * work/work_bytes: dev scratch of at least mmf_eigh_workspace() bytes.
- * dev_info: dev int32, set to 0 or to MMF_ERR_NO_CONVERGENCE by the kernels.
+ * dev_info: dev int32, set to 0 or to MMF_ERR_NO_CONVERGENCE by the kernels
+ *      (also for a matrix that holds NaN; w is then NaN).
  * Method: order <= 64: one workgroup holding the matrix and its
  * eigenvectors in LDS, parallel cyclic Jacobi (complex128).  Above that:
  * Householder reduction to a real symmetric tridiagonal matrix,

@@ -49,9 +49,11 @@ def size_classes(sizes, small_max: int = 64, group_max: int = 64, lanes: int = 4
     for key in sorted(octaves, reverse=True):
         ks = sorted(octaves[key], key=lambda k: -sizes[k])
         groups += [ks[i:i + group_max] for i in range(0, len(ks), group_max)]
-    # time of a grouped call: its sequential steps (about 40 us per column of
-    # its largest order) plus its work at about 10 TFLOP/s of the nominal
-    # (40/3) M^3 flops per problem
+    # time of a grouped call: its sequential steps (40 us per column of its
+    # largest order, measured when a column took four launches; with two it takes
+    # about 11 alone and more beside the other lanes) plus its work at about 10
+    # TFLOP/s of the nominal (40/3) M^3 flops per problem.  Only the ratios of the
+    # costs matter; they were not measured again.
     def cost(g):
         return 4e-5 * max(float(sizes[k]) for k in g) + 1.33e-12 * sum(float(sizes[k]) ** 3 for k in g)
     groups.sort(key=lambda g: -cost(g))

@@ -32,8 +32,9 @@ struct BEnt {
   int32_t *flags;      // degenerate-pair counts [G]
 };
 
-// What a call knows of a problem, packed for the kernel arguments (32 entries a
-// launch, where whole BEnt entries went 14 at a time); the table kernels derive
+// What a call knows of a problem, packed for the kernel arguments (30 entries a
+// launch of the assembly, 34 of the observables, where whole BEnt entries went 14
+// at a time); the table kernels derive
 // the rest (radix, S, M, s0 and the workspace carving).
 struct BPack {
   double omega[BMAX_F];

@@ -44,9 +44,11 @@ size_t eigh2_full_ws_bytes(int64_t M);
 
 // Batched calls could solve their complex128 problems from the two-stage
 // order up one by one on the two-stage path (as single calls do).  This is
-// switched off: the serving benchmark with it enabled ended in a GPU fault
-// whose cause has not been found; batched problems of every order take the
-// grouped one-stage path.
+// switched off: the serving benchmark with it enabled ended in a GPU fault.  A
+// mistake that fits it (weakly driven one-drive requests drove the chase's
+// reflectors to 0 / 0, and the divide and conquer used ranks of the NaN as
+// indices) has been mended since, but the path has not been run again; batched
+// problems of every order take the grouped one-stage path.
 constexpr bool BATCHED_TWO_STAGE = false;
 
 // one problem's slot in a batched call

@@ -28,7 +28,10 @@
 //     workgroup) and leaves its norm partials.
 // Four launches per column (reflector, product, u, w with the next column)
 // took 18.5 us per column at order 82, 23 at 450 and 31.5 at 1715
-// (profiled); the two take 2.1 (all in the tail), 10.0 and 11.9.
+// (profiled); the two take 2.1 (all in the tail), 10.0 and 11.5.  (The figures
+// beside the single choices below are those of the change that made them; whole
+// solves take 4.9 ms at order 450 in the dressed basis, 21.2 at 1715 and 138 at
+// 5000 with all of them.)
 // The last HT_TAIL rows of every matrix (all of a smaller one) are reduced by
 // one workgroup in registers (ht_tail).
 // All sums are over fixed partitions in fixed order (deterministic).

@@ -18,7 +18,10 @@ struct SmallProb {
 // the caller gives no tuning table: 64 up to 16, 256 up to 32, 512 above.
 // One matrix, 64 / 128 / 256 / 512 threads: order 16 112 / 102 / 107 / 108 us,
 // 32 555 / 356 / 259 / 247, 34 812 / 468 / 359 / 290, 64 4179 / 2351 / 1405 /
-// 1083; 512 matrices of order 34 1350 / 1010 / 865 / 791 us.
+// 1083; 512 matrices of order 34 1350 / 1010 / 865 / 791 us.  (Above order 64 the
+// Householder path takes over; it has become several times faster since that line
+// was drawn, 400 us for one matrix of order 82, and the line was not measured
+// again.)
 inline int32_t small_default_threads(int64_t n) { return n <= 16 ? 64 : (n <= 32 ? 256 : 512); }
 
 // Device bytes of the table region eigh_small_batched needs for `count` problems.

@@ -23,9 +23,9 @@
 // arrays, so every merge of a tree level runs in the same launches.
 //
 // Grouped execution: the kernels read each problem's tree and buffers from a
-// device table (DcProb); the grid's z (or y) dimension enumerates
-// (problem, merge) pairs, so one launch serves a tree level of every matrix
-// of a batch.  A single tridiagonal problem is the one-entry case.
+// device table (DcProb); the grid's z dimension enumerates the problems and y
+// the merges (the deflation scan's x both), so one launch serves a tree level of
+// every matrix of a batch.  A single tridiagonal problem is the one-entry case.
 #include <float.h>
 #include <vector>
 #include "common.h"
@@ -899,7 +899,7 @@ int stedc_grouped(const DcProb *pr, const int64_t *nh, int64_t count, hipStream_
   }
   if (nmax <= 0) return MMF_OK;
   {
-    // grid z holds (merge, problem) pairs: split the batch so it stays within 65535
+    // split the batch so that merges times problems stay within 65535
     int64_t Lall = 1;
     for (int64_t c = 0; c < count; ++c) {
       const int64_t L = (int64_t)1 << dc_depth(nh[c]);

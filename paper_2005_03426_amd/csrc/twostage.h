@@ -18,7 +18,8 @@ constexpr int BT2_G = 64;         // sweeps per block of the second back-transfo
 // in ms: full eigensolve 224 / 235 at order 6144, 339 / 310 at 7168;
 // eigenvalues of one matrix 138 / 142 at 5120, 203 / 177 at 6144, of 8
 // matrices (the chase steps of all share each launch) 37.0 / 42.5 at 1536,
-// 63.7 / 60.9 at 2048.  The environment variable MMF_EIGH_TWO_STAGE_MIN
+// 63.7 / 60.9 at 2048.  (Later steps made the one-stage side some 4 % faster at
+// order 5000; the lines were not measured again.)  The environment variable MMF_EIGH_TWO_STAGE_MIN
 // overrides every default.
 constexpr int64_t TWO_STAGE_MIN_DEFAULT = 6400;
 constexpr int64_t EV_TWO_STAGE_MIN_ONE = 5248;     // eigenvalues only, few problems
@@ -67,7 +68,7 @@ int hb_band_from_dense_run(int64_t n, const mmf_z *A, int64_t lda, int64_t b, mm
 
 // Batches (eigenvalues only): problem c has order n[c], its own stage-1
 // workspace stage[c] (he2hb_ws_bytes(n[c])), band array AB[c] (n x LDAB), and
-// for the chase a compact reflector store V2[c] (n x BW) and tau2[c] (n);
+// for the chase a compact reflector store V2[c] (n x 2 BW) and tau2[c] (2 n);
 // `table` holds count * STAGE_TABLE_BYTES device bytes (rewritten per stage).
 int he2hb_batched(int64_t count, const int64_t *n, mmf_z *const *A, const int64_t *lda, mmf_z *const *tau,
                   mmf_z *const *AB, void *const *stage, void *table, hipStream_t st);

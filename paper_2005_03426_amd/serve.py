@@ -20,7 +20,9 @@ Floquet matrix is banded within its 64th subdiagonal (one drive with
 D h + D - 1 <= 64) and of order at least band_min is solved alone through the
 band-aware eigensolver (mmf_eigh_band: no dense -> band stage).  That routing
 is off by default: the 2000-request serving benchmark with it ended in a GPU
-memory fault whose cause has not been found.  A batch whose workspace the caching allocator
+memory fault.  A mistake that fits it (columns of weakly driven requests with
+subnormal squares in the bulge chase) has been mended since; the routing has not
+been run again.  A batch whose workspace the caching allocator
 cannot place (fragmented free blocks) is solved one request at a time.
 Results stay on the device until
 the caller reads them.  Latency runs from a request's arrival to the moment
@@ -87,7 +89,8 @@ class Executor:
         is solved alone (the grouped eigensolver takes none); band_min: order
         from which narrow-band complex128 requests take the band-aware
         eigensolver (None, the default: never; the serving benchmark with
-        band_min = 1024 ended in a GPU fault whose cause is not known)."""
+        band_min = 1024 ended in a GPU fault and has not been run with it
+        since)."""
         import torch
         self.torch = torch
         self.retry_c128 = retry_c128

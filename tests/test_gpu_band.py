@@ -18,7 +18,7 @@ import numpy as np
 import pytest
 
 import oracle
-from workloads import Problem, one_drive_band, random_problem, tls_problem
+from workloads import Problem, cfg5_serving, one_drive_band, random_problem, tls_problem
 from gpu_util import require_gpu, to_dev_cm, from_dev_cm, log
 
 pytestmark = pytest.mark.gpu
@@ -337,3 +337,25 @@ def test_band_weakly_driven_ladders(D, N, V):
     H = oracle.build_floquet(p)
     log(f"weakly driven band D={D} n={H.shape[0]} V={V}")
     _check(H, mmf.floquet_half_bandwidth(p))
+
+
+def test_band_served_two_level_request():
+    """A request of the serving stream (two levels, one drive, order 3894) whose
+    bulge decays to columns with zero squares: finite eigenpairs, residual and
+    orthogonality as in the file's common bounds, trace and Frobenius norm."""
+    torch, mmf = require_gpu()
+    p = next(q for _, q, _, _ in cfg5_serving() if q.D == 2 and len(q.omega) == 1 and 2 * (2 * int(q.N[0]) + 1) == 3894)
+    dp = mmf.DeviceProblem(p)
+    n = dp.M
+    log(f"band eigh of a served request M={n}")
+    H = mmf.build_floquet(dp)
+    A = H.T.clone()                            # H_F in torch's row-major order
+    w, Pt, info = mmf.eigh_band(H, mmf.floquet_half_bandwidth(p))
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    Phi = Pt.T
+    hn = float(torch.linalg.vector_norm(A))
+    assert float(torch.linalg.vector_norm(A @ Phi - Phi * w)) / hn < 1e-12 * n / 100
+    assert float((Phi.conj().T @ Phi - torch.eye(n, dtype=torch.complex128, device="cuda")).abs().max()) < 1e-12 * n / 100
+    assert abs(float(w.sum()) - float(A.diagonal().real.sum())) < 1e-12 * hn * n / 100
+    assert abs(float(w.square().sum().sqrt()) - hn) < 1e-12 * hn * n / 100

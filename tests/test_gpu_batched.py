@@ -49,6 +49,8 @@ def test_batched_equals_single_calls(prec):
         assert torch.equal(Pts[k], P1), f"eigenvectors differ from the single call, n={n}"
 
 
+# (280 workgroups of 64 rows: since the line of the narrow form lies at 512, both
+# sides take the wide one here; test_batched_equals_single_with_narrow_finish)
 def test_batched_equals_single_across_kernel_forms():
     """Orders whose single reductions take other kernel forms than the batch:
     strips of two tiles beside single tiles, narrow against wide workgroups

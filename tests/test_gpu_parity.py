@@ -285,8 +285,8 @@ def test_hetrd_defining_identity(n):
     assert np.abs(Q @ T @ Q.conj().T - A).max() < 1e-13 * scale * max(1, n / 10)
 
 
-# edges of the LDS tail (order 92, panels of 32) and of the 64-row tiles, and
-# the first order whose strips hold two tiles (more than 512 interior tiles)
+# edges of the register tail (128 rows, panels of 32) and of the 64-row tiles (all
+# single tiles: strips of two begin at order 1088, test_hetrd_strip_edges)
 @pytest.mark.parametrize("n", [91, 92, 93, 124, 125, 127, 128, 129, 156, 157, 191, 192, 193, 321])
 @pytest.mark.parametrize("pad", [0, 3])
 def test_hetrd_tail_and_tile_edges(n, pad):
